@@ -324,9 +324,10 @@ int lda_solve(const void* X, const int32_t* labels, int64_t n, int d,
  * SRP_F32 or SRP_F64).  Limits: 1 <= n_rows < 2^31, 1 <= n_cols <= 8192,
  * nnz < 2^31.  Every entry point checks the structure on the device first
  * and returns SRP_EINVAL for a malformed matrix.  All arithmetic on the
- * data is FP64 (the F32 values are widened).  The library builds a
- * column-major copy of each matrix for the products A^T P (nnz index and
- * value words, from its workspace).
+ * data is FP64 (the F32 values are widened).  The products A^T P
+ * are summed from the rows; where that does not pay (more than 2048 columns,
+ * or a solve on few rows) from a column-major copy (nnz index and value
+ * words, from the library's workspace).
  */
 typedef struct srp_csr {
   int64_t n_rows;

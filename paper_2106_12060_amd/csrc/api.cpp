@@ -218,7 +218,8 @@ int srp_countsketch_csr(const srp_csr* A, int s, uint64_t seed, double* out, voi
   SRP_TRY(device_alloc(&ws.p, bytes, st));
   Arena ar{(char*)ws.p, bytes, 0};
   int* bad = ar.take<int>(4);
-  SRP_TRY(csr_check(v, "A", bad, st));
+  const char* const name = "A";
+  SRP_TRY(csr_check(1, &v, &name, bad, st));
   SRP_TRY(countsketch_csr_run(v, s, seed, out, nullptr, 0, nullptr, ar, st));
   return finish(st);
 }
@@ -239,6 +240,10 @@ int srp_gram_pass_csr(const srp_csr* A0, const srp_csr* A1, int k, const double*
   size_t scr = 0;
   for (int b = 0; b < nb; ++b) {
     SRP_REQUIRE(v[b].n >= 1 && v[b].d >= 1, "bad sizes");
+    if (csr_tsum_ok(v[b], ldp)) {
+      bytes += csr_tsum_bytes(v[b], ldp);
+      continue;
+    }
     bytes += csc_bytes(v[b]) + csc_partial_bytes(v[b], ldp);
     scr = std::max(scr, csc_scratch_bytes(v[b]));
   }
@@ -246,24 +251,28 @@ int srp_gram_pass_csr(const srp_csr* A0, const srp_csr* A1, int k, const double*
   SRP_TRY(device_alloc(&ws.p, bytes, st));
   Arena ar{(char*)ws.p, bytes, 0};
   int* bad = ar.take<int>(4);
-  SRP_TRY(csr_check(v[0], "A0", bad, st));
-  if (A1) SRP_TRY(csr_check(v[1], "A1", bad, st));
+  const char* const names[2] = {"A0", "A1"};
+  SRP_TRY(csr_check(nb, v, names, bad, st));
   double* P = ar.take<double>((size_t)v[0].n * ldp);
   CscView c[2];
   char* sbase = ar.base + ar.used;
   ar.used += (scr + 255) & ~size_t(255);
   double* part[2] = {nullptr, nullptr};
   for (int b = 0; b < nb; ++b) {
+    const bool rows = csr_tsum_ok(v[b], ldp);
     Arena t{sbase, scr, 0};
-    SRP_TRY(csc_build(v[b], &c[b], ar, t, st));
-    part[b] = (double*)ar.take<char>(csc_partial_bytes(v[b], ldp));
+    if (!rows) SRP_TRY(csc_build(v[b], &c[b], ar, t, st));
+    part[b] = (double*)ar.take<char>(rows ? csr_tsum_bytes(v[b], ldp) : csc_partial_bytes(v[b], ldp));
     if (!part[b]) { set_error("workspace layout overflow"); return SRP_ENOMEM; }
   }
   const double* Wb[2] = {W0, W1};
   double* Jb[2] = {J0, J1};
   for (int b = 0; b < nb; ++b)
     SRP_TRY(csr_times_dense(v[b], Wb[b], k, k, P + b * k, ldp, nullptr, nullptr, nullptr, st));
-  for (int b = 0; b < nb; ++b) SRP_TRY(csc_times_dense(c[b], P, ldp, ldp, Jb[b], ldp, part[b], nullptr, st));
+  for (int b = 0; b < nb; ++b) {
+    if (csr_tsum_ok(v[b], ldp)) SRP_TRY(csr_tsum(v[b], P, ldp, ldp, Jb[b], ldp, part[b], nullptr, st));
+    else SRP_TRY(csc_times_dense(c[b], P, ldp, ldp, Jb[b], ldp, part[b], nullptr, st));
+  }
   return finish(st);
 }
 

@@ -149,11 +149,9 @@ struct CscView {
 // Widest CSR input: the CountSketch keeps one bucket's row of d doubles in
 // LDS.
 constexpr int kCsrMaxCols = 8192;
-// Sets *bad (device) to 1 if A is not a well-formed CSR matrix.
-int csr_validate(const CsrView& A, int* bad, hipStream_t st);
-// Size and pointer checks, then csr_validate (bad: one device int);
-// synchronises st; SRP_EINVAL naming `name` on failure.
-int csr_check(const CsrView& A, const char* name, int* bad, hipStream_t st);
+// Size, pointer and structure checks of `count` matrices (bad: one device
+// int); synchronises st once; SRP_EINVAL naming the matrix on failure.
+int csr_check(int count, const CsrView* A, const char* const* names, int* bad, hipStream_t st);
 size_t csc_bytes(const CsrView& A);
 size_t csc_scratch_bytes(const CsrView& A);
 int csc_build(const CsrView& A, CscView* out, Arena& keep, Arena& scratch, hipStream_t st);
@@ -162,6 +160,13 @@ int csc_build(const CsrView& A, CscView* out, Arena& keep, Arena& scratch, hipSt
 // A set *done makes the launch a no-op.
 int csr_times_dense(const CsrView& A, const double* D, int ldd, int w, double* out, int ldo, const double* sub,
                     const int32_t* labels, const int* done, hipStream_t st);
+// out (d x w) = A^T P straight from the rows, for the widths csr_tsum_ok
+// takes (partial: csr_tsum_bytes(A, w) bytes); wider matrices go through
+// the column copy below.
+bool csr_tsum_ok(const CsrView& A, int w);
+size_t csr_tsum_bytes(const CsrView& A, int w);
+int csr_tsum(const CsrView& A, const double* P, int ldp, int w, double* out, int ldo, double* partial,
+             const int* done, hipStream_t st);
 // The columns' products go through per-segment partials (partial:
 // csc_partial_bytes(A, w) bytes), summed per column in segment order.
 int64_t csc_max_segments(const CsrView& A);

@@ -5,16 +5,16 @@
 //
 // Input: row-major CSR (row pointers int64, column indices int32 strictly
 // increasing within a row, values F32 or F64).  The products A W read the
-// rows.  The products A^T P read the columns: a CSC copy is built once per
-// solve by a stable counting sort (column histograms per chunk of rows, a
-// scan per column over the chunks, placement row by row inside a chunk),
-// so every column lists its rows in ascending order.  Every output is then
-// a sum in a fixed order (the kernels are bitwise reproducible), and with
-// the zero entries left out it is the same sum, in the same order, as over
-// the dense matrix.  All arithmetic is FP64.
+// rows.  The products A^T P sort blocks of rows by column in LDS
+// (k_csr_tsum), or read the columns of a CSC copy, built once per solve by
+// a stable counting sort (column histograms per chunk of rows, a scan per
+// column over the chunks, placement row by row inside a chunk), so every
+// column lists its rows in ascending order.  Every output is a sum in a
+// fixed order (the kernels are bitwise reproducible).  All arithmetic is FP64.
 #include "common.hpp"
 #include "kernels.hpp"
 
+#include <algorithm>
 #include <cmath>
 
 namespace srp {
@@ -26,27 +26,38 @@ constexpr int kCscSeg = 256;
 // ------------------------------------------------------- validation
 // Every row: 0 <= ptr[i] <= ptr[i+1] <= nnz, ptr[0] = 0, ptr[n] = nnz,
 // columns in [0, d) and strictly increasing.  Entries are only read inside
-// [0, nnz), whatever the pointers hold.
-__global__ void k_csr_check(int64_t n, int d, int64_t nnz, const int64_t* __restrict__ ptr,
-                            const int32_t* __restrict__ idx, int* bad) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int64_t p0 = ptr[i], p1 = ptr[i + 1];
-  bool ok = p0 >= 0 && p0 <= p1 && p1 <= nnz && (i != 0 || p0 == 0) && (i != n - 1 || p1 == nnz);
-  if (ok) {
-    int prev = -1;
-    for (int64_t e = p0; e < p1; ++e) {
-      const int j = idx[e];
-      if (j <= prev || j >= d) { ok = false; break; }
-      prev = j;
+// [0, nnz), whatever the pointers hold.  Sixteen lanes take a row's entries
+// together, so the indexes stream (one thread a row: 141 us for 22M entries
+// in 1M rows, its loads a cache line apart; so: 62 us); a wave walks
+// kCheckRows rows, four at a time.
+constexpr int kCheckRows = 64;
+__global__ void __launch_bounds__(256) k_csr_check(int64_t n, int d, int64_t nnz, const int64_t* __restrict__ ptr,
+                                                   const int32_t* __restrict__ idx, int bit, int* bad) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+  const int64_t base = (blockIdx.x * 4ll + (threadIdx.x >> 6)) * kCheckRows;
+  bool ok = true;
+#pragma unroll 4
+  for (int q = 0; q < kCheckRows; q += 4) {
+    const int64_t i = base + q + g;
+    if (i >= n) break;
+    const int64_t p0 = ptr[i], p1 = ptr[i + 1];
+    if (p0 >= 0 && p0 <= p1 && p1 <= nnz && (i != 0 || p0 == 0) && (i != n - 1 || p1 == nnz)) {
+      for (int64_t e = p0 + c; e < p1; e += 16) {
+        const int j = idx[e];
+        const int prev = e > p0 ? idx[e - 1] : -1;
+        if (j <= prev || j < 0 || j >= d) ok = false;
+      }
+    } else {
+      ok = false;
     }
   }
-  if (!ok) atomicOr(bad, 1);
+  if (!ok) atomicOr(bad, bit);
 }
 
-int csr_validate(const CsrView& A, int* bad, hipStream_t st) {
-  const unsigned blocks = (unsigned)((A.n + 255) / 256);
-  hipLaunchKernelGGL(k_csr_check, dim3(blocks), dim3(256), 0, st, A.n, A.d, A.nnz, A.ptr, A.idx, bad);
+// A malformed matrix sets `bit` in *bad.
+int csr_validate(const CsrView& A, int bit, int* bad, hipStream_t st) {
+  const unsigned blocks = (unsigned)((A.n + 4 * kCheckRows - 1) / (4 * kCheckRows));
+  hipLaunchKernelGGL(k_csr_check, dim3(blocks), dim3(256), 0, st, A.n, A.d, A.nnz, A.ptr, A.idx, bit, bad);
   SRP_LAUNCH_CHECK();
   return SRP_OK;
 }
@@ -344,6 +355,426 @@ __global__ void __launch_bounds__(256) k_spmm_seg_sum(int w, const int* __restri
   }
 }
 
+// The same products with D in LDS (d x w doubles, the row pitch rounded up
+// to a pair of columns): L lanes take a row, two columns each, and walk its
+// entries four at a time in stored order.  An entry costs one 16-byte LDS
+// read a lane; k_spmm_rows gathers D through the vector cache and broadcasts
+// each entry by three lane shuffles (175 us for 22M entries in 1M rows, 8
+// columns; so: 108 us,
+// bound by the LDS reads).
+template <class T> struct SpVec4;
+template <> struct SpVec4<float> { typedef float type __attribute__((ext_vector_type(4), aligned(4))); };
+template <> struct SpVec4<double> { typedef double type __attribute__((ext_vector_type(4), aligned(8))); };
+typedef int32_t sp_i32x4 __attribute__((ext_vector_type(4), aligned(4)));
+constexpr int kRowsThreads = 1024;
+
+template <class T, int L>
+__global__ void __launch_bounds__(kRowsThreads) k_spmm_rows_lds(int64_t rows, int64_t nnz, int d,
+                                                               const int64_t* __restrict__ ptr,
+                                                               const int32_t* __restrict__ idx,
+                                                               const T* __restrict__ val,
+                                                               const double* __restrict__ D, int ldd, int w,
+                                                               double* __restrict__ out, int ldo,
+                                                               const double* __restrict__ sub,
+                                                               const int32_t* __restrict__ labels,
+                                                               const int* __restrict__ done) {
+  if (done && *done) return;
+  extern __shared__ double dl[];
+  const int wp = (w + 1) & ~1;
+  for (int e = threadIdx.x; e < d * wp; e += kRowsThreads) {
+    const int j = e / wp, c = e - j * wp;
+    dl[e] = c < w ? D[(int64_t)j * ldd + c] : 0.0;
+  }
+  __syncthreads();
+  const int c = threadIdx.x % L;
+  const bool on = 2 * c < w;
+  const double* dc = dl + (on ? 2 * c : 0);
+  auto load = [&](int64_t e, sp_i32x4& j, typename SpVec4<T>::type& v) __attribute__((always_inline)) {
+    if (e + 4 <= nnz) {
+      j = *reinterpret_cast<const sp_i32x4*>(idx + e);
+      v = *reinterpret_cast<const typename SpVec4<T>::type*>(val + e);
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        j[t] = e + t < nnz ? idx[e + t] : 0;
+        v[t] = e + t < nnz ? val[e + t] : T(0);
+      }
+    }
+  };
+  constexpr int RPB = kRowsThreads / L;
+  for (int64_t r = blockIdx.x * (int64_t)RPB + threadIdx.x / L; r < rows; r += (int64_t)gridDim.x * RPB) {
+    const int64_t p0 = ptr[r], p1 = ptr[r + 1];
+    double a0 = 0.0, a1 = 0.0;
+    sp_i32x4 j, jn;
+    typename SpVec4<T>::type v, vn;
+    if (p0 < p1) load(p0, j, v);
+    for (int64_t e = p0; e < p1; e += 4) {
+      if (e + 4 < p1) load(e + 4, jn, vn);
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (e + t < p1) {
+          const double2 q = *reinterpret_cast<const double2*>(dc + j[t] * wp);
+          const double vt = to_f64((T)v[t]);
+          a0 += vt * q.x;
+          a1 += vt * q.y;
+        }
+      j = jn;
+      v = vn;
+    }
+    if (on) {
+      if (labels) {
+        a0 -= sub[(int64_t)labels[r] * w + 2 * c];
+        if (2 * c + 1 < w) a1 -= sub[(int64_t)labels[r] * w + 2 * c + 1];
+      }
+      out[r * ldo + 2 * c] = a0;
+      if (2 * c + 1 < w) out[r * ldo + 2 * c + 1] = a1;
+    }
+  }
+}
+
+// ------------------------------------- transposed products from the rows
+// out (d x w) = A^T P without a column copy.  A workgroup takes blocks of at
+// most kTsRows rows (and kTsEntries entries), sorts a block's entries by
+// column in LDS and then gathers: a group of L lanes owns NC columns of A,
+// two P columns a lane, and adds a column's entries in row order to its
+// registers, P's rows of the block read from LDS.  The sort is a counting
+// sort that needs no order among the threads: each entry sets its row's bit
+// in its column's masks, the masks' bit counts scanned over the columns are
+// the offsets, and an entry's place is its column's offset plus the bits
+// below its own.  Every sum is in a fixed order (rows ascending inside a
+// workgroup's range, then the ranges in order), so the result is the same
+// bit for bit every time.
+//
+// Entries and P stream once.  22M entries in 1M rows, 1000 columns, 16
+// columns of P: 347 us and 13 for the ranges' sums, bound by the issue of the
+// gather's instructions and the LDS latency of its short column runs.  The
+// column copy it replaces takes 1053 us to place, then 466 us of 128-byte
+// gathers of P at the last-level cache's rate and 62 us of sums; adding row
+// after row into LDS sums takes 792 us (random FP64 LDS adds, about 29
+// cycles for 44 lanes), one P column a lane instead of two 590 us.  Taken up to kTsMaxCols columns, where the
+// masks and two columns' sums a lane still fit; wider matrices go through
+// the copy.
+constexpr int kTsMaxCols = 2048;
+constexpr int kTsThreads = 512;
+constexpr int kTsRows = 128;
+constexpr int kTsEntries = 4096;   // at least one row of any matrix taken
+static_assert(kTsEntries >= kTsMaxCols && kTsRows == 128, "a row fits; four mask words a column");
+
+// A sorted entry: its value and its row in the block.
+template <class T> struct TsEntry;
+template <> struct alignas(8) TsEntry<float> { float v; int row; };
+template <> struct alignas(16) TsEntry<double> { double v; int row; };
+
+template <class T>
+static size_t ts_lds(int d, int GL) {
+  return (size_t)kTsRows * GL * 8 + (size_t)kTsEntries * sizeof(TsEntry<T>) + (size_t)d * 16 +
+         (size_t)(d + 1 + kTsRows + 1 + 8) * 4;
+}
+
+// First row of range q of G: ranges of equal weight, an entry counting 1
+// and a row 8.
+__device__ __forceinline__ int64_t ts_row(int64_t n, int64_t nnz, const int64_t* __restrict__ ptr, int q, int G,
+                                          int lane) {
+  if (q <= 0) return 0;
+  if (q >= G) return n;
+  const int64_t target = (int64_t)((double)(nnz + 8 * n) * q / G);
+  // smallest r with ptr[r] + 8 r >= target: lo <= r <= hi, 64 probes a step
+  int64_t lo = 0, hi = n;
+  while (lo < hi) {
+    const int64_t step = (hi - lo + 63) / 64;
+    const int64_t r = min(hi, lo + step * (int64_t)lane);   // lane 0 probes lo
+    const int k = __popcll(__ballot(ptr[r] + 8 * r < target));   // probes below the target: a prefix
+    if (k == 0) return lo;
+    if (k < 64) hi = min(hi, lo + step * (int64_t)k);
+    lo = min(hi, lo + step * (int64_t)(k - 1) + 1);
+  }
+  return lo;
+}
+
+template <class T, int L, int NC>
+__global__ void __launch_bounds__(kTsThreads, NC <= 16 ? 4 : 2) k_csr_tsum(int64_t n, int d, int64_t nnz,
+                                                         const int64_t* __restrict__ ptr,
+                                                         const int32_t* __restrict__ idx, const T* __restrict__ val,
+                                                         const double* __restrict__ P, int ldp, int w, int G,
+                                                         double* __restrict__ partial, const int* __restrict__ done) {
+  if (done && *done) return;
+  constexpr int RB = kTsRows, NT = kTsThreads, NGR = NT / L, GL = 2 * L;
+  extern __shared__ double ts_smem[];
+  double* pl = ts_smem;                                    // [RB][GL] rows of P
+  TsEntry<T>* ent = reinterpret_cast<TsEntry<T>*>(pl + RB * GL);     // entries by column, then row
+  uint32_t* mask = reinterpret_cast<uint32_t*>(ent + kTsEntries);    // [4][d] row bits
+  int* off = reinterpret_cast<int*>(mask + 4 * d);         // [d + 1]
+  int* pt = off + d + 1;                                   // [RB + 1] row starts
+  int* wsum = pt + RB + 1;                                 // [8]
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int w0 = blockIdx.y * GL, wt = min(GL, w - w0);
+  const int64_t r0 = ts_row(n, nnz, ptr, blockIdx.x, G, lane), r1 = ts_row(n, nnz, ptr, blockIdx.x + 1, G, lane);
+  double2 acc[NC];
+#pragma unroll
+  for (int i = 0; i < NC; ++i) acc[i] = make_double2(0.0, 0.0);
+  const int g = tid / L, c = 2 * (tid % L);  // gather: column group, first P column
+  const int g16 = tid >> 4, l16 = tid & 15; // sort: sixteen lanes a row
+  int64_t e0 = ptr[r0];                                           // the block's first entry
+  int64_t nptr = r0 < r1 ? ptr[min(r0 + min(tid, RB), r1)] : 0;   // the next block's row starts
+  for (int64_t rb = r0; rb < r1;) {
+    int nr = (int)min<int64_t>(RB, r1 - rb);
+    if (tid <= nr) pt[tid] = (int)(nptr - e0);
+    for (int q = tid; q < 4 * d; q += NT) mask[q] = 0;
+    __syncthreads();
+    // the rows of the block: those that end within kTsEntries (pt ascends)
+    nr = __popcll(__ballot(lane < nr && pt[min(lane, nr - 1) + 1] <= kTsEntries)) +
+         __popcll(__ballot(lane + 64 < nr && pt[min(lane + 64, nr - 1) + 1] <= kTsEntries));
+    const int ne = pt[nr];
+    const int32_t* __restrict__ ib = idx + e0;
+    const T* __restrict__ vb = val + e0;
+    // sixteen lanes a row, four rows each: the first 32 entries of a row are
+    // loaded together and stay in registers, the rest follow one by one
+    constexpr int RS = RB / (NT / 16);
+    int jj[RS][2];
+    T vv[RS][2];
+    bool in[RS][2];
+#pragma unroll
+    for (int a = 0; a < RS; ++a)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int r = g16 + a * (NT / 16), rc = min(r, nr - 1), q = pt[rc] + l16 + 16 * h;
+        in[a][h] = r < nr && q < pt[rc + 1];
+        const int qc = in[a][h] ? q : 0;
+        jj[a][h] = ne > 0 ? ib[qc] : 0;
+        vv[a][h] = ne > 0 ? vb[qc] : T(0);
+      }
+    for (int q = tid; q < nr * GL; q += NT) {
+      const int r = q / GL, pc = q % GL;
+      pl[q] = pc < wt ? P[(rb + r) * ldp + w0 + pc] : 0.0;
+    }
+#pragma unroll
+    for (int a = 0; a < RS; ++a) {
+      const int r = g16 + a * (NT / 16), base = (r >> 5) * d;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if (in[a][h]) atomicOr(&mask[base + jj[a][h]], 1u << (r & 31));
+      if (r < nr)
+        for (int q = pt[r] + l16 + 32; q < pt[r + 1]; q += 16) atomicOr(&mask[base + ib[q]], 1u << (r & 31));
+    }
+    __syncthreads();
+    {   // off = exclusive scan of the columns' counts
+      const int per = (d + NT - 1) / NT, j0 = min(d, tid * per), j1 = min(d, j0 + per);
+      int sum = 0;
+      for (int j = j0; j < j1; ++j)
+        sum += __popc(mask[j]) + __popc(mask[d + j]) + __popc(mask[2 * d + j]) + __popc(mask[3 * d + j]);
+      int incl = sum;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += u;
+      }
+      if (lane == 63) wsum[wv] = incl;
+      __syncthreads();
+      int run = incl - sum;
+      for (int k = 0; k < wv; ++k) run += wsum[k];
+      for (int j = j0; j < j1; ++j) {
+        off[j] = run;
+        run += __popc(mask[j]) + __popc(mask[d + j]) + __popc(mask[2 * d + j]) + __popc(mask[3 * d + j]);
+      }
+      if (tid == NT - 1) off[d] = run;
+    }
+    __syncthreads();
+    auto place = [&](int r, int j, T v) __attribute__((always_inline)) {
+      const int wd = r >> 5;
+      int pos = off[j] + __popc(mask[wd * d + j] & ((1u << (r & 31)) - 1u));
+      for (int k = 0; k < wd; ++k) pos += __popc(mask[k * d + j]);
+      ent[pos] = TsEntry<T>{v, r};
+    };
+#pragma unroll
+    for (int a = 0; a < RS; ++a) {
+      const int r = g16 + a * (NT / 16);
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if (in[a][h]) place(r, jj[a][h], vv[a][h]);
+      if (r < nr)
+        for (int q = pt[r] + l16 + 32; q < pt[r + 1]; q += 16) place(r, ib[q], vb[q]);
+    }
+    rb += nr;
+    e0 += ne;
+    nptr = ptr[min(rb + min(tid, RB), r1)];
+    __syncthreads();
+    // Four columns of the group at a time: first the columns with more than
+    // four entries left, four entries at a time, then an entry of each.
+    // Reads past a column's entries take its first place and are not added.
+#pragma unroll
+    for (int i = 0; i < NC; i += 4) {
+      int q0[4], q1[4], most = 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int j = (i + u) * NGR + g;
+        q0[u] = j < d ? off[j] : 0;
+        q1[u] = j < d ? off[j + 1] : 0;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        for (; q1[u] - q0[u] > 4; q0[u] += 4) {
+          TsEntry<T> t[4];
+          double2 p[4];
+#pragma unroll
+          for (int h = 0; h < 4; ++h) t[h] = ent[q0[u] + h];
+#pragma unroll
+          for (int h = 0; h < 4; ++h) p[h] = *reinterpret_cast<const double2*>(&pl[t[h].row * GL + c]);
+#pragma unroll
+          for (int h = 0; h < 4; ++h) {
+            acc[i + u].x = fma(to_f64(t[h].v), p[h].x, acc[i + u].x);
+            acc[i + u].y = fma(to_f64(t[h].v), p[h].y, acc[i + u].y);
+          }
+        }
+        most = max(most, q1[u] - q0[u]);
+      }
+      for (int s = 0; s < most; ++s) {
+        TsEntry<T> t[4];
+        double2 p[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) t[u] = ent[q0[u] + s < q1[u] ? q0[u] + s : 0];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          p[u] = *reinterpret_cast<const double2*>(&pl[(q0[u] + s < q1[u] ? t[u].row : 0) * GL + c]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (q0[u] + s < q1[u]) {
+            acc[i + u].x = fma(to_f64(t[u].v), p[u].x, acc[i + u].x);
+            acc[i + u].y = fma(to_f64(t[u].v), p[u].y, acc[i + u].y);
+          }
+      }
+    }
+    __syncthreads();
+  }
+  double* out = partial + ((int64_t)blockIdx.y * G + blockIdx.x) * d * GL;
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    const int j = i * NGR + g;
+    if (j < d) *reinterpret_cast<double2*>(&out[(int64_t)j * GL + c]) = acc[i];
+  }
+}
+
+// out[j][GL y + c] = the ranges' sums in range order: four groups of threads
+// take a quarter of the ranges each, sixteen loads in flight, then the
+// quarters are added.
+__global__ void __launch_bounds__(256) k_csr_tsum_add(const double* __restrict__ partial, int G, int GL, int d, int w,
+                                                      double* __restrict__ out, int ldo,
+                                                      const int* __restrict__ done) {
+  if (done && *done) return;
+  __shared__ double q4[4][64];
+  const int grp = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int64_t count = (int64_t)d * GL, i = blockIdx.x * 64ll + l;
+  const double* part = partial + (int64_t)blockIdx.y * G * count;
+  const int per = (G + 3) / 4, z0 = min(G, grp * per), z1 = min(G, z0 + per);
+  double v = 0.0;
+  if (i < count) {
+    int z = z0;
+    for (; z + 16 <= z1; z += 16) {
+      double t[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) t[u] = part[(z + u) * count + i];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v += t[u];
+    }
+    for (; z < z1; ++z) v += part[z * count + i];
+  }
+  q4[grp][l] = v;
+  __syncthreads();
+  if (grp == 0 && i < count) {
+    const int64_t j = i / GL;
+    const int col = blockIdx.y * GL + (int)(i - j * GL);
+    if (col < w) out[j * ldo + col] = ((q4[0][l] + q4[1][l]) + q4[2][l]) + q4[3][l];
+  }
+}
+
+// P columns of a column group: sixteen at most.
+static int ts_lanes(int w) { return w <= 4 ? 4 : w <= 8 ? 8 : 16; }
+// Row ranges: two workgroups a CU, at least one block of rows each.
+static int ts_ranges(const CsrView& A) {
+  return (int)std::min<int64_t>(2ll * num_cus(), std::max<int64_t>(1, (A.n + kTsRows - 1) / kTsRows));
+}
+
+bool csr_tsum_ok(const CsrView& A, int w) { return w >= 1 && A.d <= kTsMaxCols; }
+
+size_t csr_tsum_bytes(const CsrView& A, int w) {
+  const int GL = ts_lanes(w), tiles = (w + GL - 1) / GL;
+  return bytes_of<double>((size_t)tiles * ts_ranges(A) * A.d * GL);
+}
+
+template <class T, int L>
+static int tsum_launch(const CsrView& A, const double* P, int ldp, int w, double* partial, const int* done,
+                       hipStream_t st) {
+  constexpr int GL = 2 * L;
+  const int G = ts_ranges(A);
+  const dim3 grid((unsigned)G, (unsigned)((w + GL - 1) / GL));
+  const size_t lds = ts_lds<T>(A.d, GL);
+  const int nc = (A.d + kTsThreads / L - 1) / (kTsThreads / L);   // columns of A per group
+#define SRP_TS_CASE(NC_)                                                                                            \
+  if (nc <= NC_) {                                                                                                  \
+    SRP_TRY(allow_dynamic_lds((const void*)k_csr_tsum<T, L, NC_>, ts_lds<T>(kTsMaxCols, GL)));                      \
+    hipLaunchKernelGGL((k_csr_tsum<T, L, NC_>), grid, dim3(kTsThreads), lds, st, A.n, A.d, A.nnz, A.ptr, A.idx,     \
+                       (const T*)A.val, P, ldp, w, G, partial, done);                                               \
+    SRP_LAUNCH_CHECK();                                                                                             \
+    return SRP_OK;                                                                                                  \
+  }
+  SRP_TS_CASE(4)
+  SRP_TS_CASE(8)
+  if constexpr (L >= 4) { SRP_TS_CASE(16) }
+  if constexpr (L >= 8) { SRP_TS_CASE(32) }
+#undef SRP_TS_CASE
+  set_error("sparse transposed product: no instance for %d columns", A.d);
+  return SRP_EINVAL;
+}
+
+template <class T>
+static int tsum_dispatch(const CsrView& A, const double* P, int ldp, int w, double* partial, const int* done,
+                         hipStream_t st) {
+  switch (ts_lanes(w)) {
+    case 4: return tsum_launch<T, 2>(A, P, ldp, w, partial, done, st);
+    case 8: return tsum_launch<T, 4>(A, P, ldp, w, partial, done, st);
+    default: return tsum_launch<T, 8>(A, P, ldp, w, partial, done, st);
+  }
+}
+
+int csr_tsum(const CsrView& A, const double* P, int ldp, int w, double* out, int ldo, double* partial,
+             const int* done, hipStream_t st) {
+  SRP_REQUIRE(csr_tsum_ok(A, w), "sparse product width %d, %d columns", w, A.d);
+  if (A.dtype == SRP_F64) SRP_TRY(tsum_dispatch<double>(A, P, ldp, w, partial, done, st));
+  else SRP_TRY(tsum_dispatch<float>(A, P, ldp, w, partial, done, st));
+  const int GL = ts_lanes(w);
+  const dim3 grid((unsigned)(((int64_t)A.d * GL + 63) / 64), (unsigned)((w + GL - 1) / GL));
+  hipLaunchKernelGGL(k_csr_tsum_add, grid, dim3(256), 0, st, partial, ts_ranges(A), GL, A.d, w, out, ldo, done);
+  SRP_LAUNCH_CHECK();
+  return SRP_OK;
+}
+
+// D in LDS while it fits one workgroup a CU (two while it fits half).
+constexpr size_t kRowsLds = 150 * 1024;
+
+template <class T, int L>
+static int spmm_rows_lds_launch(const CsrView& A, const T* val, const double* D, int ldd, int w, double* out, int ldo,
+                                const double* sub, const int32_t* labels, const int* done, hipStream_t st) {
+  const size_t lds = (size_t)A.d * ((w + 1) & ~1) * 8;
+  const int per_cu = lds <= 76 * 1024 ? 2 : 1;
+  const int64_t rpb = kRowsThreads / L;
+  const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((A.n + rpb - 1) / rpb,
+                                                                         (int64_t)per_cu * num_cus()));
+  SRP_TRY(allow_dynamic_lds((const void*)k_spmm_rows_lds<T, L>, kRowsLds));
+  hipLaunchKernelGGL((k_spmm_rows_lds<T, L>), dim3(grid), dim3(kRowsThreads), lds, st, A.n, A.nnz, A.d, A.ptr, A.idx,
+                     val, D, ldd, w, out, ldo, sub, labels, done);
+  SRP_LAUNCH_CHECK();
+  return SRP_OK;
+}
+
+template <class T>
+static int spmm_rows_lds(const CsrView& A, const T* val, const double* D, int ldd, int w, double* out, int ldo,
+                         const double* sub, const int32_t* labels, const int* done, hipStream_t st) {
+  if (w <= 2) return spmm_rows_lds_launch<T, 1>(A, val, D, ldd, w, out, ldo, sub, labels, done, st);
+  if (w <= 4) return spmm_rows_lds_launch<T, 2>(A, val, D, ldd, w, out, ldo, sub, labels, done, st);
+  if (w <= 8) return spmm_rows_lds_launch<T, 4>(A, val, D, ldd, w, out, ldo, sub, labels, done, st);
+  if (w <= 16) return spmm_rows_lds_launch<T, 8>(A, val, D, ldd, w, out, ldo, sub, labels, done, st);
+  return spmm_rows_lds_launch<T, 16>(A, val, D, ldd, w, out, ldo, sub, labels, done, st);
+}
+
 template <class T>
 static int spmm_rows_launch(int64_t rows, const int64_t* ptr, const int32_t* idx, const T* val, const double* D,
                             int ldd, int w, double* out, int ldo, const double* sub, const int32_t* labels,
@@ -382,6 +813,14 @@ int csr_times_dense(const CsrView& A, const double* D, int ldd, int w, double* o
                     const int32_t* labels, const int* done, hipStream_t st) {
   SRP_REQUIRE(w >= 1 && w <= 64, "sparse product width %d outside 1..64", w);
   if (A.n <= 0) return SRP_OK;
+  // D in LDS pays once the rows fill a workgroup of it on every CU (below,
+  // the gathers' four times smaller workgroups spread the rows better)
+  const int64_t rpb = kRowsThreads / (w <= 2 ? 1 : w <= 4 ? 2 : w <= 8 ? 4 : w <= 16 ? 8 : 16);
+  if (w <= 32 && (size_t)A.d * ((w + 1) & ~1) * 8 <= kRowsLds && A.n >= rpb * num_cus()) {
+    if (A.dtype == SRP_F64)
+      return spmm_rows_lds(A, (const double*)A.val, D, ldd, w, out, ldo, sub, labels, done, st);
+    return spmm_rows_lds(A, (const float*)A.val, D, ldd, w, out, ldo, sub, labels, done, st);
+  }
   if (A.dtype == SRP_F64)
     return spmm_rows_launch(A.n, A.ptr, A.idx, (const double*)A.val, D, ldd, w, out, ldo, sub, labels, done, st);
   return spmm_rows_launch(A.n, A.ptr, A.idx, (const float*)A.val, D, ldd, w, out, ldo, sub, labels, done, st);
@@ -541,19 +980,22 @@ int fda_csr_stats_run(const CscView& A, int64_t n, int c, const int32_t* labels,
 
 namespace srp {
 
-int csr_check(const CsrView& A, const char* name, int* bad, hipStream_t st) {
-  SRP_REQUIRE(A.n >= 1 && A.n < (int64_t(1) << 31), "%s: rows out of range", name);
-  SRP_REQUIRE(A.d >= 1 && A.d <= kCsrMaxCols, "%s: need 1 <= columns <= %d", name, kCsrMaxCols);
-  SRP_REQUIRE(A.nnz >= 0 && A.nnz < (int64_t(1) << 31), "%s: nnz out of range", name);
-  SRP_REQUIRE(A.dtype == SRP_F32 || A.dtype == SRP_F64, "%s: values must be SRP_F32 or SRP_F64", name);
-  SRP_REQUIRE(A.ptr && (A.nnz == 0 || (A.idx && A.val)), "%s: null pointer", name);
+int csr_check(int count, const CsrView* A, const char* const* names, int* bad, hipStream_t st) {
   SRP_TRY(fill_i32(bad, 1, 0, st));
-  SRP_TRY(csr_validate(A, bad, st));
+  for (int q = 0; q < count; ++q) {
+    SRP_REQUIRE(A[q].n >= 1 && A[q].n < (int64_t(1) << 31), "%s: rows out of range", names[q]);
+    SRP_REQUIRE(A[q].d >= 1 && A[q].d <= kCsrMaxCols, "%s: need 1 <= columns <= %d", names[q], kCsrMaxCols);
+    SRP_REQUIRE(A[q].nnz >= 0 && A[q].nnz < (int64_t(1) << 31), "%s: nnz out of range", names[q]);
+    SRP_REQUIRE(A[q].dtype == SRP_F32 || A[q].dtype == SRP_F64, "%s: values must be SRP_F32 or SRP_F64", names[q]);
+    SRP_REQUIRE(A[q].ptr && (A[q].nnz == 0 || (A[q].idx && A[q].val)), "%s: null pointer", names[q]);
+    SRP_TRY(csr_validate(A[q], 1 << q, bad, st));
+  }
   int h = 0;
   SRP_HIP(hipMemcpyAsync(&h, bad, sizeof(int), hipMemcpyDeviceToHost, st));
   SRP_HIP(hipStreamSynchronize(st));
-  SRP_REQUIRE(!h, "%s is not a well-formed CSR matrix (row pointers, or columns in range and strictly increasing)",
-              name);
+  for (int q = 0; q < count; ++q)
+    SRP_REQUIRE(!(h >> q & 1), "%s is not a well-formed CSR matrix (row pointers, or columns in range and strictly "
+                "increasing)", names[q]);
   return SRP_OK;
 }
 

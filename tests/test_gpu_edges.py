@@ -47,3 +47,66 @@ def test_staging_group_edges(n, d, off):
     ref, sc = quant.fp8_stage(Xb.double().cpu().numpy())
     np.testing.assert_array_equal(scales.cpu().numpy(), sc)
     np.testing.assert_array_equal(codes.cpu().numpy(), ref)
+
+
+# blocks cut by rows (128) and by entries (4096), runs of empty rows, fewer
+# rows than a block, column groups of 4, 8 and 16 lanes and two tiles of
+# them, the widest matrix summed from the rows (2048 columns) and the first
+# that takes the column copy, D gathered and (from 1024 / lanes rows a CU) in LDS
+@pytest.mark.parametrize("n,d,nb,k,per_row,dt", [(1, 5, 1, 1, 3, np.float32), (63, 40, 2, 3, 35, np.float64),
+                                                 (5000, 129, 2, 16, 12, np.float32), (4097, 2048, 1, 5, 90, np.float32),
+                                                 (700, 2048, 1, 9, 1500, np.float64), (129, 1000, 2, 2, 30, np.float32),
+                                                 (900, 2049, 2, 2, 40, np.float64), (20600, 2049, 1, 2, 4, np.float64),
+                                                 (3000, 17, 1, 31, 0, np.float32),
+                                                 (70001, 33, 2, 7, 4, np.float64), (40003, 50, 1, 27, 5, np.float32)])
+def test_csr_products_edges(n, d, nb, k, per_row, dt):
+    """Integer entries and directions: every sum is exact, so the products
+    match bit for bit whatever the split."""
+    from oracle import sparse as osp
+    srp = _srp()
+    rng = np.random.default_rng(n + d)
+    blocks = []
+    for _ in range(nb):
+        counts = np.minimum(rng.poisson(per_row, n), d)
+        counts[rng.random(n) < 0.2] = 0
+        counts[n // 3: n // 3 + n // 4] = 0
+        counts[-1] = min(d, 3 * per_row)
+        ptr = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+        cols = np.concatenate([np.sort(rng.choice(d, c, replace=False)) for c in counts]) if ptr[-1] else np.zeros(0)
+        vals = rng.choice([-2.0, -1.0, 1.0, 2.0], size=int(ptr[-1])).astype(dt)
+        blocks.append((ptr, cols.astype(np.int32), vals, d))
+    Ws = [rng.integers(-3, 4, size=(d, k)).astype(np.float64) for _ in range(nb)]
+    want = osp.pass_csr(blocks, Ws)
+    on = [srp.Csr(*(torch.from_numpy(np.ascontiguousarray(a)).to(DEV) for a in b[:3]), d) for b in blocks]
+    wd = [torch.from_numpy(W).to(DEV) for W in Ws]
+    got = srp.srp_gram_pass_csr(on[0], wd[0], *((on[1], wd[1]) if nb == 2 else ()))
+    for g, w in zip(got, want):
+        np.testing.assert_array_equal(g.cpu().numpy(), w)
+
+
+@pytest.mark.parametrize("fault", ["decreasing", "repeat", "range", "negative", "end"])
+def test_csr_structure_refused(fault):
+    srp = _srp()
+    n, d = 300, 50
+    ptr = np.arange(0, 20 * n + 1, 20, dtype=np.int64)
+    cols = np.tile(np.arange(0, 40, 2, dtype=np.int32), n)
+    good = (ptr.copy(), cols.copy())
+    r = 207
+    if fault == "decreasing":
+        ptr[r] = ptr[r + 1] + 5
+    elif fault == "repeat":
+        cols[20 * r + 17] = cols[20 * r + 16]
+    elif fault == "range":
+        cols[20 * r + 19] = d
+    elif fault == "negative":
+        cols[20 * r] = -1
+    else:
+        ptr[n] -= 1
+    mk = lambda p, c: srp.Csr(torch.from_numpy(p).to(DEV), torch.from_numpy(c).to(DEV),
+                              torch.ones(20 * n, device=DEV), d)
+    W = torch.ones((d, 2), dtype=torch.float64, device=DEV)
+    srp.srp_gram_pass_csr(mk(*good), W, mk(*good), W)
+    for pair, name in (((mk(ptr, cols), mk(*good)), "A0"), ((mk(*good), mk(ptr, cols)), "A1")):
+        with pytest.raises(srp.SrpError, match=name) as e:
+            srp.srp_gram_pass_csr(pair[0], W, pair[1], W)
+        assert e.value.code == srp.SRP_EINVAL
