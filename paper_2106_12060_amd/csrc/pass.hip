@@ -30,6 +30,9 @@
 #include "common.hpp"
 #include "kernels.hpp"
 
+#include <algorithm>
+#include <type_traits>
+
 namespace srp {
 
 constexpr int kPassWaves = 8;
@@ -331,9 +334,12 @@ __device__ __forceinline__ void lds_only_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-template <int VEC>
+// NT: the non-temporal hint (data that no cache keeps until its next use).
+template <int VEC, bool NT = false>
 __device__ __forceinline__ void dma_row_chunk(__amdgpu_buffer_rsrc_t r, float* lds_dst, int voff) {
-  if constexpr (VEC == 4)
+  if constexpr (VEC == 4 && NT)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds_dst, 16, voff, 0, 0, 2);
+  else if constexpr (VEC == 4)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds_dst, 16, voff, 0, 0, 0);
   else
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds_dst, 4, voff, 0, 0, 0);
@@ -341,7 +347,7 @@ __device__ __forceinline__ void dma_row_chunk(__amdgpu_buffer_rsrc_t r, float* l
 
 __host__ __device__ constexpr int dma_pitch(int TT) { return ((TT * 16 + 31) / 32) * 32 + 4; }
 
-template <int NB, int TPB, int VEC>
+template <int TPB, int VEC>
 __global__ void __launch_bounds__(kF32Threads) k_pass_dma(const float* __restrict__ A0, const float* __restrict__ A1,
                                                           int64_t n, int d0, int d1, int k,
                                                           const float* __restrict__ Wp0,
@@ -350,23 +356,23 @@ __global__ void __launch_bounds__(kF32Threads) k_pass_dma(const float* __restric
   if (done && *done) return;
   constexpr int R = kDmaRows;
   constexpr int CH = 64 * VEC;
-  constexpr int NT = NB;                                        // [P_0 | P_1] tiles of the J phase
+  constexpr int NT = 2;                                         // [P_0 | P_1] tiles of the J phase
   using acc_t = f32x4;
   extern __shared__ float dsm[];
   const int T0 = (d0 + 15) >> 4;
-  const int T1 = NB == 2 ? ((d1 + 15) >> 4) : 0;
+  const int T1 = (d1 + 15) >> 4;
   const int TT = T0 + T1;
-  const int nch0 = (T0 * 16 + CH - 1) / CH, nch1 = NB == 2 ? (T1 * 16 + CH - 1) / CH : 0;
+  const int nch0 = (T0 * 16 + CH - 1) / CH, nch1 = (T1 * 16 + CH - 1) / CH;
   const int nch = nch0 + nch1;
   const int pitch = dma_pitch(kF32Waves * TPB);
   float* red = dsm + 2 * R * pitch;              // [waves][16 x 16]
-  float* pfull = red + kF32Waves * 256;          // [NB][R][17]
+  float* pfull = red + kF32Waves * 256;          // [2][R][17]
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, l16 = lane & 15;
   const __amdgpu_buffer_rsrc_t wr0 = make_rsrc(Wp0, (int64_t)T0 * 16 * 16 * 4);
-  const __amdgpu_buffer_rsrc_t wr1 = make_rsrc(NB == 2 ? Wp1 : Wp0, (int64_t)(NB == 2 ? T1 : T0) * 16 * 16 * 4);
+  const __amdgpu_buffer_rsrc_t wr1 = make_rsrc(Wp1, (int64_t)T1 * 16 * 16 * 4);
   const int wvoff = (g * 16 + l16) * 4;
 
   // Slot i of wave w is tile t = w + 16 i (TPB >= the tiles / 16); slots past
@@ -375,13 +381,13 @@ __global__ void __launch_bounds__(kF32Threads) k_pass_dma(const float* __restric
   // zeroes, in the P products, the lanes of MFMA rows that belong to the
   // other view (rows 0-7: A_0, rows 8-15: A_1).
   float wreg[TPB][4];
-  float keep[TPB];
+  uint32_t keep[TPB];
   acc_t acc[TPB][NT];
 #pragma unroll
   for (int i = 0; i < TPB; ++i) {
     const int t = w + kF32Waves * i;
-    const bool b1 = (NB == 2) && (t >= T0);
-    keep[i] = (NB == 1 || (l16 >> 3) == (int)b1) ? 1.f : 0.f;
+    const bool b1 = t >= T0;
+    keep[i] = (l16 >> 3) == (int)b1 ? ~0u : 0u;
     const int ct = b1 ? t - T0 : t;
 #pragma unroll
     for (int s2 = 0; s2 < 4; ++s2) {
@@ -407,10 +413,9 @@ __global__ void __launch_bounds__(kF32Threads) k_pass_dma(const float* __restric
     const int64_t row0 = (int64_t)rbk * R;
     const int rows = (int)(n - row0 < R ? n - row0 : R);
     const __amdgpu_buffer_rsrc_t r0 = make_rsrc(A0 + row0 * d0, (int64_t)rows * d0 * 4);
-    const __amdgpu_buffer_rsrc_t r1 =
-        NB == 2 ? make_rsrc(A1 + row0 * d1, (int64_t)rows * d1 * 4) : r0;
+    const __amdgpu_buffer_rsrc_t r1 = make_rsrc(A1 + row0 * d1, (int64_t)rows * d1 * 4);
     for (int j = w; j < nch; j += kF32Waves) {
-      const bool s1 = (NB == 2) && (j >= nch0);
+      const bool s1 = j >= nch0;
       const int jj = s1 ? j - nch0 : j;
       const int span = (s1 ? T1 : T0) * 16;
       const int o = min(jj * CH, span - CH);
@@ -445,8 +450,8 @@ __global__ void __launch_bounds__(kF32Threads) k_pass_dma(const float* __restric
     for (int i = 0; i < TPB; ++i) {
 #pragma unroll
       for (int s2 = 0; s2 < 4; ++s2) {
-        float a = xs[base_b + 16 * kF32Waves * i + 4 * s2];
-        if (NB == 2) a *= keep[i];
+        const float a = __builtin_bit_cast(
+            float, __builtin_bit_cast(uint32_t, xs[base_b + 16 * kF32Waves * i + 4 * s2]) & keep[i]);
         pacc[i & 1] = mfma16x16x4(a, wreg[i][s2], pacc[i & 1]);
       }
     }
@@ -454,7 +459,7 @@ __global__ void __launch_bounds__(kF32Threads) k_pass_dma(const float* __restric
 #pragma unroll
     for (int r = 0; r < 4; ++r) red[w * 256 + (4 * g + r) * 16 + l16] = pacc[0][r] + pacc[1][r];
     lds_only_barrier();
-    if (tid < NB * R * 16) {
+    if (tid < 2 * R * 16) {
       float v = 0.f;
 #pragma unroll
       for (int ww = 0; ww < kF32Waves; ++ww) v += red[ww * 256 + tid];
@@ -480,14 +485,14 @@ __global__ void __launch_bounds__(kF32Threads) k_pass_dma(const float* __restric
     boff = R * pitch - boff;
   }
   // epilogue: this workgroup's partial (rows = concatenated columns of A)
-  const int W_out = NB * k;
-  const int D = d0 + (NB == 2 ? d1 : 0);
+  const int W_out = 2 * k;
+  const int D = d0 + d1;
   float* out = partial + (int64_t)blockIdx.x * D * W_out;
 #pragma unroll
   for (int i = 0; i < TPB; ++i) {
     const int t = w + kF32Waves * i;
     if (t < TT) {
-      const bool b1 = (NB == 2) && (t >= T0);
+      const bool b1 = t >= T0;
       const int db = b1 ? d1 : d0;
       const int ct = b1 ? t - T0 : t;
       const int rowbase = b1 ? d0 : 0;
@@ -507,53 +512,47 @@ __global__ void __launch_bounds__(kF32Threads) k_pass_dma(const float* __restric
 }
 
 // ------------------------------------------------------------------
-// FP32, two views: the DMA-fed pass above with the narrow products on 4x4
-// matrix-core blocks (v_mfma_f32_4x4x1f32: sixteen independent 4 x 4 outer
-// products per instruction), which removes most of the zero padding that
-// 16 x 16 tiles carry for 8-row blocks and k <= 12:
-//   * P_b = A_b W_b (8 rows x k): waves 0-7 work on view 0, waves 8-15 on
-//     view 1.  A block is 4 rows x 4 direction columns of one tile over one
-//     of every four of its columns: the four 16-lane rows take four tiles,
-//     the four blocks of a row the four column phases, rows 0-3 and 4-7 are
-//     separate instructions.  The four tiles are summed in registers by
-//     lane-row swaps and the column phases by two DPP rotations, so each
-//     wave publishes one partial to the cross-wave sum.
-//   * J_b = A_b^T [P_0 | P_1]: whole 16-column tiles of [P_0 | P_1] on the
-//     16 x 16 x 4 products; the remaining 4-column groups on 4x4 blocks,
-//     one row of the block per instruction over four tiles at once (the
-//     16-lane rows take the tiles, the blocks of a row 4 of its columns).
-// [P_0 | P_1] is packed tight (2k columns; C4 = ceil(k / 2) groups of 4).
-// In the P products wave w takes tiles w % 8 + 8 (4 G + row) of view w / 8
-// (G < SV / 2); in the J products it owns SV tiles of each view (slot
-// i < SV: tile w + 16 i of view 0, slot SV + i: tile w + 16 i of view 1).
-// Tiles past a view's last have a zero direction operand and their J rows
-// are not stored.  The row-block stream (DMA loads, double buffer,
-// barriers) is that of k_pass_dma.
+// FP32, one or two views: the narrow products on 4x4 matrix-core blocks
+// (v_mfma_f32_4x4x1f32: sixteen independent 4 x 4 outer products per
+// instruction; 16 x 16 tiles would carry mostly zero padding for a few rows
+// and k columns), the two products of a block of R rows pipelined over two
+// sets of waves:
+//   * the loader wave moves the rows HBM -> LDS (buffer loads with the LDS
+//     flag) into a ring of four blocks.  A wave that issues loads stalls
+//     while the load queue is full, so none of the others does.
+//   * eight producer waves form P_b = A_b W_b: half of them take a view (all
+//     with one view) and own groups of four of its tiles; an instruction
+//     takes a group, 4 rows x 4 direction columns per tile over one of every
+//     four of its columns.  The four tiles are summed in registers by
+//     lane-row swaps and the column phases by two DPP rotations: one partial
+//     per wave, into LDS.
+//   * seven consumer waves add the producers' partials in wave order as they
+//     read them and accumulate J_b = A_b^T [P_0 | P_1] over runs of
+//     neighbouring tiles: whole 16-column tiles of [P_0 | P_1] on 16x16x4
+//     products, the remaining 4-column groups on 4x4 blocks, one row of the
+//     block per instruction over four tiles at once (the 16-lane rows take
+//     the tiles, the blocks of a row 4 of its columns).  [P_0 | P_1] is
+//     packed tight (C4 groups of 4).
+// In step i the loader issues block i + 2 and waits for block i + 1 (issued
+// a step earlier), the producers multiply block i and the consumers work on
+// block i - 1; one barrier per step.  R rows a block, by the width, so that
+// a step is 33 KB of LDS for every width and its fixed cost is spread alike.
+//
+// Bounds: the row stream up to about 8 direction columns of [P_0 | P_1]
+// (6.7 TB/s), past that the products: the producers' chain (LDS reads,
+// products, lane sums, partials) and the consumers' on the same SIMDs.
+// Measured, us, against one set of 16 waves that did both products in turn
+// (two barriers more a block, and 4-byte loads for odd widths):
+//   200000 x (1000 + 1000), k = 10   377 -> 335 (4.8 TB/s)   k = 3  250 -> 240
+//   100000 x 2000, k = 19            236 -> 220              k = 9  159 -> 143
+//   52345 x (531 + 347), k = 9       99 -> 59                20011 x (301 + 203), k = 8  24 -> 20
+//   100000 x (250 + 256), k = 10     121 -> 68               200000 x (64 + 50), k = 4   132 -> 58
 template <int N>
 __device__ __forceinline__ float dpp_row_ror(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + N, 0xF, 0xF, false));
 }
 __device__ __forceinline__ f32x4 mfma4x4(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0);
-}
-
-// Row pitch of the 4x4-block pass: 16 mod 64 floats, so that four rows of
-// 16 consecutive columns (the J-phase operand) fall on 64 distinct banks,
-// as do the P operands' column quadruples of one 16-lane row.
-__host__ __device__ constexpr int quad_pitch(int TPB) { return ((16 * 16 * TPB + 63) / 64) * 64 + 16; }
-
-// The matrix-core results in p are complete before the lane swaps below
-// read them (the swaps are inline assembly, outside the compiler's hazard
-// tracking): 19 wait states cover the longest result latency.
-template <int KH>
-__device__ __forceinline__ void xdl_settle(f32x4 (&p)[KH]) {
-  if constexpr (KH == 1) asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3" : "+v"(p[0]));
-  else if constexpr (KH == 2) asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3" : "+v"(p[0]), "+v"(p[1]));
-  else if constexpr (KH == 3) asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]));
-  else {
-    static_assert(KH == 4, "up to four accumulators");
-    asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]));
-  }
 }
 
 // Sums of the four values x[0..3] over the four 16-lane rows, scattered:
@@ -566,618 +565,431 @@ __device__ __forceinline__ void xdl_settle(f32x4 (&p)[KH]) {
 // adds reduce four values, against two swaps and three adds per value for
 // separate full sums.
 __device__ __forceinline__ float rows_scatter_sum(f32x4 x) {
-  float u0 = x[0], v0 = x[1], u1 = x[2], v1 = x[3];
-  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\tv_permlane32_swap_b32 %2, %3\n\ts_nop 1"
-      : "+v"(u0), "+v"(v0), "+v"(u1), "+v"(v1));
-  float p = u0 + v0, q = u1 + v1;
-  asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(p), "+v"(q));
-  return p + q;
+  auto u = [](float v) { return __builtin_bit_cast(uint32_t, v); };
+  auto f = [](uint32_t v) { return __builtin_bit_cast(float, v); };
+  const auto a = __builtin_amdgcn_permlane32_swap(u(x[0]), u(x[1]), false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(u(x[2]), u(x[3]), false, false);
+  const float p = f(a[0]) + f(a[1]), q = f(b[0]) + f(b[1]);
+  const auto c = __builtin_amdgcn_permlane16_swap(u(p), u(q), false, false);
+  return f(c[0]) + f(c[1]);
 }
 
-// The same settle for two rows of KG accumulators.
-template <int KG>
-__device__ __forceinline__ void xdl_settle2(f32x4 (&p)[2][KG]) {
-  if constexpr (KG == 1) asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3" : "+v"(p[0][0]), "+v"(p[1][0]));
-  else if constexpr (KG == 2)
-    asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3" : "+v"(p[0][0]), "+v"(p[0][1]), "+v"(p[1][0]), "+v"(p[1][1]));
-  else if constexpr (KG == 3)
-    asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3"
-                 : "+v"(p[0][0]), "+v"(p[0][1]), "+v"(p[0][2]), "+v"(p[1][0]), "+v"(p[1][1]), "+v"(p[1][2]));
-  else {
-    static_assert(KG == 4, "up to four accumulators per row group");
-    asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3"
-                 : "+v"(p[0][0]), "+v"(p[0][1]), "+v"(p[0][2]), "+v"(p[0][3]), "+v"(p[1][0]), "+v"(p[1][1]),
-                   "+v"(p[1][2]), "+v"(p[1][3]));
-  }
-}
+constexpr int kPipeProd = 8;    // producer waves: 0 .. 7
+constexpr int kPipeCons = 7;    // consumer waves: 8 .. 14; wave 15 loads
+constexpr int kPipeRing = 4;    // blocks of rows in LDS
 
-template <int SV, int C4>
-struct QuadShape {
-  static constexpr int TPB = 2 * SV;        // tile slots per wave
-  static constexpr int KG = (C4 + 1) / 2;   // 4-column groups of one view's P
-  static constexpr int JQ = C4 / 4;         // whole 16-column tiles of [P_0 | P_1]
-  static constexpr int JR = C4 % 4;         // remaining 4-column groups
-  static constexpr int NG = TPB / 4;        // 4-slot groups of the remainder products
-  static constexpr int PP = 4 * C4 + 1;     // row pitch of [P_0 | P_1] in LDS
-  static constexpr int PG = SV / 2;        // 4-tile groups of a wave's P products
-  static constexpr int RED = kDmaRows * 4 * KG;   // one P partial (8 rows x 4 KG)
-  // LDS pitch of the wave partials: 8 mod 32 floats, so that the four lanes
-  // of a reducing quad (partials 2 apart) fall on different banks
-  static constexpr int REDP = RED + 8;
+// R rows a block (4, 8 or 16 for up to 128, 64 or 32 tiles of [A_0 | A_1]);
+// C4 4-column groups of [P_0 | P_1]; PG_ 4-tile groups a producer may hold.
+template <int NV, int R_, int C4, int PG_>
+struct PipeShape {
+  static constexpr int R = R_;
+  static constexpr int TILES = 512 / R;            // most tiles
+  static constexpr int SLOTS = (TILES + kPipeCons - 1) / kPipeCons;   // tiles of a consumer
+  static constexpr int NG = (SLOTS + 3) / 4;       // 4-tile groups of a consumer
+  static constexpr int KG = NV == 2 ? (C4 + 1) / 2 : C4;   // 4-column groups of one view's P
+  static constexpr int JQ = (C4 + 2) / 4;          // 16-column tiles of [P_0 | P_1]
+  static constexpr int JR = C4 % 4 == 1 ? 1 : 0;   // a single 4-column group past them (two or three: a tile)
+  static constexpr int PG = PG_;
+  static constexpr int NPV = kPipeProd / NV;       // producers of a view
+  // one view: a producer's groups that are whole in every wave (an instance
+  // of PG groups serves widths that need more than PG / 2 of them)
+  static constexpr int FULL = NV == 1 ? PG / 2 : 0;
+  // a producer's sums for 8 rows and KH direction-column groups at a time,
+  // its operands for BT tile groups at a time: beside its directions they
+  // take at most 96 of a wave's 128 registers.  One group at a time is read
+  // ahead of its use instead (AHEAD): 2000 columns, k = 19: 245 us without
+  static constexpr int RB = R < 8 ? R : 8;
+  static constexpr bool over(int kh, int b) { return 4 * KG * PG + RB * kh + b * RB > 96; }
+  static constexpr int KH = over(KG, 1) ? (KG + 1) / 2 : KG;
+  static constexpr int bt(int b) { return b > 1 && (b > PG || over(KH, b)) ? bt(b / 2) : b; }
+  static constexpr int BT = bt(4);
+  static constexpr bool AHEAD = BT == 1 && PG > 1;
+  // row pitch in floats, 16 mod 64: four rows of 16 consecutive columns (a
+  // consumer's operand) fall on 64 distinct banks, as do the producers'
+  // column quadruples of one 16-lane row
+  static constexpr int PITCH = 16 * TILES + 16;
+  static constexpr int BUF = R * PITCH;
+  // the partials of one element of P lie side by side (8 floats: a
+  // consumer reads its view's four, or all eight, in 16-byte loads)
+  static constexpr int PART = R * 4 * KG * kPipeProd;
+  static constexpr size_t lds_bytes() { return (size_t)(kPipeRing * BUF + 2 * PART) * 4; }
 };
 
-// Per-block work of k_pass_quad.  The LDS regions arrive as separate
-// restrict pointers: the inlined accesses then carry alias scopes, and the
-// compiler's wait insertion can see that the reads of the current block,
-// the P partials and [P_0 | P_1] are disjoint from the next block's
-// in-flight DMA (without that it waits for the DMA before the first LDS
-// read, and the double buffer overlaps nothing).  The next block's DMA is
-// issued here when next_row0 >= 0.
-template <int SV, int C4, int VEC>
-__device__ __forceinline__ void quad_step(const float* __restrict__ xs, float* __restrict__ xnext,
-                                          float* __restrict__ red, float* __restrict__ pfull, int64_t next_row0,
-                                          const float* A0, const float* A1, int64_t n, int d0, int d1, int k,
-                                          int T0, int T1, int nch0, int nch, int pitch, int w, int lane,
-                                          const float (&wreg)[QuadShape<SV, C4>::PG][4][QuadShape<SV, C4>::KG],
-                                          const int (&pcol)[QuadShape<SV, C4>::PG],
-                                          const int (&rbase)[QuadShape<SV, C4>::NG],
-                                          f32x4 (&acc)[QuadShape<SV, C4>::TPB][QuadShape<SV, C4>::JQ > 0 ? QuadShape<SV, C4>::JQ : 1],
-                                          f32x4 (&accr)[QuadShape<SV, C4>::NG][QuadShape<SV, C4>::JR > 0 ? QuadShape<SV, C4>::JR : 1],
-                                          bool dma_only) {
-  using Q = QuadShape<SV, C4>;
-  constexpr int R = kDmaRows;
-  constexpr int CH = 64 * VEC;
-  constexpr int TPB = Q::TPB, KG = Q::KG, JQ = Q::JQ, JR = Q::JR, NG = Q::NG, PP = Q::PP, PG = Q::PG;
-  constexpr int RED = Q::RED, REDP = Q::REDP;
-  const int tid = threadIdx.x;
-  const int g = lane >> 4, l16 = lane & 15, cs = (lane >> 2) & 3, q4 = lane & 3;
-  if (next_row0 >= 0) {
-    // waves 0-7 move chunks j = w, w + 8, ... of every row (the other
-    // eight waves go straight to the products); one buffer resource per
-    // view, rows past n read as zero
-    const int rows = (int)(n - next_row0 < R ? n - next_row0 : R);
-    const __amdgpu_buffer_rsrc_t r0 = make_rsrc(A0 + next_row0 * d0, (int64_t)rows * d0 * 4);
-    const __amdgpu_buffer_rsrc_t r1 = make_rsrc(A1 + next_row0 * d1, (int64_t)rows * d1 * 4);
-    for (int j = w; j < nch && w < kF32Waves / 2; j += kF32Waves / 2) {
-      const bool s1 = j >= nch0;
-      const int jj = s1 ? j - nch0 : j;
-      const int span = (s1 ? T1 : T0) * 16;
-      const int o = min(jj * CH, span - CH);
-      const int db4 = (s1 ? d1 : d0) * 4;
-      float* dst = xnext + (s1 ? T0 * 16 : 0) + o;
-      const int vbase = (o + lane * VEC) * 4;
-      const __amdgpu_buffer_rsrc_t rs = s1 ? r1 : r0;
+// The loader's loads of the R rows at a0 (and a1), `left` of them before the
+// end of the data, into dst: chunks of 256 columns (16 bytes a lane), rows
+// past the end read zero through the resource's range check.  Columns
+// between a view's last and its last tile's read the next row's first
+// values (they meet zero direction rows in P and land in J rows that are not
+// stored).  Rows need not start on 16-byte boundaries (a 16-byte load takes
+// any 4-byte one); but a load that straddles the end of the matrix must not
+// lose its valid part to the range check, so the block with the last row is
+// loaded 4 bytes a lane when a row is no multiple of 16 bytes.  Returns the
+// number of loads in flight for the block (0 stands for "wait for all").
+template <int NV, int R, int PITCH, bool NT>
+__device__ __forceinline__ int pipe_load(const float* a0, const float* a1, int64_t left, int d0, int d1, int T0,
+                                         int T1, float* __restrict__ dst, int lane) {
+  const bool tail = left <= R && ((d0 | d1) & 3) != 0;
+  int cnt = 0;
 #pragma unroll
-      for (int r = 0; r < R; ++r) dma_row_chunk<VEC>(rs, dst + r * pitch, vbase + r * db4);
+  for (int v = 0; v < NV; ++v) {
+    const int dv = v ? d1 : d0, span = (v ? T1 : T0) * 16;
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(v ? a1 : a0, left * dv * 4);
+    float* dv0 = dst + (v ? T0 * 16 : 0);
+    if (!tail) {
+      // whole chunks, then the part of one that is left
+      int c0 = 0;
+      for (; c0 + 256 <= span; c0 += 256)
+#pragma unroll
+        for (int r = 0; r < R; ++r) dma_row_chunk<4, NT>(rs, dv0 + r * PITCH + c0, (r * dv + c0 + 4 * lane) * 4);
+      if (c0 + 4 * lane < span)
+#pragma unroll
+        for (int r = 0; r < R; ++r) dma_row_chunk<4, NT>(rs, dv0 + r * PITCH + c0, (r * dv + c0 + 4 * lane) * 4);
+      cnt += R * ((span + 255) / 256);
+    } else {
+      for (int c0 = 0; c0 < span; c0 += 64)
+        if (c0 + lane < span)
+#pragma unroll
+          for (int r = 0; r < R; ++r) dma_row_chunk<1>(rs, dv0 + r * PITCH + c0, (r * dv + c0 + lane) * 4);
     }
   }
-  if (dma_only) return;
-  // (b) P partials of this wave's view over its tiles: rows 4 rg + q4,
-  // columns 4 cs .. 4 cs + 3 of each tile
-  {
-    f32x4 pacc[R / 4][KG];
+  return tail ? 0 : cnt;
+}
+
+// At most n of this wave's loads outstanding (n a multiple of 4: blocks are
+// 4, 8 or 16 loads a chunk of columns; gfx9 encoding of vmcnt).
+__device__ __forceinline__ void pipe_wait(int n) {
+  switch (n) {
+#define SRP_VM(N) case N: __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8)); break;
+    SRP_VM(4) SRP_VM(8) SRP_VM(12) SRP_VM(16) SRP_VM(20) SRP_VM(24) SRP_VM(28) SRP_VM(32) SRP_VM(36) SRP_VM(40)
+    SRP_VM(48)
+#undef SRP_VM
+    default: __builtin_amdgcn_s_waitcnt((0x7 << 4) | (0xF << 8));
+  }
+}
+
+// A producer's partial of P for the block in xs (ngrp groups).  pcol: the
+// LDS column of this lane's quadruple in group 0; nok: groups whose tile of
+// this lane row exists (the zeros of the row's padding stand for the rest).
+template <class S>
+__device__ __forceinline__ void pipe_produce(const float* __restrict__ xs, float* __restrict__ part, int w, int lane,
+                                             int ngrp, const float (&wreg)[S::PG][4][S::KG], int pcol, int nok) {
+  constexpr int R = S::R, KG = S::KG, PG = S::PG, RG = S::RB / 4, KH = S::KH, BT = S::BT;
+  // lane-dependent offsets are formed per block: live across the loop they
+  // would spill beside the directions
+  asm volatile("" : "+v"(lane), "+v"(pcol), "+v"(nok));
+  const int g = lane >> 4, cs = (lane >> 2) & 3, q4 = lane & 3;
+  const float* xq = xs + q4 * S::PITCH;
+  // items: batches of BT groups, in turn for each half of the directions and
+  // each RB rows
+  constexpr int NBT = (PG + BT - 1) / BT, NK = (KG + KH - 1) / KH, NIT = R / S::RB * NK * NBT;
+  float4 a4[S::AHEAD ? 2 : 1][BT][RG];
+  auto read = [&](int it) __attribute__((always_inline)) {
+    const int b = it % NBT * BT, r0 = it / (NBT * NK) * S::RB;
 #pragma unroll
-    for (int rg = 0; rg < R / 4; ++rg)
+    for (int u = 0; u < BT; ++u)
 #pragma unroll
-      for (int kg = 0; kg < KG; ++kg) pacc[rg][kg] = f32x4{0, 0, 0, 0};
-    // all operand reads of the block issued before the first product
-    float4 a4[PG][R / 4];
+      for (int rg = 0; rg < RG; ++rg)
+        a4[S::AHEAD ? it & 1 : 0][u][rg] = *reinterpret_cast<const float4*>(
+            xq + (r0 + 4 * rg) * S::PITCH +
+            (b + u < S::FULL || b + u < nok ? pcol + 64 * S::NPV * (b + u) : S::PITCH - 16));
+  };
+  f32x4 pacc[RG][KH];
+  if (S::AHEAD) read(0);
 #pragma unroll
-    for (int G = 0; G < PG; ++G)
+  for (int it = 0; it < NIT; ++it) {
+    const int b = it % NBT * BT, k0 = it / NBT % NK * KH, r0 = it / (NBT * NK) * S::RB;
+    if (b == 0)
 #pragma unroll
-      for (int rg = 0; rg < R / 4; ++rg) a4[G][rg] = *reinterpret_cast<const float4*>(xs + (4 * rg + q4) * pitch + pcol[G]);
+      for (int rg = 0; rg < RG; ++rg)
 #pragma unroll
-    for (int G = 0; G < PG; ++G)
+        for (int kk = 0; kk < KH; ++kk) pacc[rg][kk] = f32x4{0, 0, 0, 0};
+    if (S::AHEAD) {
+      if (it + 1 < NIT) read(it + 1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (b < S::FULL || b < ngrp) {
+      if (!S::AHEAD) read(it);
 #pragma unroll
-      for (int rg = 0; rg < R / 4; ++rg) {
-        const float av[4] = {a4[G][rg].x, a4[G][rg].y, a4[G][rg].z, a4[G][rg].w};
+      for (int u = 0; u < BT; ++u)
 #pragma unroll
         for (int s = 0; s < 4; ++s)
 #pragma unroll
-          for (int kg = 0; kg < KG; ++kg) pacc[rg][kg] = mfma4x4(av[s], wreg[G][s][kg], pacc[rg][kg]);
-      }
-    // The wave's partial: the four tiles of a 16-lane row by a scattered
-    // row sum, then the four column phases (in every lane, so that both
-    // rotations fold into the adds); lane (g, 0, q4) holds row 4 rg + r,
-    // r = (0, 2, 1, 3)[g], direction column 4 kg + q4: element
-    // ((rg KG + kg) 4 + q4) 4 + r of the partial.
-    xdl_settle2<KG>(pacc);
-    float sums[2][KG];
+          for (int rg = 0; rg < RG; ++rg) {
+            const float4 a = a4[S::AHEAD ? it & 1 : 0][u][rg];
+            const float av = s == 0 ? a.x : s == 1 ? a.y : s == 2 ? a.z : a.w;
 #pragma unroll
-    for (int rg = 0; rg < 2; ++rg)
-#pragma unroll
-      for (int kg = 0; kg < KG; ++kg) {
-        float x = rows_scatter_sum(pacc[rg][kg]);
-        x += dpp_row_ror<4>(x);
-        x += dpp_row_ror<8>(x);
-        asm volatile("" : "+v"(x));
-        sums[rg][kg] = x;
-      }
-    if (cs == 0) {
+            for (int kk = 0; kk < KH; ++kk)
+              if (k0 + kk < KG) pacc[rg][kk] = mfma4x4(av, wreg[b + u][s][k0 + kk], pacc[rg][kk]);
+          }
+    }
+    if (b + BT >= PG) {
+      // the four tiles of a 16-lane row by a scattered row sum, then the
+      // column phases: lane (g, 0, q4) holds row r0 + 4 rg + (0, 2, 1, 3)[g],
+      // direction column 4 (k0 + kk) + q4
       const int r = ((g & 1) << 1) | (g >> 1);
-      float* rw = red + w * REDP + 4 * q4 + r;
+      float* rw = part + ((r0 + r) * (4 * KG) + 4 * k0 + q4) * kPipeProd + w;
 #pragma unroll
-      for (int rg = 0; rg < 2; ++rg)
+      for (int rg = 0; rg < RG; ++rg)
 #pragma unroll
-        for (int kg = 0; kg < KG; ++kg) rw[(rg * KG + kg) * 16] = sums[rg][kg];
-    }
-  }
-  lds_only_barrier();
-  // Sum over a view's 8 wave partials in a fixed order: the four lanes of a
-  // quad add two partials each, then two quad exchanges combine them.  The indexes are recomputed per
-  // block (an opaque copy of tid): hoisted out of the loop they would stay
-  // live through the whole block and be spilled.
-  for (int t4 = tid; t4 < 8 * RED; t4 += kF32Threads) {
-    int t = t4;
-    asm volatile("" : "+v"(t));
-    const int o = t >> 2, j = t & 3;
-    const int v = o / RED, e = o - v * RED;
-    const float* src = red + (v * kF32Waves / 2 + 2 * j) * REDP + e;
-    float sum = src[0] + src[REDP];
-    sum += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, sum), 0xB1, 0xF, 0xF, true));
-    sum += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, sum), 0x4E, 0xF, 0xF, true));
-    const int r = e & 3, q = (e >> 2) & 3, rk = e >> 4;
-    const int rg = rk / KG, kg = rk - rg * KG;
-    const int col = 4 * kg + q;
-    if (j == 0 && col < k) pfull[(4 * rg + r) * PP + v * k + col] = sum;
-  }
-  lds_only_barrier();
-  // (d) J = A_b^T [P_0 | P_1]
-  if constexpr (JQ > 0) {
-    float pb[R / 4][JQ];
-#pragma unroll
-    for (int s = 0; s < R / 4; ++s)
-#pragma unroll
-      for (int jq = 0; jq < JQ; ++jq) pb[s][jq] = pfull[(g + 4 * s) * PP + 16 * jq + l16];
-#pragma unroll
-    for (int i = 0; i < TPB; ++i) {
-      const int col = 16 * (i < SV ? w + 16 * i : T0 + w + 16 * (i - SV));
-#pragma unroll
-      for (int s = 0; s < R / 4; ++s) {
-        const float a = xs[(g + 4 * s) * pitch + col + l16];
-#pragma unroll
-        for (int jq = 0; jq < JQ; ++jq) acc[i][jq] = mfma16x16x4(a, pb[s][jq], acc[i][jq]);
-      }
-    }
-  }
-  if constexpr (JR > 0) {
-    // step rho: lane row g takes block row (rho + g) mod R (the four tiles
-    // of an instruction then read different banks)
-#pragma unroll
-    for (int rho = 0; rho < R; ++rho) {
-      const int row = (rho + g) & (R - 1);
-      float b[JR];
-#pragma unroll
-      for (int jr = 0; jr < JR; ++jr) b[jr] = pfull[row * PP + 16 * JQ + 4 * jr + q4];
-#pragma unroll
-      for (int G = 0; G < NG; ++G) {
-        const float a = xs[row * pitch + rbase[G]];
-#pragma unroll
-        for (int jr = 0; jr < JR; ++jr) accr[G][jr] = mfma4x4(a, b[jr], accr[G][jr]);
-      }
+        for (int kk = 0; kk < KH; ++kk)
+          if (k0 + kk < KG) {
+            float x = rows_scatter_sum(pacc[rg][kk]);
+            x += dpp_row_ror<4>(x);
+            x += dpp_row_ror<8>(x);
+            asm volatile("" : "+v"(x));   // the sum in every lane: both rotations fold into the adds
+            if (cs == 0) rw[(rg * 16 * KG + 4 * kk) * kPipeProd] = x;
+          }
     }
   }
 }
 
-template <int SV, int C4, int VEC>
+// An element of [P_0 | P_1]: its view's partials in wave order.
+template <int NV>
+__device__ __forceinline__ float pipe_sum(const float* p) {
+  const float4 a = *reinterpret_cast<const float4*>(p);
+  float s = ((a.x + a.y) + a.z) + a.w;
+  if constexpr (NV == 1) {
+    const float4 b = *reinterpret_cast<const float4*>(p + 4);
+    s = (((s + b.x) + b.y) + b.z) + b.w;
+  }
+  return s;
+}
+
+// A consumer's step: J += A_b^T [P_0 | P_1] over this wave's first 4 NACT
+// tiles (its groups that hold any), P from the producers' partials.  xs: the
+// block at this wave's first tile.  pq, pr: this lane's element of a row of
+// P for column l16 of the whole tiles and column q4 of the groups past them.
+// The operands are read two batches ahead of the products that use them (the
+// scheduling barriers keep them there), so that a wave does not wait for LDS
+// at every product.
+template <class S, int NV, int NACT>
+__device__ __forceinline__ void pipe_consume(const float* __restrict__ xs, const float* __restrict__ part, int lane,
+                                             const int (&pq)[2], const int (&pr)[3],
+                                             f32x4 (&acc)[S::SLOTS][S::JQ > 0 ? S::JQ : 1],
+                                             f32x4 (&accr)[S::NG][S::JR > 0 ? S::JR : 1]) {
+  constexpr int R = S::R, KG = S::KG, JQ = S::JQ, JR = S::JR;
+  constexpr int NS = 4 * NACT < S::SLOTS ? 4 * NACT : S::SLOTS;   // tiles
+  constexpr int ROW = 4 * KG * kPipeProd;   // floats per row of the partials
+  const int g = lane >> 4, l16 = lane & 15;
+#pragma unroll
+  for (int h = 0; h < R / 4; ++h) {   // four rows at a time
+    // whole tiles: lane row g takes block row 4 h + g, a tile per product;
+    // 4x4 blocks: a row per product, lane row g takes its tile 4 G + g
+    const float* xq = xs + (4 * h + g) * S::PITCH + l16;
+    const float* xr = xs + 4 * h * S::PITCH + lane;
+    float pbq[JQ > 0 ? JQ : 1], pbr[4][JR > 0 ? JR : 1];
+#pragma unroll
+    for (int jq = 0; jq < JQ; ++jq) pbq[jq] = pipe_sum<NV>(part + (4 * h + g) * ROW + pq[jq]);
+#pragma unroll
+    for (int jr = 0; jr < JR; ++jr) {
+      // this lane row's element; swaps then give every lane row each of the
+      // four: the swap of a value with its copy leaves lane rows 0 1 0 1 in
+      // one and 2 3 2 3 in the other, the next ones a row each.
+      const uint32_t x = __builtin_bit_cast(uint32_t, pipe_sum<NV>(part + (4 * h + g) * ROW + pr[jr]));
+      const auto y = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+      const auto z0 = __builtin_amdgcn_permlane16_swap(y[0], y[0], false, false);
+      const auto z1 = __builtin_amdgcn_permlane16_swap(y[1], y[1], false, false);
+      const uint32_t z[4] = {z0[0], z0[1], z1[0], z1[1]};
+#pragma unroll
+      for (int rho = 0; rho < 4; ++rho) pbr[rho][jr] = __builtin_bit_cast(float, z[rho]);
+    }
+    if constexpr (JQ > 0)
+#pragma unroll
+      for (int t = 0; t < NS; ++t) {
+        const float a = xq[16 * t];
+#pragma unroll
+        for (int jq = 0; jq < JQ; ++jq) acc[t][jq] = mfma16x16x4(a, pbq[jq], acc[t][jq]);
+      }
+    if constexpr (JR > 0)
+#pragma unroll
+      for (int rho = 0; rho < 4; ++rho)
+#pragma unroll
+        for (int G = 0; G < NACT; ++G) {
+          const float a = xr[rho * S::PITCH + 64 * G];
+#pragma unroll
+          for (int jr = 0; jr < JR; ++jr) accr[G][jr] = mfma4x4(a, pbr[rho][jr], accr[G][jr]);
+        }
+  }
+}
+
+template <int NV, int R_, int C4, int PG_>
 __global__ void __launch_bounds__(kF32Threads) k_pass_quad(const float* __restrict__ A0, const float* __restrict__ A1,
                                                            int64_t n, int d0, int d1, int k,
                                                            const double* __restrict__ W0,
                                                            const double* __restrict__ W1, int nrb,
                                                            float* __restrict__ partial, const int* __restrict__ done) {
   if (done && *done) return;
-  using Q = QuadShape<SV, C4>;
-  constexpr int R = kDmaRows;
-  constexpr int CH = 64 * VEC;
-  constexpr int TPB = Q::TPB, KG = Q::KG, JQ = Q::JQ, JR = Q::JR, NG = Q::NG, PP = Q::PP, PG = Q::PG;
+  using S = PipeShape<NV, R_, C4, PG_>;
+  constexpr int R = S::R, KG = S::KG, JQ = S::JQ, JR = S::JR, NG = S::NG, PG = S::PG;
   extern __shared__ float dsm[];
-  const int T0 = (d0 + 15) >> 4, T1 = (d1 + 15) >> 4;
-  const int nch0 = (T0 * 16 + CH - 1) / CH, nch1 = (T1 * 16 + CH - 1) / CH;
-  const int nch = nch0 + nch1;
-  const int pitch = quad_pitch(TPB);
-  float* red = dsm + 2 * R * pitch;                 // [wave] partials, pitch REDP
-  float* pfull = red + kF32Waves * Q::REDP;         // [R][PP]
-
+  float* parts = dsm + kPipeRing * S::BUF;   // two sets of partials
+  const int T0 = (d0 + 15) >> 4, T1 = NV == 2 ? (d1 + 15) >> 4 : 0;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = lane >> 4, l16 = lane & 15;
-  const int cs = (lane >> 2) & 3, q4 = lane & 3;
-  const int pv = w >> 3;   // view of this wave's P products (wave-uniform)
-
-  // direction operands of the P blocks: group G, tile tv = w % 8 + 8 (4 G +
-  // g) of view pv, its column 4 cs + s, direction column 4 kg + q4, read
-  // from the FP64 directions (d x k row-major; rows past d lie past the
-  // resource and read zero, columns past k take the zero offset)
-  const __amdgpu_buffer_rsrc_t wrs = make_rsrc(pv ? W1 : W0, (int64_t)(pv ? d1 : d0) * k * 8);
-  float wreg[PG][4][KG];
-  int pcol[PG];   // LDS column of the tile's phase-cs quadruple
-#pragma unroll
-  for (int G = 0; G < PG; ++G) {
-    const int tv = (w & 7) + 8 * (4 * G + g);
-    const bool ok = tv < (pv ? T1 : T0);
-    pcol[G] = 16 * (pv ? T0 + tv : tv) + 4 * cs;
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int kg = 0; kg < KG; ++kg) {
-        const int col = 4 * kg + q4;
-        const int off = (ok && col < k) ? ((16 * tv + 4 * cs + s) * k + col) * 8 : kOob;
-        wreg[G][s][kg] = (float)buf_load<double>(wrs, off, 0);
+  // this workgroup's blocks: pairs of neighbours, pair blockIdx.x + j grid
+  // (twice the run of bytes: the row stream alone takes 264 us against 279
+  // with single blocks, 200000 x (1000 + 1000))
+  const int pairs = (nrb + 1) / 2, mine = (pairs - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
+  const int nst = 2 * mine - ((nrb & 1) && (pairs - 1) % (int)gridDim.x == (int)blockIdx.x ? 1 : 0);
+  if (w == kPipeProd + kPipeCons) {
+    auto stream = [&](auto nt_) __attribute__((always_inline)) {
+      int64_t row = (int64_t)blockIdx.x * 2 * R;
+      auto load = [&](int i) __attribute__((always_inline)) {   // block i, at `row`
+        const int cnt = pipe_load<NV, R, S::PITCH, decltype(nt_)::value>(
+            A0 + row * d0, NV == 2 ? A1 + row * d1 : nullptr, n - row, d0, NV == 2 ? d1 : 0, T0, T1,
+            dsm + (i & 3) * S::BUF, lane);
+        row += (i & 1) ? (2ll * gridDim.x - 1) * R : R;
+        return cnt;
+      };
+      load(0);
+      pipe_wait(nst > 1 ? load(1) : 0);   // block 0 has landed
+      lds_only_barrier();
+      for (int i = 0; i <= nst; ++i) {
+        pipe_wait(i + 2 < nst ? load(i + 2) : 0);   // block i + 1 has landed; block i + 2 stays in flight
+        lds_only_barrier();
       }
-  }
-  f32x4 acc[TPB][JQ > 0 ? JQ : 1];
-  f32x4 accr[NG][JR > 0 ? JR : 1];
-#pragma unroll
-  for (int i = 0; i < TPB; ++i)
-#pragma unroll
-    for (int j = 0; j < (JQ > 0 ? JQ : 1); ++j) acc[i][j] = f32x4{0, 0, 0, 0};
-#pragma unroll
-  for (int G = 0; G < NG; ++G)
-#pragma unroll
-    for (int j = 0; j < (JR > 0 ? JR : 1); ++j) accr[G][j] = f32x4{0, 0, 0, 0};
-  int rbase[NG];   // remainder blocks: slot 4 G + g, column l16
-#pragma unroll
-  for (int G = 0; G < NG; ++G) {
-    const int i = 4 * G + g;
-    rbase[G] = 16 * (i < SV ? w + 16 * i : T0 + w + 16 * (i - SV)) + l16;
-  }
-  // Columns past the last tile are never loaded and the padding columns of
-  // [P_0 | P_1] never written: zero both row buffers and pfull once.
-  for (int e = tid; e < 2 * R * pitch; e += kF32Threads) dsm[e] = 0.f;
-  for (int e = tid; e < R * PP; e += kF32Threads) pfull[e] = 0.f;
-  __syncthreads();
-
-  int rb = blockIdx.x;
-  int boff = 0;
-  if (rb < nrb)
-    quad_step<SV, C4, VEC>(dsm + R * pitch, dsm, red, pfull, (int64_t)rb * R, A0, A1, n, d0, d1, k, T0, T1, nch0,
-                           nch, pitch, w, lane, wreg, pcol, rbase, acc, accr, true);
-  for (; rb < nrb; rb += gridDim.x) {
-    __builtin_amdgcn_s_waitcnt(0);   // this wave's loads of the block have landed
-    __syncthreads();                 // ... and every wave's; the other buffer is free
-    const int64_t nxt = rb + (int)gridDim.x < nrb ? (int64_t)(rb + gridDim.x) * R : -1;
-    quad_step<SV, C4, VEC>(dsm + boff, dsm + (R * pitch - boff), red, pfull, nxt, A0, A1, n, d0, d1, k, T0, T1,
-                           nch0, nch, pitch, w, lane, wreg, pcol, rbase, acc, accr, false);
-    boff = R * pitch - boff;
-  }
-  // epilogue: this workgroup's partial (rows = concatenated columns of A,
-  // columns = [P_0 | P_1])
-  const int W_out = 2 * k;
-  const int D = d0 + d1;
-  float* out = partial + (int64_t)blockIdx.x * D * W_out;
-  if constexpr (JQ > 0) {
-#pragma unroll
-    for (int i = 0; i < TPB; ++i) {
-      const int v = i < SV ? 0 : 1;
-      const int tv = w + 16 * (i - v * SV);
-      if (tv < (v ? T1 : T0)) {
-        const int db = v ? d1 : d0, rowbase = v ? d0 : 0;
-#pragma unroll
-        for (int jq = 0; jq < JQ; ++jq) {
-          const int c = 16 * jq + l16;
-          if (c < W_out) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const int row = 16 * tv + acc_row<float>(lane, r);
-              if (row < db) out[(int64_t)(rowbase + row) * W_out + c] = acc[i][jq][r];
-            }
-          }
-        }
-      }
-    }
-  }
-  if constexpr (JR > 0) {
-#pragma unroll
-    for (int G = 0; G < NG; ++G) {
-      const int i = 4 * G + g;
-      const int v = i < SV ? 0 : 1;
-      const int tv = w + 16 * (i - v * SV);
-      if (tv < (v ? T1 : T0)) {
-        const int db = v ? d1 : d0, rowbase = v ? d0 : 0;
-#pragma unroll
-        for (int jr = 0; jr < JR; ++jr) {
-          const int c = 16 * JQ + 4 * jr + q4;
-          if (c < W_out) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const int row = 16 * tv + 4 * cs + r;
-              if (row < db) out[(int64_t)(rowbase + row) * W_out + c] = accr[G][jr][r];
-            }
-          }
-        }
-      }
-    }
-  }
-}
-
-
-// ------------------------------------------------------------------
-// FP32, one view (FDA: J = A^T (A W), k <= 20): the same row stream with
-// the narrow products on 4x4 blocks.
-//   * P = A W (8 rows x k): wave w takes tiles w + 16 (4 G + g) (the four
-//     16-lane rows g of an instruction take four tiles); a block is 4 rows
-//     x 4 direction columns over one column in four; rows 0-3 and 4-7 are
-//     done one after the other (20 accumulator registers at k = 20).  The
-//     four tiles of an instruction are summed by lane-row swaps
-//     (v_permlane32_swap, v_permlane16_swap) that scatter the sums of four
-//     values over the four lane rows, the column phases by two DPP
-//     rotations, so each wave publishes one 8 x 4 KG partial.
-//   * J = A^T P: whole 16-column tiles of P on 16x16x4, the remaining
-//     4-column groups on 4x4 blocks over four tiles at once, as above.
-// Wave w owns J slots w + 16 i (i < TPB); slots and P tiles past the last
-// tile have zero directions and their rows are not stored.
-template <int TPB, int KG>
-struct Quad1Shape {
-  static constexpr int PG = TPB / 4;        // 4-tile groups of a wave's P products
-  static constexpr int JQ = KG / 4;         // whole 16-column tiles of P
-  static constexpr int JR = KG % 4;         // remaining 4-column groups
-  static constexpr int NG = TPB / 4;        // 4-slot groups of the remainder products
-  static constexpr int PP = 4 * KG + 1;     // row pitch of P in LDS
-  static constexpr int RED = kDmaRows * 4 * KG;
-  // LDS pitch of the wave partials: 4 mod 16 floats, so that the four lanes
-  // of a reducing quad (partials 4 apart) fall on different banks
-  static constexpr int REDP = RED + 4;
-};
-
-template <int TPB, int KG, int VEC>
-__device__ __forceinline__ void quad1_step(const float* __restrict__ xs, float* __restrict__ xnext,
-                                           float* __restrict__ red, float* __restrict__ pfull, int64_t next_row0,
-                                           const float* A0, int64_t n, int d0, int k, int T0, int nch0, int pitch,
-                                           int w, int lane, const float (&wreg)[TPB / 4][4][KG],
-                                           f32x4 (&acc)[TPB][Quad1Shape<TPB, KG>::JQ > 0 ? Quad1Shape<TPB, KG>::JQ : 1],
-                                           f32x4 (&accr)[TPB / 4][Quad1Shape<TPB, KG>::JR > 0 ? Quad1Shape<TPB, KG>::JR : 1],
-                                           bool dma_only) {
-  using Q = Quad1Shape<TPB, KG>;
-  constexpr int R = kDmaRows;
-  constexpr int CH = 64 * VEC;
-  constexpr int JQ = Q::JQ, JR = Q::JR, NG = Q::NG, PP = Q::PP, PG = Q::PG, RED = Q::RED, REDP = Q::REDP;
-  const int tid = threadIdx.x;
-  const int g = lane >> 4, l16 = lane & 15, cs = (lane >> 2) & 3, q4 = lane & 3;
-  if (next_row0 >= 0) {
-    const int rows = (int)(n - next_row0 < R ? n - next_row0 : R);
-    const __amdgpu_buffer_rsrc_t r0 = make_rsrc(A0 + next_row0 * d0, (int64_t)rows * d0 * 4);
-    const int span = T0 * 16;
-    const int db4 = d0 * 4;
-    for (int j = w; j < nch0; j += kF32Waves) {
-      const int o = min(j * CH, span - CH);
-      float* dst = xnext + o;
-      const int vbase = (o + lane * VEC) * 4;
-#pragma unroll
-      for (int r = 0; r < R; ++r) dma_row_chunk<VEC>(r0, dst + r * pitch, vbase + r * db4);
-    }
-  }
-  if (dma_only) return;
-  // (b) P partial of this wave: rows 4 rg + q4, one half at a time; with
-  // five direction-column groups also in two passes over the groups (the
-  // accumulators of all five would not fit beside the J accumulators)
-  constexpr int KH = KG >= 5 ? (KG + 1) / 2 : KG;
-#pragma unroll
-  for (int rg = 0; rg < 2; ++rg)
-#pragma unroll
-  for (int k0 = 0; k0 < KG; k0 += KH) {
-    f32x4 pacc[KH];
-#pragma unroll
-    for (int kk = 0; kk < KH; ++kk) pacc[kk] = f32x4{0, 0, 0, 0};
+    };
+    // data past the 256 MB that the memory-side cache holds is read once per
+    // pass: without the hint its stream runs at 5.9 TB/s, with it at 6.7
+    // (100000 x (1000 + 1000), k = 1: 135 and 120 us); data that fits is
+    // still there in the next pass (3000 x 2000, k = 9: 19 us, with the hint 22)
+    if (n * (d0 + (NV == 2 ? d1 : 0)) * 4 > (256ll << 20)) stream(std::integral_constant<bool, true>{});
+    else stream(std::integral_constant<bool, false>{});
+  } else if (w < kPipeProd) {
+    const int g = lane >> 4, cs = (lane >> 2) & 3, q4 = lane & 3;
+    // this wave's direction operands: group G is tiles 4 (wl + NPV G) .. + 3
+    // of its view, lane (g, cs, q4) holds direction column 4 kg + q4 for
+    // column 4 cs + s of tile g, read from the FP64 directions (rows past d
+    // lie past the resource and read zero, columns past k and tiles past the
+    // last take the zero offset)
+    const bool v1 = w >= S::NPV;   // NV == 1: never
+    const int wl = v1 ? w - S::NPV : w;
+    const int Tv = v1 ? T1 : T0;
+    const int ngrp = (((Tv + 3) >> 2) - wl + S::NPV - 1) / S::NPV;
+    const __amdgpu_buffer_rsrc_t wrs = make_rsrc(v1 ? W1 : W0, (int64_t)(v1 ? d1 : d0) * k * 8);
+    float wreg[PG][4][KG];
+    const int pcol = 16 * ((v1 ? T0 : 0) + 4 * wl + g) + 4 * cs;
+    const int nok = (Tv - (4 * wl + g) + 4 * S::NPV - 1) / (4 * S::NPV);   // <= 0 where the first is past the last
+    // the padding of the ring's rows, which no load touches
+    for (int e = tid; e < kPipeRing * R * 16; e += 64 * kPipeProd) dsm[(e >> 4) * S::PITCH + S::PITCH - 16 + (e & 15)] = 0.f;
 #pragma unroll
     for (int G = 0; G < PG; ++G) {
-      const int col = 16 * (w + 16 * (4 * G + g)) + 4 * cs;
-      const float4 a = *reinterpret_cast<const float4*>(xs + (4 * rg + q4) * pitch + col);
-      const float av[4] = {a.x, a.y, a.z, a.w};
+      const int tv = 4 * (wl + S::NPV * G) + g;
+      const bool ok = tv < Tv;
 #pragma unroll
       for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int kk = 0; kk < KH; ++kk)
-          if (k0 + kk < KG) pacc[kk] = mfma4x4(av[s], wreg[G][s][k0 + kk], pacc[kk]);
+        for (int kg = 0; kg < KG; ++kg) {
+          const int col = 4 * kg + q4;
+          const int off = (ok && col < k) ? ((16 * tv + 4 * cs + s) * k + col) * 8 : kOob;
+          wreg[G][s][kg] = (float)buf_load<double>(wrs, off, 0);
+        }
     }
-    // the wave's partial: the four tiles of a lane row by a scattered
-    // row sum, then the four column phases (in every lane, so that both
-    // rotations fold into the adds); lane (g, 0, q4) holds row 4 rg + r,
-    // r = (0, 2, 1, 3)[g], direction column 4 kg + q4
-    xdl_settle<KH>(pacc);
-    float sums[KH];
-#pragma unroll
-    for (int kk = 0; kk < KH; ++kk) {
-      float x = rows_scatter_sum(pacc[kk]);
-      x += dpp_row_ror<4>(x);
-      x += dpp_row_ror<8>(x);
-      asm volatile("" : "+v"(x));
-      sums[kk] = x;
+    lds_only_barrier();
+    for (int i = 0; i <= nst; ++i) {
+      if (i < nst)
+        pipe_produce<S>(dsm + (i & 3) * S::BUF, parts + (i & 1) * S::PART, w, lane, ngrp, wreg, pcol, nok);
+      lds_only_barrier();
     }
-    if (cs == 0) {
-      const int r = ((g & 1) << 1) | (g >> 1);
+  } else {
+    const int wj = w - kPipeProd;
+    const int g = lane >> 4, l16 = lane & 15, cs = (lane >> 2) & 3, q4 = lane & 3;
+    const int TT = T0 + T1;
+    const int per = (TT + kPipeCons - 1) / kPipeCons;   // tiles of a consumer: per wj .. per wj + per - 1
+    f32x4 acc[S::SLOTS][JQ > 0 ? JQ : 1];
+    f32x4 accr[NG][JR > 0 ? JR : 1];
 #pragma unroll
-      for (int kk = 0; kk < KH; ++kk)
-        if (k0 + kk < KG) red[w * REDP + (4 * rg + r) * (4 * KG) + 4 * (k0 + kk) + q4] = sums[kk];
-    }
-  }
-  lds_only_barrier();
-  // Sum over the 16 wave partials in a fixed order: the four lanes of a
-  // quad add four partials each, then two quad exchanges combine them.
-  for (int t4 = tid; t4 < 4 * RED; t4 += kF32Threads) {
-    int t = t4;
-    asm volatile("" : "+v"(t));
-    const int e = t >> 2, j = t & 3;
-    const float* src = red + 4 * j * REDP + e;
-    float sum = 0.f;
+    for (int i = 0; i < S::SLOTS; ++i)
 #pragma unroll
-    for (int h = 0; h < 4; ++h) sum += src[h * REDP];
-    sum += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, sum), 0xB1, 0xF, 0xF, true));
-    sum += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, sum), 0x4E, 0xF, 0xF, true));
-    const int row = e / (4 * KG), col = e - row * (4 * KG);
-    if (j == 0 && col < k) pfull[row * PP + col] = sum;
-  }
-  lds_only_barrier();
-  // (d) J = A^T P
-  if constexpr (JQ > 0) {
-    float pb[2][JQ];
+      for (int j = 0; j < (JQ > 0 ? JQ : 1); ++j) acc[i][j] = f32x4{0, 0, 0, 0};
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
+    for (int G = 0; G < NG; ++G)
 #pragma unroll
-      for (int jq = 0; jq < JQ; ++jq) pb[s][jq] = pfull[(g + 4 * s) * PP + 16 * jq + l16];
+      for (int j = 0; j < (JR > 0 ? JR : 1); ++j) accr[G][j] = f32x4{0, 0, 0, 0};
+    // column c of [P_0 | P_1] is column c - v k of view v (columns past the
+    // last read the last's; their sums are not stored)
+    const int cmax = NV * k - 1;
+    int pq[2] = {0, 0}, pr[3] = {0, 0, 0};
+    auto element = [&](int c) {
+      c = min(c, cmax);
+      const int v = c >= k ? 1 : 0;
+      return (c - v * k) * kPipeProd + v * S::NPV;
+    };
 #pragma unroll
-    for (int i = 0; i < TPB; ++i) {
-      const int col = 16 * (w + 16 * i);
+    for (int jq = 0; jq < JQ; ++jq) pq[jq] = element(16 * jq + l16);
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        const float a = xs[(g + 4 * s) * pitch + col + l16];
-#pragma unroll
-        for (int jq = 0; jq < JQ; ++jq) acc[i][jq] = mfma16x16x4(a, pb[s][jq], acc[i][jq]);
+    for (int jr = 0; jr < JR; ++jr) pr[jr] = element(16 * JQ + 4 * jr + q4);
+    lds_only_barrier();
+    lds_only_barrier();   // the producers' step 0
+    auto steps = [&](auto n_) __attribute__((always_inline)) {
+      for (int i = 0; i < nst; ++i) {
+        pipe_consume<S, NV, decltype(n_)::value>(dsm + (i & 3) * S::BUF + 16 * per * wj, parts + (i & 1) * S::PART,
+                                                 lane, pq, pr, acc, accr);
+        lds_only_barrier();
       }
+    };
+    const int nact = (per + 3) / 4;
+    if (NG == 1 || nact == 1) steps(std::integral_constant<int, 1>{});
+    else if (NG == 2 || nact == 2) steps(std::integral_constant<int, 2>{});
+    else if (NG == 3 || nact == 3) steps(std::integral_constant<int, NG < 3 ? 1 : 3>{});
+    else if (nact == 4) steps(std::integral_constant<int, NG < 4 ? 1 : 4>{});
+    else steps(std::integral_constant<int, NG < 5 ? 1 : 5>{});
+    // this workgroup's partial (rows = concatenated columns of A, columns =
+    // [P_0 | P_1])
+    const int W_out = NV * k;
+    float* out = partial + (int64_t)blockIdx.x * (d0 + (NV == 2 ? d1 : 0)) * W_out;
+    auto put = [&](int slot, int row, int c, float x) __attribute__((always_inline)) {
+      const int t = per * wj + slot;
+      const bool b1 = NV == 2 && t >= T0;
+      const int rv = 16 * (b1 ? t - T0 : t) + row;
+      if (slot < per && t < TT && c < W_out && rv < (b1 ? d1 : d0)) out[(int64_t)((b1 ? d0 : 0) + rv) * W_out + c] = x;
+    };
+    if constexpr (JQ > 0) {
+#pragma unroll
+      for (int i = 0; i < S::SLOTS; ++i)
+#pragma unroll
+        for (int jq = 0; jq < JQ; ++jq)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) put(i, acc_row<float>(lane, r), 16 * jq + l16, acc[i][jq][r]);
     }
-  }
-  if constexpr (JR > 0) {
+    if constexpr (JR > 0) {
 #pragma unroll
-    for (int rho = 0; rho < R; ++rho) {
-      const int row = (rho + g) & (R - 1);
-      float b[JR];
+      for (int G = 0; G < NG; ++G)
 #pragma unroll
-      for (int jr = 0; jr < JR; ++jr) b[jr] = pfull[row * PP + 16 * JQ + 4 * jr + q4];
+        for (int jr = 0; jr < JR; ++jr)
 #pragma unroll
-      for (int G = 0; G < NG; ++G) {
-        const float a = xs[row * pitch + 16 * (w + 16 * (4 * G + g)) + l16];
-#pragma unroll
-        for (int jr = 0; jr < JR; ++jr) accr[G][jr] = mfma4x4(a, b[jr], accr[G][jr]);
-      }
+          for (int r = 0; r < 4; ++r) put(4 * G + g, 4 * cs + r, 16 * JQ + 4 * jr + q4, accr[G][jr][r]);
     }
   }
 }
 
-template <int TPB, int KG, int VEC>
-__global__ void __launch_bounds__(kF32Threads) k_pass_quad1(const float* __restrict__ A0, int64_t n, int d0, int k,
-                                                            const float* __restrict__ Wp0, int nrb,
-                                                            float* __restrict__ partial, const int* __restrict__ done) {
-  if (done && *done) return;
-  using Q = Quad1Shape<TPB, KG>;
-  constexpr int R = kDmaRows;
-  constexpr int CH = 64 * VEC;
-  constexpr int JQ = Q::JQ, JR = Q::JR, NG = Q::NG, PP = Q::PP, PG = Q::PG;
-  extern __shared__ float dsm[];
-  const int T0 = (d0 + 15) >> 4;
-  const int nch0 = (T0 * 16 + CH - 1) / CH;
-  const int pitch = quad_pitch(TPB);
-  float* red = dsm + 2 * R * pitch;          // [wave][R][4 KG], pitch REDP
-  float* pfull = red + kF32Waves * Q::REDP;  // [R][PP]
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = lane >> 4, l16 = lane & 15, cs = (lane >> 2) & 3, q4 = lane & 3;
-
-  // direction operands of the P blocks: tile w + 16 (4 G + g), its column
-  // 4 cs + s, direction column 4 kg + q4, from the directions packed to
-  // FP32 (4 KG columns, zero padded; every workgroup reads all of them, and
-  // at k = 19 the FP64 iterate would double that L2 traffic)
-  const __amdgpu_buffer_rsrc_t wrs = make_rsrc(Wp0, (int64_t)T0 * 16 * (4 * KG) * 4);
-  float wreg[PG][4][KG];
-#pragma unroll
-  for (int G = 0; G < PG; ++G) {
-    const int tv = w + 16 * (4 * G + g);
-    const bool ok = tv < T0;
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int kg = 0; kg < KG; ++kg) {
-        const int off = ok ? ((16 * tv + 4 * cs + s) * (4 * KG) + 4 * kg + q4) * 4 : kOob;
-        wreg[G][s][kg] = buf_load<float>(wrs, off, 0);
-      }
-  }
-  f32x4 acc[TPB][JQ > 0 ? JQ : 1];
-  f32x4 accr[NG][JR > 0 ? JR : 1];
-#pragma unroll
-  for (int i = 0; i < TPB; ++i)
-#pragma unroll
-    for (int j = 0; j < (JQ > 0 ? JQ : 1); ++j) acc[i][j] = f32x4{0, 0, 0, 0};
-#pragma unroll
-  for (int G = 0; G < NG; ++G)
-#pragma unroll
-    for (int j = 0; j < (JR > 0 ? JR : 1); ++j) accr[G][j] = f32x4{0, 0, 0, 0};
-  for (int e = tid; e < 2 * R * pitch; e += kF32Threads) dsm[e] = 0.f;
-  for (int e = tid; e < R * PP; e += kF32Threads) pfull[e] = 0.f;
-  __syncthreads();
-
-  int rb = blockIdx.x;
-  int boff = 0;
-  if (rb < nrb)
-    quad1_step<TPB, KG, VEC>(dsm + R * pitch, dsm, red, pfull, (int64_t)rb * R, A0, n, d0, k, T0, nch0, pitch, w,
-                             lane, wreg, acc, accr, true);
-  for (; rb < nrb; rb += gridDim.x) {
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    const int64_t nxt = rb + (int)gridDim.x < nrb ? (int64_t)(rb + gridDim.x) * R : -1;
-    quad1_step<TPB, KG, VEC>(dsm + boff, dsm + (R * pitch - boff), red, pfull, nxt, A0, n, d0, k, T0, nch0, pitch,
-                             w, lane, wreg, acc, accr, false);
-    boff = R * pitch - boff;
-  }
-  // epilogue: this workgroup's partial (d0 x k)
-  float* out = partial + (int64_t)blockIdx.x * d0 * k;
-  if constexpr (JQ > 0) {
-#pragma unroll
-    for (int i = 0; i < TPB; ++i) {
-      const int tv = w + 16 * i;
-      if (tv < T0) {
-#pragma unroll
-        for (int jq = 0; jq < JQ; ++jq) {
-          const int c = 16 * jq + l16;
-          if (c < k) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const int row = 16 * tv + acc_row<float>(lane, r);
-              if (row < d0) out[(int64_t)row * k + c] = acc[i][jq][r];
-            }
-          }
-        }
-      }
-    }
-  }
-  if constexpr (JR > 0) {
-#pragma unroll
-    for (int G = 0; G < NG; ++G) {
-      const int tv = w + 16 * (4 * G + g);
-      if (tv < T0) {
-#pragma unroll
-        for (int jr = 0; jr < JR; ++jr) {
-          const int c = 16 * JQ + 4 * jr + q4;
-          if (c < k) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const int row = 16 * tv + 4 * cs + r;
-              if (row < d0) out[(int64_t)row * k + c] = accr[G][jr][r];
-            }
-          }
-        }
-      }
-    }
-  }
-}
-
-// Tile slots per wave: the smallest instance (2, 4, 6 or 8) covering
-// the tiles of [A_0 | A_1].
+// Tile slots per wave: the smaller instance covering the tiles of
+// [A_0 | A_1] (two views of at most 64 tiles together take k_pass_quad).
 static int dma_slots(int d0, int d1) {
-  const int TT = (d0 + 15) / 16 + (d1 > 0 ? (d1 + 15) / 16 : 0);
-  const int need = (TT + kF32Waves - 1) / kF32Waves;
-  return need <= 2 ? 2 : need <= 4 ? 4 : need <= 6 ? 6 : 8;
+  const int TT = (d0 + 15) / 16 + (d1 + 15) / 16;
+  return TT <= 6 * kF32Waves ? 6 : 8;
 }
 
-static size_t dma_lds_bytes(int d0, int d1, int NT) {
+static size_t dma_lds_bytes(int d0, int d1) {
   const size_t pitch = (size_t)dma_pitch(kF32Waves * dma_slots(d0, d1));
-  return (2 * kDmaRows * pitch + (size_t)kF32Waves * 256 + (size_t)NT * kDmaRows * 17) * sizeof(float);
+  return (2 * kDmaRows * pitch + (size_t)kF32Waves * 256 + (size_t)2 * kDmaRows * 17) * sizeof(float);
 }
 
 // 16-byte loads need rows that start on 16-byte boundaries and blocks of
 // at least 16 tiles (one 256-float chunk); 4-byte loads blocks of 4 tiles.
 static int dma_vec(const void* A0, const void* A1, int d0, int d1) {
-  const int T0 = (d0 + 15) / 16, T1 = A1 ? (d1 + 15) / 16 : 0;
-  const bool al = ((uintptr_t)A0 % 16 == 0) && (!A1 || (uintptr_t)A1 % 16 == 0) && d0 % 4 == 0 && (!A1 || d1 % 4 == 0);
-  if (al && T0 >= 16 && (!A1 || T1 >= 16)) return 4;
-  if (T0 >= 4 && (!A1 || T1 >= 4)) return 1;
-  return 0;
+  const int T0 = (d0 + 15) / 16, T1 = (d1 + 15) / 16;
+  const bool al = (uintptr_t)A0 % 16 == 0 && (uintptr_t)A1 % 16 == 0 && d0 % 4 == 0 && d1 % 4 == 0;
+  if (al && T0 >= 16 && T1 >= 16) return 4;
+  return T0 >= 4 && T1 >= 4 ? 1 : 0;
 }
 
 static bool dma_fits(int d0, int d1, int k, int nb, int vec) {
-  if (vec == 0) return false;
+  if (nb != 2 || vec == 0) return false;
   if (k > 16) return false;   // two k-tiles would not fit the registers
-  const int TT = (d0 + 15) / 16 + (nb == 2 ? (d1 + 15) / 16 : 0);
+  const int TT = (d0 + 15) / 16 + (d1 + 15) / 16;
   if (TT > kDmaMaxTiles) return false;
-  const int NT = nb * ((k + 15) / 16);
-  return dma_lds_bytes(d0, nb == 2 ? d1 : 0, NT) <= (size_t)kPassLds + 8 * 1024;
+  return dma_lds_bytes(d0, d1) <= (size_t)kPassLds + 8 * 1024;
 }
 
 template <class CT> static size_t pass_lds_bytes(int D, int NT) {
@@ -1605,96 +1417,26 @@ static int pass_launch(const DT* A0, const DT* A1, int64_t n, int d0, int d1, in
   return SRP_OK;
 }
 
-template <int NB, int TPB, int VEC>
+template <int TPB, int VEC>
 static int pass_launch_dma(const float* A0, const float* A1, int64_t n, int d0, int d1, int k, const double* W0,
                            const double* W1, double* J0, double* J1, const int* done, Arena& ws, hipStream_t st,
                            hipEvent_t before_pass, hipEvent_t after_pass) {
-  const int dp0 = (d0 + 15) / 16 * 16, dp1 = NB == 2 ? (d1 + 15) / 16 * 16 : 0;
+  const int dp0 = (d0 + 15) / 16 * 16, dp1 = (d1 + 15) / 16 * 16;
   const int KP = 16;
   float* Wp0 = ws.take<float>((size_t)dp0 * KP);
-  float* Wp1 = NB == 2 ? ws.take<float>((size_t)dp1 * KP) : nullptr;
-  const int nrb = (int)((n + kDmaRows - 1) / kDmaRows);
-  // at least 4 blocks per workgroup (fewer partials to add for short data)
-  const int grid = std::max(1, std::min(num_cus(), (nrb + 3) / 4));
-  const int Dtot = d0 + (NB == 2 ? d1 : 0);
-  float* part = ws.take<float>((size_t)grid * Dtot * NB * k);
-  if (!Wp0 || !part || (NB == 2 && !Wp1)) { set_error("gram_pass: workspace too small"); return SRP_ENOMEM; }
-  SRP_TRY(pack_dirs<float>(W0, d0, dp0, Wp0, W1, d1, dp1, Wp1, k, KP, st));
-  const size_t lds = dma_lds_bytes(d0, NB == 2 ? d1 : 0, NB);
-  SRP_TRY(allow_dynamic_lds((const void*)k_pass_dma<NB, TPB, VEC>, kPassLds + 8 * 1024));
-  if (before_pass) SRP_HIP(hipEventRecord(before_pass, st));
-  hipLaunchKernelGGL((k_pass_dma<NB, TPB, VEC>), dim3(grid), dim3(kF32Threads), lds, st, A0, A1, n, d0,
-                     NB == 2 ? d1 : 0, k, Wp0, Wp1, nrb, part, done);
-  SRP_LAUNCH_CHECK();
-  if (after_pass) SRP_HIP(hipEventRecord(after_pass, st));
-  const int64_t count = (int64_t)Dtot * NB * k;
-  hipLaunchKernelGGL((k_pass_reduce<float>), dim3((unsigned)((count + 63) / 64)), dim3(256), 0, st, part, grid, d0,
-                     NB == 2 ? d1 : 0, NB * k, J0, J1, done, t_pass_ran);
-  SRP_LAUNCH_CHECK();
-  return SRP_OK;
-}
-
-static int pass_dispatch_dma(const float* A0, const float* A1, int64_t n, int d0, int d1, int k, const double* W0,
-                             const double* W1, double* J0, double* J1, const int* done, Arena& ws, hipStream_t st,
-                             hipEvent_t ev0, hipEvent_t ev) {
-  const int vec = dma_vec(A0, A1, d0, d1);
-  const int slots = dma_slots(d0, A1 ? d1 : 0);
-#define SRP_DMA_CASE(NB_, TPB_)                                                                             \
-  if (slots == TPB_)                                                                                        \
-    return vec == 4 ? pass_launch_dma<NB_, TPB_, 4>(A0, A1, n, d0, d1, k, W0, W1, J0, J1, done, ws, st, ev0, ev) \
-                    : pass_launch_dma<NB_, TPB_, 1>(A0, A1, n, d0, d1, k, W0, W1, J0, J1, done, ws, st, ev0, ev);
-  if (A1) {
-    SRP_DMA_CASE(2, 2) SRP_DMA_CASE(2, 4) SRP_DMA_CASE(2, 6) SRP_DMA_CASE(2, 8)
-  } else {
-    d1 = 0;
-    SRP_DMA_CASE(1, 2) SRP_DMA_CASE(1, 4) SRP_DMA_CASE(1, 6) SRP_DMA_CASE(1, 8)
-  }
-#undef SRP_DMA_CASE
-  set_error("gram_pass: no DMA pass instance for %d tile slots", slots);
-  return SRP_EINVAL;
-}
-
-// The 4x4-block pass: two views, each of at most 64 tiles (1024 columns);
-// SV = 2 tile slots per view and wave up to 32 tiles, else 4.  k <= 10
-// with 4 slots (beyond that the registers no longer hold the accumulators
-// and operands of a block without spilling inside the row loop), k <= 16
-// with 2.
-static int quad_sv(int d0, int d1) {
-  const int tmax = std::max((d0 + 15) / 16, (d1 + 15) / 16);
-  return tmax <= 32 ? 2 : tmax <= 64 ? 4 : 0;
-}
-
-static size_t quad_lds_bytes(int sv, int c4) {
-  const size_t pitch = (size_t)quad_pitch(2 * sv);
-  const size_t kg = (size_t)(c4 + 1) / 2;
-  return (2 * kDmaRows * pitch + (size_t)kF32Waves * (kDmaRows * 4 * kg + 8) + (size_t)kDmaRows * (4 * c4 + 1)) *
-         sizeof(float);
-}
-
-static bool quad_fits(int d0, int d1, int k, int nb, int vec) {
-  if (nb != 2 || vec == 0 || k < 1) return false;
-  const int sv = quad_sv(d0, d1);
-  const int c4 = (k + 1) / 2;
-  if (sv == 0 || c4 > (sv == 4 ? 5 : 8)) return false;
-  return quad_lds_bytes(sv, c4) <= (size_t)kPassLds + 8 * 1024;
-}
-
-template <int SV, int C4, int VEC>
-static int pass_launch_quad(const float* A0, const float* A1, int64_t n, int d0, int d1, int k, const double* W0,
-                            const double* W1, double* J0, double* J1, const int* done, Arena& ws, hipStream_t st,
-                            hipEvent_t before_pass, hipEvent_t after_pass) {
+  float* Wp1 = ws.take<float>((size_t)dp1 * KP);
   const int nrb = (int)((n + kDmaRows - 1) / kDmaRows);
   // at least 4 blocks per workgroup (fewer partials to add for short data)
   const int grid = std::max(1, std::min(num_cus(), (nrb + 3) / 4));
   const int Dtot = d0 + d1;
   float* part = ws.take<float>((size_t)grid * Dtot * 2 * k);
-  if (!part) { set_error("gram_pass: workspace too small"); return SRP_ENOMEM; }
-  if ((int64_t)std::max(d0, d1) * k * 8 >= 0x7ffff000ll) { set_error("gram_pass: directions too large"); return SRP_EINVAL; }
-  const size_t lds = quad_lds_bytes(SV, C4);
-  SRP_TRY(allow_dynamic_lds((const void*)k_pass_quad<SV, C4, VEC>, kPassLds + 8 * 1024));
+  if (!Wp0 || !Wp1 || !part) { set_error("gram_pass: workspace too small"); return SRP_ENOMEM; }
+  SRP_TRY(pack_dirs<float>(W0, d0, dp0, Wp0, W1, d1, dp1, Wp1, k, KP, st));
+  const size_t lds = dma_lds_bytes(d0, d1);
+  SRP_TRY(allow_dynamic_lds((const void*)k_pass_dma<TPB, VEC>, kPassLds + 8 * 1024));
   if (before_pass) SRP_HIP(hipEventRecord(before_pass, st));
-  hipLaunchKernelGGL((k_pass_quad<SV, C4, VEC>), dim3(grid), dim3(kF32Threads), lds, st, A0, A1, n, d0, d1, k, W0,
-                     W1, nrb, part, done);
+  hipLaunchKernelGGL((k_pass_dma<TPB, VEC>), dim3(grid), dim3(kF32Threads), lds, st, A0, A1, n, d0,
+                     d1, k, Wp0, Wp1, nrb, part, done);
   SRP_LAUNCH_CHECK();
   if (after_pass) SRP_HIP(hipEventRecord(after_pass, st));
   const int64_t count = (int64_t)Dtot * 2 * k;
@@ -1704,83 +1446,94 @@ static int pass_launch_quad(const float* A0, const float* A1, int64_t n, int d0,
   return SRP_OK;
 }
 
-static int pass_dispatch_quad(const float* A0, const float* A1, int64_t n, int d0, int d1, int k, const double* W0,
-                              const double* W1, double* J0, double* J1, const int* done, Arena& ws, hipStream_t st,
-                              hipEvent_t ev0, hipEvent_t ev) {
+static int pass_dispatch_dma(const float* A0, const float* A1, int64_t n, int d0, int d1, int k, const double* W0,
+                             const double* W1, double* J0, double* J1, const int* done, Arena& ws, hipStream_t st,
+                             hipEvent_t ev0, hipEvent_t ev) {
   const int vec = dma_vec(A0, A1, d0, d1);
-  const int sv = quad_sv(d0, d1);
-  const int c4 = (k + 1) / 2;
-#define SRP_QUAD_CASE(SV_, C4_)                                                                                     \
-  if (sv == SV_ && c4 == C4_)                                                                                       \
-    return vec == 4 ? pass_launch_quad<SV_, C4_, 4>(A0, A1, n, d0, d1, k, W0, W1, J0, J1, done, ws, st, ev0, ev) \
-                    : pass_launch_quad<SV_, C4_, 1>(A0, A1, n, d0, d1, k, W0, W1, J0, J1, done, ws, st, ev0, ev);
-  SRP_QUAD_CASE(2, 1) SRP_QUAD_CASE(2, 2) SRP_QUAD_CASE(2, 3) SRP_QUAD_CASE(2, 4)
-  SRP_QUAD_CASE(2, 5) SRP_QUAD_CASE(2, 6) SRP_QUAD_CASE(2, 7) SRP_QUAD_CASE(2, 8)
-  SRP_QUAD_CASE(4, 1) SRP_QUAD_CASE(4, 2) SRP_QUAD_CASE(4, 3) SRP_QUAD_CASE(4, 4)
-  SRP_QUAD_CASE(4, 5)
-#undef SRP_QUAD_CASE
-  set_error("gram_pass: no 4x4-block pass instance for %d slots, k = %d", sv, k);
+  const int slots = dma_slots(d0, d1);
+#define SRP_DMA_CASE(TPB_)                                                                             \
+  if (slots == TPB_)                                                                                   \
+    return vec == 4 ? pass_launch_dma<TPB_, 4>(A0, A1, n, d0, d1, k, W0, W1, J0, J1, done, ws, st, ev0, ev) \
+                    : pass_launch_dma<TPB_, 1>(A0, A1, n, d0, d1, k, W0, W1, J0, J1, done, ws, st, ev0, ev);
+  SRP_DMA_CASE(6) SRP_DMA_CASE(8)
+#undef SRP_DMA_CASE
+  set_error("gram_pass: no DMA pass instance for %d tile slots", slots);
   return SRP_EINVAL;
 }
 
-// The one-view 4x4-block pass: k <= 20, at most 128 tiles (2048 columns);
-// 4 J slots per wave up to 64 tiles, else 8.
-static int quad1_tpb(int d0) {
-  const int T0 = (d0 + 15) / 16;
-  return T0 <= 64 ? 4 : T0 <= 128 ? 8 : 0;
+// The pipelined pass (k_pass_quad): rows of a block for the tiles of
+// [A_0 | A_1], 0 where it has no instance.  Up to 64 tiles two views take
+// k <= 16; beyond, the consumers' registers hold at most five 4-column
+// groups of sums (two views: k <= 10, one: k <= 20), and with a view past 64
+// tiles the producers' hold four (k <= 8; with five they spill: 100000 x
+// (1500 + 300), k = 10 took 314 us, k_pass_dma 262).
+static int pipe_rows(int d0, int d1, int k, int nb) {
+  const int T0 = (d0 + 15) / 16, T1 = nb == 2 ? (d1 + 15) / 16 : 0, TT = T0 + T1;
+  const int c4 = (nb * k + 3) / 4;
+  // views under four tiles leave most of a producer's groups empty
+  if (k < 1 || TT > 128 || T0 < 4 || (nb == 2 && T1 < 4)) return 0;
+  const int rows = TT <= 32 ? 16 : TT <= 64 ? 8 : 4;
+  const int most = nb == 1 ? 5 : rows > 4 ? 8 : std::max(T0, T1) <= 64 ? 5 : 4;
+  return c4 <= most ? rows : 0;
 }
 
-static size_t quad1_lds_bytes(int tpb, int kg) {
-  return (2 * kDmaRows * (size_t)quad_pitch(tpb) + (size_t)kF32Waves * (kDmaRows * 4 * kg + 4) +
-          (size_t)kDmaRows * (4 * kg + 1)) * sizeof(float);
-}
-
-static bool quad1_fits(int d0, int k, int nb, int vec) {
-  if (nb != 1 || vec == 0 || k < 1 || k > 20) return false;
-  const int tpb = quad1_tpb(d0);
-  if (tpb == 0) return false;
-  return quad1_lds_bytes(tpb, (k + 3) / 4) <= (size_t)kPassLds + 8 * 1024;
-}
-
-template <int TPB, int KG, int VEC>
-static int pass_launch_quad1(const float* A0, int64_t n, int d0, int k, const double* W0, double* J0,
-                             const int* done, Arena& ws, hipStream_t st, hipEvent_t before_pass,
-                             hipEvent_t after_pass) {
-  const int dp0 = (d0 + 15) / 16 * 16;
-  const int KP = 4 * KG;
-  float* Wp0 = ws.take<float>((size_t)dp0 * KP);
-  const int nrb = (int)((n + kDmaRows - 1) / kDmaRows);
-  const int grid = std::max(1, std::min(num_cus(), (nrb + 3) / 4));
-  float* part = ws.take<float>((size_t)grid * d0 * k);
-  if (!Wp0 || !part) { set_error("gram_pass: workspace too small"); return SRP_ENOMEM; }
-  SRP_TRY(pack_dirs<float>(W0, d0, dp0, Wp0, nullptr, 0, 0, nullptr, k, KP, st));
-  const size_t lds = quad1_lds_bytes(TPB, KG);
-  SRP_TRY(allow_dynamic_lds((const void*)k_pass_quad1<TPB, KG, VEC>, kPassLds + 8 * 1024));
+template <int NV, int R, int C4, int PG>
+static int pass_launch_pipe(const float* A0, const float* A1, int64_t n, int d0, int d1, int k, const double* W0,
+                            const double* W1, double* J0, double* J1, const int* done, Arena& ws, hipStream_t st,
+                            hipEvent_t before_pass, hipEvent_t after_pass) {
+  using S = PipeShape<NV, R, C4, PG>;
+  static_assert(S::lds_bytes() <= 160 * 1024, "the ring and the partials fit a CU's LDS");
+  const int nrb = (int)((n + S::R - 1) / S::R);
+  // at least 4 blocks per workgroup (fewer partials to add for short data)
+  const int grid = std::max(1, std::min(num_cus(), (nrb + 3) / 4));   // at most one per pair of blocks
+  const int Dtot = d0 + (NV == 2 ? d1 : 0);
+  float* part = ws.take<float>((size_t)grid * Dtot * NV * k);
+  if (!part) { set_error("gram_pass: workspace too small"); return SRP_ENOMEM; }
+  SRP_TRY(allow_dynamic_lds((const void*)k_pass_quad<NV, R, C4, PG>, S::lds_bytes()));
   if (before_pass) SRP_HIP(hipEventRecord(before_pass, st));
-  hipLaunchKernelGGL((k_pass_quad1<TPB, KG, VEC>), dim3(grid), dim3(kF32Threads), lds, st, A0, n, d0, k, Wp0, nrb,
-                     part, done);
+  hipLaunchKernelGGL((k_pass_quad<NV, R, C4, PG>), dim3(grid), dim3(kF32Threads), S::lds_bytes(), st, A0, A1, n,
+                     d0, d1, k, W0, W1, nrb, part, done);
   SRP_LAUNCH_CHECK();
   if (after_pass) SRP_HIP(hipEventRecord(after_pass, st));
-  const int64_t count = (int64_t)d0 * k;
+  const int64_t count = (int64_t)Dtot * NV * k;
   hipLaunchKernelGGL((k_pass_reduce<float>), dim3((unsigned)((count + 63) / 64)), dim3(256), 0, st, part, grid, d0,
-                     0, k, J0, (double*)nullptr, done, t_pass_ran);
+                     NV == 2 ? d1 : 0, NV * k, J0, J1, done, t_pass_ran);
   SRP_LAUNCH_CHECK();
   return SRP_OK;
 }
 
-static int pass_dispatch_quad1(const float* A0, int64_t n, int d0, int k, const double* W0, double* J0,
-                               const int* done, Arena& ws, hipStream_t st, hipEvent_t ev0, hipEvent_t ev) {
-  const int vec = dma_vec(A0, nullptr, d0, 0);
-  const int tpb = quad1_tpb(d0);
-  const int kg = (k + 3) / 4;
-#define SRP_QUAD1_CASE(TPB_, KG_)                                                                              \
-  if (tpb == TPB_ && kg == KG_)                                                                                \
-    return vec == 4 ? pass_launch_quad1<TPB_, KG_, 4>(A0, n, d0, k, W0, J0, done, ws, st, ev0, ev)            \
-                    : pass_launch_quad1<TPB_, KG_, 1>(A0, n, d0, k, W0, J0, done, ws, st, ev0, ev);
-  SRP_QUAD1_CASE(4, 1) SRP_QUAD1_CASE(4, 2) SRP_QUAD1_CASE(4, 3) SRP_QUAD1_CASE(4, 4) SRP_QUAD1_CASE(4, 5)
-  SRP_QUAD1_CASE(8, 1) SRP_QUAD1_CASE(8, 2) SRP_QUAD1_CASE(8, 3) SRP_QUAD1_CASE(8, 4) SRP_QUAD1_CASE(8, 5)
-#undef SRP_QUAD1_CASE
-  set_error("gram_pass: no one-view 4x4-block pass instance for %d slots, k = %d", tpb, k);
+static int pass_dispatch_pipe(const float* A0, const float* A1, int64_t n, int d0, int d1, int k, const double* W0,
+                              const double* W1, double* J0, double* J1, const int* done, Arena& ws, hipStream_t st,
+                              hipEvent_t ev0, hipEvent_t ev) {
+  const int nb = A1 ? 2 : 1, c4 = (nb * k + 3) / 4;
+  int rows = pipe_rows(d0, d1, k, nb);
+  // short data: smaller blocks for more workgroups (a workgroup takes at
+  // least four blocks: 1500 x (301 + 203), k = 8 takes 15.3 us with 4 rows a
+  // block, 18.4 with 16; 3000 x (400 + 300), k = 4 16.8 with 4, 15.7 with 8)
+  while (c4 <= 5 && rows > 4 && n < (int64_t)rows * num_cus()) rows /= 2;
+  // groups of the busiest producer: a quarter of the wider view's 4-tile
+  // groups with two views, an eighth with one
+  const int tmax = (std::max(d0, nb == 2 ? d1 : 0) + 15) / 16;
+  const int pg = ((tmax + 3) / 4 + 8 / nb - 1) / (8 / nb);
+#define SRP_PIPE_CASE(NV_, R_, C4_, PG_)                                                                         \
+  if (nb == NV_ && rows == R_ && c4 == C4_ && pg <= PG_)                                                         \
+    return pass_launch_pipe<NV_, R_, C4_, PG_>(A0, A1, n, d0, d1, k, W0, W1, J0, J1, done, ws, st, ev0, ev);
+#define SRP_PIPE_FIVE(NV_, R_, PG_)                                                                              \
+  SRP_PIPE_CASE(NV_, R_, 1, PG_) SRP_PIPE_CASE(NV_, R_, 2, PG_) SRP_PIPE_CASE(NV_, R_, 3, PG_)                   \
+  SRP_PIPE_CASE(NV_, R_, 4, PG_) SRP_PIPE_CASE(NV_, R_, 5, PG_)
+  SRP_PIPE_FIVE(1, 16, 1)
+  SRP_PIPE_FIVE(1, 8, 1) SRP_PIPE_FIVE(1, 8, 2)
+  SRP_PIPE_FIVE(1, 4, 1) SRP_PIPE_FIVE(1, 4, 2) SRP_PIPE_FIVE(1, 4, 4)
+  SRP_PIPE_FIVE(2, 16, 1) SRP_PIPE_FIVE(2, 16, 2)
+  SRP_PIPE_FIVE(2, 8, 1) SRP_PIPE_FIVE(2, 8, 2) SRP_PIPE_FIVE(2, 8, 4)
+  SRP_PIPE_FIVE(2, 4, 1) SRP_PIPE_FIVE(2, 4, 2) SRP_PIPE_FIVE(2, 4, 4)
+  SRP_PIPE_CASE(2, 4, 1, 8) SRP_PIPE_CASE(2, 4, 2, 8) SRP_PIPE_CASE(2, 4, 3, 8) SRP_PIPE_CASE(2, 4, 4, 8)
+  SRP_PIPE_CASE(2, 16, 6, 2) SRP_PIPE_CASE(2, 16, 7, 2) SRP_PIPE_CASE(2, 16, 8, 2)
+  SRP_PIPE_CASE(2, 8, 6, 2) SRP_PIPE_CASE(2, 8, 7, 2) SRP_PIPE_CASE(2, 8, 8, 2)
+  SRP_PIPE_CASE(2, 8, 6, 4) SRP_PIPE_CASE(2, 8, 7, 4) SRP_PIPE_CASE(2, 8, 8, 4)
+#undef SRP_PIPE_FIVE
+#undef SRP_PIPE_CASE
+  set_error("gram_pass: no pipelined pass instance for %d rows, k = %d", rows, k);
   return SRP_EINVAL;
 }
 
@@ -1809,8 +1562,7 @@ const char* gram_pass_kernel_name(int dtype, int compute, int d0, int d1, int k)
   }
   if (compute == SRP_F32 && dtype == SRP_F32) {
     const int vec = (al && T0 >= 16 && (nb == 1 || T1 >= 16)) ? 4 : (T0 >= 4 && (nb == 1 || T1 >= 4)) ? 1 : 0;
-    if (quad1_fits(d0, k, nb, vec)) return "k_pass_quad1";
-    if (quad_fits(d0, d1, k, nb, vec)) return "k_pass_quad";
+    if (pipe_rows(d0, d1, k, nb)) return nb == 1 ? "k_pass_quad1" : "k_pass_quad";
     if (dma_fits(d0, d1, k, nb, vec)) return "k_pass_dma";
   }
   return "k_pass";
@@ -1850,10 +1602,8 @@ int gram_pass_run(const void* A0, const void* A1, int dtype, int compute, int64_
   } else {
     switch (dtype) {
       case SRP_F32:
-        if (quad1_fits(d0, k, nb, dma_vec(A0, A1, d0, d1)))
-          return pass_dispatch_quad1((const float*)A0, n, d0, k, W0, J0, done, ws, st, before_pass, after_pass);
-        if (quad_fits(d0, nb == 2 ? d1 : 0, k, nb, dma_vec(A0, A1, d0, d1)))
-          return pass_dispatch_quad((const float*)A0, (const float*)A1, n, d0, d1, k, W0, W1, J0, J1, done, ws, st,
+        if (pipe_rows(d0, d1, k, nb))
+          return pass_dispatch_pipe((const float*)A0, (const float*)A1, n, d0, d1, k, W0, W1, J0, J1, done, ws, st,
                                     before_pass, after_pass);
         if (dma_fits(d0, nb == 2 ? d1 : 0, k, nb, dma_vec(A0, A1, d0, d1)))
           return pass_dispatch_dma((const float*)A0, (const float*)A1, n, d0, d1, k, W0, W1, J0, J1, done, ws, st,

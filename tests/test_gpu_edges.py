@@ -110,3 +110,37 @@ def test_csr_structure_refused(fault):
         with pytest.raises(srp.SrpError, match=name) as e:
             srp.srp_gram_pass_csr(pair[0], W, pair[1], W)
         assert e.value.code == srp.SRP_EINVAL
+
+
+# blocks of 4, 8 and 16 rows at their last and first widths (32, 33, 64, 65
+# and 128 tiles of 16 columns), a tile with one column, views just wide
+# enough, rows off every 16-byte boundary, fewer rows than a block or a pair
+# of blocks, an odd last block, short data on smaller blocks, direction
+# groups with and without whole tiles, uneven views on either side of the
+# producers' limit, more than the memory-side cache holds
+@pytest.mark.parametrize("n,d0,d1,k,off", [(1, 64, 49, 1, 0), (3, 513, 0, 20, 1), (17, 49, 0, 16, 3),
+                                           (8209, 256, 256, 16, 0), (8200, 257, 256, 9, 1), (9001, 512, 0, 17, 2),
+                                           (9001, 513, 511, 14, 3), (2047, 1024, 0, 20, 0), (2049, 1025, 0, 3, 1),
+                                           (1777, 1024, 1024, 10, 0), (1779, 1023, 1017, 7, 2), (777, 2048, 0, 19, 0),
+                                           (640, 1500, 500, 10, 0), (3001, 99, 1201, 5, 3),
+                                           (70003, 999, 2, 4, 0), (70001, 1000, 0, 12, 1)])
+def test_gram_pass_block_edges(n, d0, d1, k, off):
+    srp = _srp()
+    rng = np.random.default_rng(n + d0 + d1)
+    A = [rng.standard_normal((n, d), dtype=np.float32) for d in (d0, d1) if d]
+    W = [rng.standard_normal((d, k)) for d in (d0, d1) if d]
+    if d1 >= 49 and n > 2:
+        A[1][n // 2, 33] = np.inf   # touches row 33 of J_1 and the products with P_1, nothing else
+    D = [off_boundary(a, off + 1 - i) if off else off_boundary(a, 0) for i, a in enumerate(A)]
+    out = srp.srp_gram_pass(D[0], torch.from_numpy(W[0]).to(DEV), *([D[1], torch.from_numpy(W[1]).to(DEV)] if d1 else []))
+    Q = [a.astype(np.float64) for a in A]
+    with np.errstate(invalid="ignore"):
+        P = np.concatenate([a @ w for a, w in zip(Q, W)], axis=1)
+        Pabs = np.concatenate([np.abs(a) @ np.abs(w) for a, w in zip(Q, W)], axis=1)
+        ref, mag = [a.T @ P for a in Q], [np.abs(a).T @ Pabs for a in Q]
+    for g, r, m in zip(out, ref, mag):
+        g = g.cpu().numpy()
+        ok = np.isfinite(r)
+        assert np.array_equal(np.isfinite(g), ok)
+        bound = (d0 + d1 + n + 2) * 2.0 ** -24 * m[ok]
+        assert np.all(np.abs(g[ok] - r[ok]) <= bound)
