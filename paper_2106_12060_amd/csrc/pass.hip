@@ -90,20 +90,21 @@ template <> __device__ __forceinline__ double cvt<double, bf16>(bf16 v) { return
 constexpr int kPassSplit = 2;   // column halves per row block
 constexpr int kXcds = 8;
 
-template <class DT, class CT, int NB, int KT>
+// TMAX: most tiles of [A_0 | A_1] (two views that do not end on tiles take
+// one more than their columns alone would).
+template <class DT, class CT, int NB, int KT, int TMAX>
 __global__ void __launch_bounds__(kPassThreads) k_pass(const DT* __restrict__ A0, const DT* __restrict__ A1,
                                                        int64_t n, int d0, int d1, int k,
                                                        const CT* __restrict__ Wp0, const CT* __restrict__ Wp1,
                                                        int nrb, CT* __restrict__ partial,
                                                        const int* __restrict__ done) {
   if (done && *done) return;
-  constexpr int DMAX = PassCfg<CT>::dmax;
   constexpr int JPR = PassCfg<CT>::jpr;
   constexpr int JPF = PassCfg<CT>::jpf;
-  constexpr int TPW = (DMAX / 16 + kPassWaves * kPassSplit - 1) / (kPassWaves * kPassSplit);
+  constexpr int TPW = (TMAX + kPassWaves * kPassSplit - 1) / (kPassWaves * kPassSplit);
   constexpr int NT = NB * KT;
   constexpr int KP = KT * 16;
-  constexpr int TPB = (DMAX / 16 + kPassWaves - 1) / kPassWaves;        // P tiles per wave
+  constexpr int TPB = (TMAX + kPassWaves - 1) / kPassWaves;        // P tiles per wave
   constexpr bool WREG = TPB * 4 * KT * (int)sizeof(CT) <= 64 * 4;       // W operands in registers
   using acc_t = typename Acc4<CT>::type;
   extern __shared__ unsigned char pass_smem[];
@@ -1404,11 +1405,18 @@ static int pass_launch(const DT* A0, const DT* A1, int64_t n, int d0, int d1, in
   SRP_TRY(pack_dirs<CT>(W0, d0, dp0, Wp0, W1, d1, dp1, Wp1, k, KP, st));
   const int nrb = (int)((n + 15) / 16);
   const size_t lds = pass_lds_bytes<CT>(Dtot, NB * KT);
-  SRP_TRY(allow_dynamic_lds((const void*)k_pass<DT, CT, NB, KT>, kPassLds));
-  if (before_pass) SRP_HIP(hipEventRecord(before_pass, st));
-  hipLaunchKernelGGL((k_pass<DT, CT, NB, KT>), dim3(grid), dim3(kPassThreads), lds, st, A0, A1, n, d0,
-                     NB == 2 ? d1 : 0, k, Wp0, Wp1, nrb, part, done);
-  SRP_LAUNCH_CHECK();
+  constexpr int TM = PassCfg<CT>::dmax / 16;
+  auto launch = [&](auto tmax) -> int {
+    constexpr int T = decltype(tmax)::value;
+    SRP_TRY(allow_dynamic_lds((const void*)k_pass<DT, CT, NB, KT, T>, kPassLds));
+    if (before_pass) SRP_HIP(hipEventRecord(before_pass, st));
+    hipLaunchKernelGGL((k_pass<DT, CT, NB, KT, T>), dim3(grid), dim3(kPassThreads), lds, st, A0, A1, n, d0,
+                       NB == 2 ? d1 : 0, k, Wp0, Wp1, nrb, part, done);
+    SRP_LAUNCH_CHECK();
+    return SRP_OK;
+  };
+  if (NB == 2 && (dp0 + dp1) / 16 > TM) SRP_TRY(launch(std::integral_constant<int, TM + (NB == 2 ? 1 : 0)>{}));
+  else SRP_TRY(launch(std::integral_constant<int, TM>{}));
   if (after_pass) SRP_HIP(hipEventRecord(after_pass, st));
   const int64_t count = (int64_t)Dtot * NB * k;
   hipLaunchKernelGGL((k_pass_reduce<CT>), dim3((unsigned)((count + 63) / 64)), dim3(256), 0, st, part, groups, d0,

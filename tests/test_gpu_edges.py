@@ -144,3 +144,23 @@ def test_gram_pass_block_edges(n, d0, d1, k, off):
         assert np.array_equal(np.isfinite(g), ok)
         bound = (d0 + d1 + n + 2) * 2.0 ** -24 * m[ok]
         assert np.all(np.abs(g[ok] - r[ok]) <= bound)
+
+
+# two views whose tiles are one more than their columns fill: the last of
+# 129 (FP32, BF16 data) and of 57 (FP64)
+@pytest.mark.parametrize("d0,d1,dt,comp", [(1985, 63, "f32", "f32"), (1025, 1023, "bf16", "f32"), (449, 447, "f64", "f64"),
+                                           (833, 63, "f32", "f64")])
+def test_gram_pass_one_tile_more(d0, d1, dt, comp):
+    srp = _srp()
+    rng = np.random.default_rng(d0)
+    tdt = {"f32": torch.float32, "bf16": torch.bfloat16, "f64": torch.float64}[dt]
+    n, k = 701, 8
+    A = [torch.from_numpy(rng.standard_normal((n, d))).to(tdt).to(DEV) for d in (d0, d1)]
+    W = [rng.standard_normal((d, k)) for d in (d0, d1)]
+    out = srp.srp_gram_pass(A[0], torch.from_numpy(W[0]).to(DEV), A[1], torch.from_numpy(W[1]).to(DEV), compute=comp)
+    Q = [a.double().cpu().numpy() for a in A]
+    P = np.concatenate([a @ w for a, w in zip(Q, W)], axis=1)
+    Pabs = np.concatenate([np.abs(a) @ np.abs(w) for a, w in zip(Q, W)], axis=1)
+    u = 2.0 ** -53 if comp == "f64" else 2.0 ** -24
+    for g, q in zip(out, Q):
+        assert np.all(np.abs(g.cpu().numpy() - q.T @ P) <= (d0 + d1 + n + 2) * u * (np.abs(q).T @ Pabs))
