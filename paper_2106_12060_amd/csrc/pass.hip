@@ -321,8 +321,6 @@ __global__ void __launch_bounds__(kPassThreads) k_pass(const DT* __restrict__ A0
 // rows 8-15 A_1 W_1 (each lane zeroes the operand of the other view), so
 // one accumulator serves both views and the tile loop has no view branch.
 constexpr int kDmaRows = 8;
-constexpr int kDmaWaves = 8;
-constexpr int kDmaThreads = 64 * kDmaWaves;
 constexpr int kDmaMaxTiles = 128;   // 2048 columns of [A_0 | A_1]
 // The FP32 pass runs 16 waves (4 per SIMD, 128 registers each): a wave
 // holds the direction operands and the J accumulators of at most 8 tiles.
@@ -1042,22 +1040,37 @@ __global__ void __launch_bounds__(256) k_pass_reduce(const CT* __restrict__ part
 
 // ------------------------------------------------------------------
 // BF16 data with BF16 matrix-core products (FP32 accumulation): the
-// low-precision form of the pass.  Same streaming scheme as the FP32 DMA
-// pass (double-buffered global-to-LDS row blocks, direction operands in
-// registers, one workgroup owns whole rows), with 16-row blocks:
-//   (b) P_b = A_b W_b on 16x16x32 BF16 MFMA over 32-column tiles (A_1's
-//       tiles start on a 32-column boundary, so no tile mixes the blocks;
-//       the pad columns are zero in LDS and in the packed direction);
-//   (c) the wave partials of P are summed in FP32 and rounded to BF16,
-//       stored pcol-major so a lane's four rows are one 8-byte read;
-//   (d) A_b^T [P_0 | P_1] on 16x16x16 BF16 MFMA, the 16 rows of the block
-//       as the contraction.
-constexpr int kBfRows = 16;
+// low-precision form of the pass, pipelined like k_pass_quad over one loader,
+// three producer and eight consumer waves (three waves a SIMD, 168 registers
+// each: the consumers hold the 32 x 2048 sums of a CU):
+//   * the loader moves rows of R (8, or 16 up to 64 tiles) into a ring of
+//     four LDS blocks, 16 bytes a lane, and the last d % 8 columns of a row
+//     4 bytes a lane: no column past a view's last is written, so those of
+//     its last 32-column tile stay zero (A_1's tiles start on a 32-column
+//     boundary);
+//   * the producers form P_b = A_b W_b on 16x16x32 products.  32-column tile
+//     T belongs to chain T mod 8; a chain's tiles are summed in turn by the
+//     matrix cores and the eight chains in order 0 .. 7: chains 0 - 2 by
+//     their producer, the others' sums are added by the consumers.  Eight
+//     rows fill half the product's rows (the others repeat them);
+//   * the consumers round P to BF16 and accumulate J = A^T [P_0 | P_1] for 32
+//     columns of A and the 32 of [P_0 | P_1] (16 a view) at a time on
+//     32x32x8 products, whose contraction is eight rows of a block; A comes
+//     transposed out of LDS (ds_read_b64_tr_b16: a lane's column, four rows).
+// Bounds: the row stream (5.3 to 5.7 TB/s); narrow rows, the chain of a step.
+// Measured, us, against eight waves that did both products in turn with A
+// read from LDS two bytes a lane: 200000 x (1000 + 1000), k = 10 230 -> 151;
+// 100000 x 2000, k = 16 96 -> 71; 52344 x (532 + 348), k = 9 83 -> 28;
+// 100000 x (1002 + 998), k = 3 (4-byte loads before) 267 -> 79.
+constexpr int kBfProd = 3, kBfCons = 8;
+constexpr int kBfThreads = 64 * (kBfProd + kBfCons + 1);
+constexpr int kBfChains = 8, kBfParts = 6;   // chain sums a row's element of P is stored as
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 struct BfGeom {
-  int T0, T1, T0p, T1p, TTp, pitch;   // pitch in bf16 elements
+  int T0, T1, T0p, T1p, TTp;
 };
 __host__ __device__ inline BfGeom bf_geom(int d0, int d1) {
   BfGeom g;
@@ -1066,265 +1079,276 @@ __host__ __device__ inline BfGeom bf_geom(int d0, int d1) {
   g.T0p = (g.T0 + 1) & ~1;
   g.T1p = (g.T1 + 1) & ~1;
   g.TTp = g.T0p + g.T1p;
-  g.pitch = g.TTp * 16 + 8;
   return g;
 }
 
-template <int VEC>
-__device__ __forceinline__ void dma_row_chunk_bf(__amdgpu_buffer_rsrc_t r, unsigned short* lds_dst, int voff) {
-  if constexpr (VEC == 8)
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds_dst, 16, voff, 0, 0, 0);
-  else
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds_dst, 4, voff, 0, 0, 0);
-}
+// TPC: 32-column tiles of a chain, and of a consumer.
+template <int R_, int TPC_>
+struct BfShape {
+  static constexpr int R = R_, TPC = TPC_;
+  // row pitch in elements, 64 bytes mod 256: rows 0 - 3 of a transposed read
+  // and of the producers' 64-byte runs fall on all 64 banks
+  static constexpr int PITCH = 32 * kBfChains * TPC + 32;
+  static constexpr int BUF = R * PITCH;
+  static constexpr int PART = R * 32 * kBfParts;   // floats: [R][32] of four, then [R][32] of two
+  static constexpr size_t lds_bytes() { return (size_t)kPipeRing * BUF * 2 + 2 * PART * 4; }
+};
 
-// Pack double d x k directions into zero-padded (ceil32(d) x 16) BF16.
-__global__ void k_pack_dir_bf(const double* __restrict__ W0, int d0, int dp0, unsigned short* __restrict__ Wp0,
-                              const double* __restrict__ W1, int d1, int dp1, unsigned short* __restrict__ Wp1,
-                              int k) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n0 = dp0 * 16;
-  const double* W = W0;
-  unsigned short* Wp = Wp0;
-  int d = d0;
-  if (i >= n0) {
-    i -= n0;
-    if (i >= dp1 * 16) return;
-    W = W1; Wp = Wp1; d = d1;
-  }
-  const int r = i >> 4, c = i & 15;
-  const float v = (r < d && c < k) ? (float)W[(int64_t)r * k + c] : 0.0f;
+// The directions as the producers' operands: lane (l16, g) of 32-column tile T
+// takes W[32 T + 8 g + e][l16], e < 8 (zero past d and k; A_1's tiles from
+// tiles0 on).
+__global__ void k_pack_dir_bf(const double* __restrict__ W0, int d0, const double* __restrict__ W1, int d1, int tiles0,
+                              int k, int count, uint16_t* __restrict__ Wp) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= count) return;
+  const int e = i & 7, l16 = (i >> 3) & 15, g = (i >> 7) & 3, T = i >> 9;
+  const bool b1 = T >= tiles0;
+  const int r = 32 * (b1 ? T - tiles0 : T) + 8 * g + e;
+  const float v = r < (b1 ? d1 : d0) && l16 < k ? (float)(b1 ? W1 : W0)[(int64_t)r * k + l16] : 0.0f;
   Wp[i] = bf16_rne_bits(v);
 }
 
-// Per-block work of k_pass_bf; the LDS regions arrive as separate restrict
-// pointers so that the reads of the current block, the partials and P carry
-// alias scopes disjoint from the next block's in-flight DMA (see quad_step).
-template <int NB, int VEC>
-__device__ __forceinline__ void bf_step(const unsigned short* __restrict__ xs, unsigned short* __restrict__ xnext,
-                                        float* __restrict__ red, unsigned short* __restrict__ pb, int next_rb,
-                                        const unsigned short* A0, const unsigned short* A1, int64_t n, int d0,
-                                        int d1, const BfGeom& G, int nch0, int nch, int w, int lane,
-                                        const bf16x8_t (&wreg)[(kDmaMaxTiles / 2 + kDmaWaves - 1) / kDmaWaves],
-                                        f32x4 (&acc)[(kDmaMaxTiles + kDmaWaves - 1) / kDmaWaves][NB], bool dma_only) {
-  constexpr int R = kBfRows;
-  constexpr int CH = 64 * VEC;
-  constexpr int NT = NB;
-  constexpr int TPB32 = (kDmaMaxTiles / 2 + kDmaWaves - 1) / kDmaWaves;
-  constexpr int TPB = (kDmaMaxTiles + kDmaWaves - 1) / kDmaWaves;
-  const int tid = threadIdx.x;
+// The loads of the R rows at a0 (and a1), `left` of them before the end of
+// the data (rows past it read zero).  Returns the number in flight.
+template <int NB, class S, bool NT>
+__device__ __forceinline__ int bf_load(const unsigned short* a0, const unsigned short* a1, int64_t left, int d0, int d1,
+                                       int T0p, unsigned short* __restrict__ dst, int lane) {
+  int cnt = 0;
+#pragma unroll
+  for (int v = 0; v < NB; ++v) {
+    const int d = v ? d1 : d0, whole = d & ~7, tail = d & 7;
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(v ? a1 : a0, left * d * 2);
+    unsigned short* dv = dst + (v ? T0p * 16 : 0);
+    for (int c0 = 0; c0 < whole; c0 += 512) {
+      const int c = c0 + 8 * lane;
+      if (c < whole)
+#pragma unroll
+        for (int r = 0; r < S::R; ++r) dma_row_chunk<4, NT>(rs, (float*)(dv + r * S::PITCH + c0), (r * d + c) * 2);
+      cnt += S::R;
+    }
+    if (tail) {
+      if (2 * lane < tail)
+#pragma unroll
+        for (int r = 0; r < S::R; ++r)
+          dma_row_chunk<1>(rs, (float*)(dv + r * S::PITCH + whole), (r * d + whole + 2 * lane) * 2);
+      cnt += S::R;
+    }
+  }
+  return cnt;
+}
+
+__device__ __forceinline__ void bf_wait(int n) {   // at most n (a multiple of 8) of this wave's loads outstanding
+  switch (n) {
+#define SRP_VM(N) case N: __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8)); break;
+    SRP_VM(8) SRP_VM(16) SRP_VM(24) SRP_VM(32) SRP_VM(40) SRP_VM(48) SRP_VM(56)
+#undef SRP_VM
+    default: __builtin_amdgcn_s_waitcnt((0x7 << 4) | (0xF << 8));
+  }
+}
+
+// A producer's chains (NCH from c0 on) of P for the block in xs.
+template <class S, int NB, int NCH>
+__device__ __forceinline__ void bf_produce(const unsigned short* __restrict__ xs, float* __restrict__ part, int lane,
+                                           int c0, int tiles0, const bf16x8_t (&wreg)[NCH][S::TPC]) {
+  constexpr int R = S::R, TPC = S::TPC;
   const int g = lane >> 4, l16 = lane & 15;
-  const int pitch = G.pitch;
-  if (next_rb >= 0) {
-    const int nq = R * nch;
-    for (int q = w; q < nq; q += kDmaWaves) {
-      const int r = q / nch, j = q - r * nch;
-      const int64_t row = (int64_t)next_rb * R + r;
-      const bool s1 = (NB == 2) && (j >= nch0);
-      const int jj = s1 ? j - nch0 : j;
-      const int span = (s1 ? G.T1 : G.T0) * 16;
-      const int o = min(jj * CH, span - CH);
-      unsigned short* dst = xnext + r * pitch + (s1 ? G.T0p * 16 : 0) + o;
-      const int voff = (o + lane * VEC) * 2;
-      if (s1) dma_row_chunk_bf<VEC>(make_rsrc(A1 + row * d1, row < n ? (int64_t)d1 * 2 : 0), dst, voff);
-      else dma_row_chunk_bf<VEC>(make_rsrc(A0 + row * d0, row < n ? (int64_t)d0 * 2 : 0), dst, voff);
+  const unsigned short* xp = xs + (l16 & (R - 1)) * S::PITCH + 8 * g;
+  f32x4 sum[NB];
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) {
+    f32x4 pacc[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) pacc[b] = f32x4{0, 0, 0, 0};
+    // four operands read ahead of their products; past the last tile zeros
+    // meet zeros
+    constexpr int B = TPC < 4 ? TPC : 4;
+#pragma unroll
+    for (int i0 = 0; i0 < TPC; i0 += B) {
+      bf16x8_t a[B];
+#pragma unroll
+      for (int u = 0; u < B; ++u) a[u] = *reinterpret_cast<const bf16x8_t*>(xp + 32 * (c0 + c + kBfChains * (i0 + u)));
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        if (NB == 2 && c0 + c + kBfChains * (i0 + u) >= tiles0)
+          pacc[NB - 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u], wreg[c][i0 + u], pacc[NB - 1], 0, 0, 0);
+        else pacc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u], wreg[c][i0 + u], pacc[0], 0, 0, 0);
+      }
     }
-  }
-  if (dma_only) return;
-  const int base_b = l16 * pitch + 8 * g + 32 * w;    // P phase: row l16, columns 32 T + 8 g .. + 7
-  const int base_d = (4 * g) * pitch + l16 + 16 * w;  // J phase: rows 4 g .. 4 g + 3, column 16 t + l16
-  // (b)
-  f32x4 pacc[NB];
 #pragma unroll
-  for (int b = 0; b < NB; ++b) pacc[b] = f32x4{0, 0, 0, 0};
+    for (int b = 0; b < NB; ++b) {
+      if (c0 == 0 && c > 0) sum[b] += pacc[b];   // chains 0 - 2: one partial
+      else sum[b] = pacc[b];
+      // partial 0 is chains 0 - 2, partial m > 0 chain m + 2
+      const int m = c0 == 0 ? (c == 2 ? 0 : -1) : c0 + c - 2;
+      if (m >= 0 && 4 * g < R) {
+        float* pw = part + (m < 4 ? m : R * 32 * 4 + m - 4);
+        const int st = m < 4 ? 4 : 2;
 #pragma unroll
-  for (int i = 0; i < TPB32; ++i) {
-    const int T = w + kDmaWaves * i;
-    if (2 * T < G.TTp) {
-      const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(xs + base_b + 32 * kDmaWaves * i);
-      if (NB == 2 && 2 * T >= G.T0p) pacc[NB - 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wreg[i], pacc[NB - 1], 0, 0, 0);
-      else pacc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wreg[i], pacc[0], 0, 0, 0);
-    }
-  }
-  // (c)
-#pragma unroll
-  for (int b = 0; b < NB; ++b)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) red[(w * NT + b) * 256 + (4 * g + r) * 16 + l16] = pacc[b][r];
-  lds_only_barrier();
-  for (int e = tid; e < NT * 256; e += kDmaThreads) {
-    const int nt = e >> 8, q = e & 255;   // q = row * 16 + pcol
-    float v = 0.f;
-#pragma unroll
-    for (int ww = 0; ww < kDmaWaves; ++ww) v += red[(ww * NT + nt) * 256 + q];
-    pb[nt * 256 + (q & 15) * 16 + (q >> 4)] = bf16_rne_bits(v);
-  }
-  lds_only_barrier();
-  // (d)
-  s16x4_t bop[NT];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) bop[nt] = *reinterpret_cast<const s16x4_t*>(pb + nt * 256 + l16 * 16 + 4 * g);
-#pragma unroll
-  for (int i = 0; i < TPB; ++i) {
-    const int t = w + kDmaWaves * i;
-    if (t < G.TTp) {
-      const unsigned short* xp = xs + base_d + 16 * kDmaWaves * i;
-      s16x4_t a;
-      a[0] = (short)xp[0];
-      a[1] = (short)xp[pitch];
-      a[2] = (short)xp[2 * pitch];
-      a[3] = (short)xp[3 * pitch];
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) acc[i][nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bop[nt], acc[i][nt], 0, 0, 0);
+        for (int r = 0; r < 4; ++r) pw[((4 * g + r) * 32 + 16 * b + l16) * st] = sum[b][r];
+      }
     }
   }
 }
 
-template <int NB, int VEC>
-__global__ void __launch_bounds__(kDmaThreads) k_pass_bf(const unsigned short* __restrict__ A0,
-                                                         const unsigned short* __restrict__ A1, int64_t n, int d0,
-                                                         int d1, int k, const unsigned short* __restrict__ Wp0,
-                                                         const unsigned short* __restrict__ Wp1, int nrb,
-                                                         float* __restrict__ partial, const int* __restrict__ done) {
-  if (done && *done) return;
-  constexpr int R = kBfRows;
-  constexpr int CH = 64 * VEC;          // bf16 elements per load instruction
-  constexpr int NT = NB;                // k <= 16: one k-tile per block
-  constexpr int TPB32 = (kDmaMaxTiles / 2 + kDmaWaves - 1) / kDmaWaves;   // 32-column P tiles per wave
-  constexpr int TPB = (kDmaMaxTiles + kDmaWaves - 1) / kDmaWaves;         // 16-column J tiles per wave
-  extern __shared__ unsigned short bsm[];
-  const BfGeom G = bf_geom(d0, NB == 2 ? d1 : 0);
-  const int pitch = G.pitch;
-  unsigned short* xsb0 = bsm;
-  float* red = reinterpret_cast<float*>(bsm + 2 * R * pitch);          // [waves][NT][256]
-  unsigned short* pb = reinterpret_cast<unsigned short*>(red + kDmaWaves * NT * 256);   // [NT][16 pcol][16 row]
+// A consumer's step: J += A^T [P_0 | P_1] over tiles wj, wj + 8, ...
+template <class S, int NB>
+__device__ __forceinline__ void bf_consume(const unsigned short* __restrict__ xs, const float* __restrict__ part,
+                                           int wj, int lane, f32x16 (&acc)[S::TPC]) {
+  const int n = lane & 31, h = lane >> 5;
+  // lane's piece of a transposed read: row 4 h + (lane % 16) / 4 of eight,
+  // four columns
+  const unsigned short* xr = xs + (4 * h + ((lane & 15) >> 2)) * S::PITCH + 16 * ((lane >> 4) & 1) + 4 * (lane & 3) +
+                             32 * wj;
+#pragma unroll
+  for (int q = 0; q < S::R / 8; ++q) {   // eight rows at a time
+    s16x4_t a[S::TPC], pb;
+#pragma unroll
+    for (int i = 0; i < S::TPC; ++i)
+      a[i] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+          (__attribute__((address_space(3))) s16x4_t*)(xr + 8 * q * S::PITCH + 32 * kBfCons * i));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int el = (8 * q + 4 * h + e) * 32 + n;
+      const float4 u = *reinterpret_cast<const float4*>(part + el * 4);
+      const float2 v = *reinterpret_cast<const float2*>(part + S::R * 32 * 4 + el * 2);
+      const float x = ((((u.x + u.y) + u.z) + u.w) + v.x) + v.y;
+      pb[e] = NB == 2 || n < 16 ? __builtin_bit_cast(short, (__bf16)x) : (short)0;
+    }
+#pragma unroll
+    for (int i = 0; i < S::TPC; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a[i], pb, acc[i], 0, 0, 0);
+  }
+}
 
+template <int NB, int R_, int TPC_>
+__global__ void __launch_bounds__(kBfThreads) k_pass_bf(const unsigned short* __restrict__ A0,
+                                                        const unsigned short* __restrict__ A1, int64_t n, int d0,
+                                                        int d1, int k, const bf16x8_t* __restrict__ Wp, int nrb,
+                                                        float* __restrict__ partial, const int* __restrict__ done) {
+  if (done && *done) return;
+  using S = BfShape<R_, TPC_>;
+  constexpr int R = S::R, TPC = S::TPC;
+  extern __shared__ unsigned short bsm[];
+  float* parts = reinterpret_cast<float*>(bsm + kPipeRing * S::BUF);
+  const BfGeom G = bf_geom(d0, NB == 2 ? d1 : 0);
+  const int tiles = G.TTp / 2, tiles0 = G.T0p / 2;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = lane >> 4, l16 = lane & 15;
-  const int nch0 = (G.T0 * 16 + CH - 1) / CH, nch1 = NB == 2 ? (G.T1 * 16 + CH - 1) / CH : 0;
-  const int nch = nch0 + nch1;
-
-  // zero the pad columns of both buffers once (no load ever writes them)
-  for (int e = tid; e < 2 * R * (G.TTp * 16); e += kDmaThreads) {
-    const int rr = e / (G.TTp * 16), c = e - rr * (G.TTp * 16);
-    const bool pad = (c >= G.T0 * 16 && c < G.T0p * 16) || (c >= G.T0p * 16 + G.T1 * 16);
-    if (pad) xsb0[rr * pitch + c] = 0;
-  }
-  // direction operands: 32-column tile T = w + 8 i, lane (l16, g) holds
-  // W[32 T + 8 g + e][l16] for e < 8 (A_1's rows start at T0p / 2)
-  bf16x8_t wreg[TPB32];
-#pragma unroll
-  for (int i = 0; i < TPB32; ++i) {
-    const int T = w + kDmaWaves * i;
-    const bool b1 = (NB == 2) && (2 * T >= G.T0p);
-    const int rowb = b1 ? 32 * T - 16 * G.T0p : 32 * T;
-    const unsigned short* Wp = b1 ? Wp1 : Wp0;
-    const int lim = b1 ? G.T1p * 16 : G.T0p * 16;
-    bf16x8_t v;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int r = rowb + 8 * g + e;
-      const unsigned short bits = (2 * T < G.TTp && r < lim) ? Wp[r * 16 + l16] : (unsigned short)0;
-      v[e] = __builtin_bit_cast(__bf16, bits);
-    }
-    wreg[i] = v;
-  }
-  f32x4 acc[TPB][NT];
-#pragma unroll
-  for (int i = 0; i < TPB; ++i)
-#pragma unroll
-    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0, 0, 0, 0};
-
-  int rb = blockIdx.x;
-  int boff = 0;
-  if (rb < nrb)
-    bf_step<NB, VEC>(bsm + R * pitch, bsm, red, pb, rb, A0, A1, n, d0, d1, G, nch0, nch, w, lane, wreg, acc, true);
-  for (; rb < nrb; rb += gridDim.x) {
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    const int nxt = rb + (int)gridDim.x < nrb ? rb + (int)gridDim.x : -1;
-    bf_step<NB, VEC>(bsm + boff, bsm + (R * pitch - boff), red, pb, nxt, A0, A1, n, d0, d1, G, nch0, nch, w, lane,
-                     wreg, acc, false);
-    boff = R * pitch - boff;
-  }
-  // epilogue: tile t of the padded space -> block and tile, pads skipped
-  const int W_out = NB * k;
-  const int D = d0 + (NB == 2 ? d1 : 0);
-  float* out = partial + (int64_t)blockIdx.x * D * W_out;
-#pragma unroll
-  for (int i = 0; i < TPB; ++i) {
-    const int t = w + kDmaWaves * i;
-    if (t < G.TTp) {
-      bool b1 = false, ok = true;
-      int ct = t;
-      if (t >= G.T0) {
-        if (NB == 2 && t >= G.T0p && t < G.T0p + G.T1) { b1 = true; ct = t - G.T0p; }
-        else ok = false;
+  // columns no load writes stay zero
+  for (int e = tid; e < kPipeRing * S::BUF / 2; e += kBfThreads) reinterpret_cast<uint32_t*>(bsm)[e] = 0;
+  __syncthreads();
+  // this workgroup's blocks: pairs of neighbours, as in k_pass_quad
+  const int pairs = (nrb + 1) / 2, mine = (pairs - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
+  const int nst = 2 * mine - ((nrb & 1) && (pairs - 1) % (int)gridDim.x == (int)blockIdx.x ? 1 : 0);
+  if (w == kBfProd + kBfCons) {
+    auto stream = [&](auto nt_) __attribute__((always_inline)) {
+      int64_t row = (int64_t)blockIdx.x * 2 * R;
+      auto load = [&](int i) __attribute__((always_inline)) {   // block i, at `row`
+        const int cnt = bf_load<NB, S, decltype(nt_)::value>(A0 + row * d0, NB == 2 ? A1 + row * d1 : nullptr, n - row,
+                                                             d0, NB == 2 ? d1 : 0, G.T0p, bsm + (i & 3) * S::BUF, lane);
+        row += (i & 1) ? (2ll * gridDim.x - 1) * R : R;
+        return cnt;
+      };
+      load(0);
+      bf_wait(nst > 1 ? load(1) : 0);   // block 0 has landed
+      lds_only_barrier();
+      for (int i = 0; i <= nst; ++i) {
+        bf_wait(i + 2 < nst ? load(i + 2) : 0);   // block i + 1 has landed; block i + 2 stays in flight
+        lds_only_barrier();
       }
-      if (ok) {
-        const int db = b1 ? d1 : d0;
-        const int rowbase = b1 ? d0 : 0;
+    };
+    // non-temporal past the memory-side cache, as in k_pass_quad
+    if (n * (d0 + (NB == 2 ? d1 : 0)) * 2 > (256ll << 20)) stream(std::integral_constant<bool, true>{});
+    else stream(std::integral_constant<bool, false>{});
+  } else if (w < kBfProd) {
+    auto produce = [&](auto c0_, auto nch_) __attribute__((always_inline)) {
+      constexpr int C0 = decltype(c0_)::value, NCH = decltype(nch_)::value;
+      bf16x8_t wreg[NCH][TPC];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-          const int col = l16;
-          if (col < k) {
+      for (int c = 0; c < NCH; ++c)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const int c = ct * 16 + acc_row<float>(lane, r);
-              if (c < db) out[(int64_t)(rowbase + c) * W_out + nt * k + col] = acc[i][nt][r];
-            }
-          }
+        for (int i = 0; i < TPC; ++i) {
+          const int T = C0 + c + kBfChains * i;
+          wreg[c][i] = bf16x8_t{};
+          if (T < tiles) wreg[c][i] = Wp[T * 64 + lane];
         }
+      lds_only_barrier();
+      for (int i = 0; i <= nst; ++i) {
+        if (i < nst)
+          bf_produce<S, NB, NCH>(bsm + (i & 3) * S::BUF, parts + (i & 1) * S::PART, lane, C0, tiles0, wreg);
+        lds_only_barrier();
       }
+    };
+    if (w == 0) produce(std::integral_constant<int, 0>{}, std::integral_constant<int, 3>{});
+    else if (w == 1) produce(std::integral_constant<int, 3>{}, std::integral_constant<int, 3>{});
+    else produce(std::integral_constant<int, 6>{}, std::integral_constant<int, 2>{});
+  } else {
+    const int wj = w - kBfProd;
+    f32x16 acc[TPC];
+#pragma unroll
+    for (int i = 0; i < TPC; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+    lds_only_barrier();
+    lds_only_barrier();   // the producers' step 0
+    for (int i = 0; i < nst; ++i) {
+      bf_consume<S, NB>(bsm + (i & 3) * S::BUF, parts + (i & 1) * S::PART, wj, lane, acc);
+      lds_only_barrier();
     }
+    // this workgroup's partial (rows = concatenated columns of A, columns =
+    // [P_0 | P_1]); lane: column lane % 32 of the products, rows 8 (r / 4) +
+    // 4 (lane / 32) + r % 4
+    const int W_out = NB * k, v = (lane & 31) >> 4, col = lane & 15;
+    float* out = partial + (int64_t)blockIdx.x * (d0 + (NB == 2 ? d1 : 0)) * W_out + v * k + col;
+    if (v < NB && col < k)
+#pragma unroll
+      for (int i = 0; i < TPC; ++i) {
+        const int T = wj + kBfCons * i;
+        const bool b1 = NB == 2 && T >= tiles0;
+        const int row0 = 32 * (b1 ? T - tiles0 : T) + 4 * (lane >> 5), d = b1 ? d1 : d0;
+        if (T < tiles)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int row = row0 + 8 * (r / 4) + r % 4;
+            if (row < d) out[(int64_t)((b1 ? d0 : 0) + row) * W_out] = acc[i][r];
+          }
+      }
   }
 }
 
-static size_t bf_lds_bytes(int d0, int d1, int NT) {
-  const BfGeom G = bf_geom(d0, d1);
-  return (size_t)2 * kBfRows * G.pitch * 2 + (size_t)kDmaWaves * NT * 256 * 4 + (size_t)NT * 256 * 2;
+// The BF16 pass takes rows of whole dwords on 4-byte boundaries, views of at
+// least 113 columns (narrower ones keep the FP32 arithmetic of k_pass) and
+// at most 128 tiles of 16 columns, each view's count rounded up to even.
+static bool bf_rows_ok(const void* A0, const void* A1, int d0, int d1) {
+  if ((uintptr_t)A0 % 4 != 0 || d0 % 2 != 0 || (d0 + 15) / 16 < 8) return false;
+  return !A1 || ((uintptr_t)A1 % 4 == 0 && d1 % 2 == 0 && (d1 + 15) / 16 >= 8);
 }
 
-static int bf_vec(const void* A0, const void* A1, int d0, int d1) {
-  const int T0 = (d0 + 15) / 16, T1 = A1 ? (d1 + 15) / 16 : 0;
-  const bool al16 = ((uintptr_t)A0 % 16 == 0) && (!A1 || (uintptr_t)A1 % 16 == 0) && d0 % 8 == 0 &&
-                    (!A1 || d1 % 8 == 0);
-  if (al16 && T0 * 16 >= 512 && (!A1 || T1 * 16 >= 512)) return 8;
-  const bool al4 = ((uintptr_t)A0 % 4 == 0) && (!A1 || (uintptr_t)A1 % 4 == 0) && d0 % 2 == 0 && (!A1 || d1 % 2 == 0);
-  if (al4 && T0 * 16 >= 128 && (!A1 || T1 * 16 >= 128)) return 2;
-  return 0;
+static bool bf_fits(int d0, int d1, int k, int nb) {
+  return k <= 16 && bf_geom(d0, nb == 2 ? d1 : 0).TTp <= kDmaMaxTiles;
 }
 
-static bool bf_fits(int d0, int d1, int k, int nb, int vec) {
-  if (vec == 0 || k > 16) return false;
-  const BfGeom G = bf_geom(d0, nb == 2 ? d1 : 0);
-  if (G.TTp > kDmaMaxTiles) return false;
-  return bf_lds_bytes(d0, nb == 2 ? d1 : 0, nb) <= (size_t)kPassLds + 8 * 1024;
-}
-
-template <int NB, int VEC>
+template <int NB, int R, int TPC>
 static int pass_launch_bf(const unsigned short* A0, const unsigned short* A1, int64_t n, int d0, int d1, int k,
                           const double* W0, const double* W1, double* J0, double* J1, const int* done, Arena& ws,
                           hipStream_t st, hipEvent_t before_pass, hipEvent_t after_pass) {
-  const BfGeom G = bf_geom(d0, NB == 2 ? d1 : 0);
-  const int dp0 = G.T0p * 16, dp1 = NB == 2 ? G.T1p * 16 : 0;
-  unsigned short* Wp0 = ws.take<unsigned short>((size_t)dp0 * 16);
-  unsigned short* Wp1 = NB == 2 ? ws.take<unsigned short>((size_t)dp1 * 16) : nullptr;
-  const int nrb = (int)((n + kBfRows - 1) / kBfRows);
+  using S = BfShape<R, TPC>;
+  static_assert(S::lds_bytes() <= 160 * 1024, "the ring and the partials fit a CU's LDS");
+  const int nrb = (int)((n + R - 1) / R);
+  // at least 4 blocks per workgroup (fewer partials to add for short data)
   const int grid = std::max(1, std::min(num_cus(), (nrb + 3) / 4));
   const int Dtot = d0 + (NB == 2 ? d1 : 0);
+  const BfGeom G = bf_geom(d0, NB == 2 ? d1 : 0);
+  const int WN = G.TTp / 2 * 512;
+  uint16_t* Wp = ws.take<uint16_t>(WN);
   float* part = ws.take<float>((size_t)grid * Dtot * NB * k);
-  if (!Wp0 || !part || (NB == 2 && !Wp1)) { set_error("gram_pass: workspace too small"); return SRP_ENOMEM; }
-  const int tot = dp0 * 16 + dp1 * 16;
-  hipLaunchKernelGGL(k_pack_dir_bf, dim3((tot + 255) / 256), dim3(256), 0, st, W0, d0, dp0, Wp0, W1, d1, dp1, Wp1,
-                     k);
+  if (!Wp || !part) { set_error("gram_pass: workspace too small"); return SRP_ENOMEM; }
+  hipLaunchKernelGGL(k_pack_dir_bf, dim3(WN / 256), dim3(256), 0, st, W0, d0, W1, NB == 2 ? d1 : 0, G.T0p / 2, k, WN,
+                     Wp);
   SRP_LAUNCH_CHECK();
-  const size_t lds = bf_lds_bytes(d0, NB == 2 ? d1 : 0, NB);
-  SRP_TRY(allow_dynamic_lds((const void*)k_pass_bf<NB, VEC>, kPassLds + 8 * 1024));
+  SRP_TRY(allow_dynamic_lds((const void*)k_pass_bf<NB, R, TPC>, S::lds_bytes()));
   if (before_pass) SRP_HIP(hipEventRecord(before_pass, st));
-  hipLaunchKernelGGL((k_pass_bf<NB, VEC>), dim3(grid), dim3(kDmaThreads), lds, st, A0, A1, n, d0, NB == 2 ? d1 : 0,
-                     k, Wp0, Wp1, nrb, part, done);
+  hipLaunchKernelGGL((k_pass_bf<NB, R, TPC>), dim3(grid), dim3(kBfThreads), S::lds_bytes(), st, A0, A1, n, d0,
+                     NB == 2 ? d1 : 0, k, reinterpret_cast<const bf16x8_t*>(Wp), nrb, part, done);
   SRP_LAUNCH_CHECK();
   if (after_pass) SRP_HIP(hipEventRecord(after_pass, st));
   const int64_t count = (int64_t)Dtot * NB * k;
@@ -1337,21 +1361,23 @@ static int pass_launch_bf(const unsigned short* A0, const unsigned short* A1, in
 static int pass_dispatch_bf(const unsigned short* A0, const unsigned short* A1, int64_t n, int d0, int d1, int k,
                             const double* W0, const double* W1, double* J0, double* J1, const int* done, Arena& ws,
                             hipStream_t st, hipEvent_t ev0, hipEvent_t ev) {
-  const int vec = bf_vec(A0, A1, d0, d1);
+  const int TTp = bf_geom(d0, A1 ? d1 : 0).TTp;
+#define SRP_BF_CASE(NB_, TT_, R_, TPC_)                                                                         \
+  if (TTp <= TT_) return pass_launch_bf<NB_, R_, TPC_>(A0, A1, n, d0, d1, k, W0, W1, J0, J1, done, ws, st, ev0, ev);
   if (A1) {
-    if (vec == 8) return pass_launch_bf<2, 8>(A0, A1, n, d0, d1, k, W0, W1, J0, J1, done, ws, st, ev0, ev);
-    return pass_launch_bf<2, 2>(A0, A1, n, d0, d1, k, W0, W1, J0, J1, done, ws, st, ev0, ev);
+    SRP_BF_CASE(2, 32, 16, 2) SRP_BF_CASE(2, 64, 16, 4) SRP_BF_CASE(2, 128, 8, 8)
+  } else {
+    SRP_BF_CASE(1, 32, 16, 2) SRP_BF_CASE(1, 64, 16, 4) SRP_BF_CASE(1, 128, 8, 8)
   }
-  if (vec == 8) return pass_launch_bf<1, 8>(A0, A1, n, d0, 0, k, W0, W1, J0, J1, done, ws, st, ev0, ev);
-  return pass_launch_bf<1, 2>(A0, A1, n, d0, 0, k, W0, W1, J0, J1, done, ws, st, ev0, ev);
+#undef SRP_BF_CASE
+  set_error("gram_pass: no BF16 pass instance for %d tiles", TTp);
+  return SRP_EINVAL;
 }
 
 int pass_limits_ok(int dtype, int compute, int d0, int d1, int k, int nblocks) {
   if (compute == SRP_BF16) {
     if (dtype != SRP_BF16 || k > 16) return 0;
-    const BfGeom G = bf_geom(d0, nblocks == 2 ? d1 : 0);
-    if (G.TTp <= kDmaMaxTiles && bf_lds_bytes(d0, nblocks == 2 ? d1 : 0, nblocks) <= (size_t)kPassLds + 8 * 1024)
-      return 1;
+    if (bf_fits(d0, d1, k, nblocks)) return 1;
     return pass_limits_ok(SRP_BF16, SRP_F32, d0, d1, k, nblocks);   // the FP32-arithmetic pass takes it
   }
   const int D = d0 + (nblocks == 2 ? d1 : 0);
@@ -1565,8 +1591,8 @@ const char* gram_pass_kernel_name(int dtype, int compute, int d0, int d1, int k)
   const bool al = d0 % 4 == 0 && (nb == 1 || d1 % 4 == 0);
   if (compute == SRP_BF16) {
     if (dtype != SRP_BF16) return nullptr;
-    const int bvec = ((d0 * 2) % 4 == 0 && (nb == 1 || (d1 * 2) % 4 == 0)) ? 1 : 0;
-    return bf_fits(d0, d1, k, nb, bvec ? 1 : 0) ? "k_pass_bf" : "k_pass";
+    const bool even = d0 % 2 == 0 && (nb == 1 || d1 % 2 == 0);
+    return even && bf_fits(d0, d1, k, nb) ? "k_pass_bf" : "k_pass";
   }
   if (compute == SRP_F32 && dtype == SRP_F32) {
     const int vec = (al && T0 >= 16 && (nb == 1 || T1 >= 16)) ? 4 : (T0 >= 4 && (nb == 1 || T1 >= 4)) ? 1 : 0;
@@ -1593,7 +1619,7 @@ int gram_pass_run(const void* A0, const void* A1, int dtype, int compute, int64_
       set_error("gram_pass: BF16 products need BF16 data");
       return SRP_EINVAL;
     }
-    if (bf_fits(d0, nb == 2 ? d1 : 0, k, nb, bf_vec(A0, A1, d0, d1)))
+    if (bf_rows_ok(A0, A1, d0, d1) && bf_fits(d0, d1, k, nb))
       return pass_dispatch_bf((const unsigned short*)A0, (const unsigned short*)A1, n, d0, d1, k, W0, W1, J0, J1,
                               done, ws, st, before_pass, after_pass);
     // views narrower than one 64-lane row chunk (or rows not 4-byte

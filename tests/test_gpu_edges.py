@@ -164,3 +164,37 @@ def test_gram_pass_one_tile_more(d0, d1, dt, comp):
     u = 2.0 ** -53 if comp == "f64" else 2.0 ** -24
     for g, q in zip(out, Q):
         assert np.all(np.abs(g.cpu().numpy() - q.T @ P) <= (d0 + d1 + n + 2) * u * (np.abs(q).T @ Pabs))
+
+
+# BF16 products on whole numbers (P fits 8 bits, sums 24: every step exact):
+# 16 and 8 rows a block at their last and first widths (32, 34, 64, 66 and
+# 128 tiles), rows of 2, 4 and 6 columns past a 16-byte piece, rows off 16-byte
+# boundaries, views that end half way into a 32-column tile, fewer rows than
+# a block, an odd last block, one direction and sixteen
+@pytest.mark.parametrize("n,d0,d1,k,off", [(3, 128, 0, 1, 0), (17, 256, 256, 16, 2), (1200, 258, 250, 5, 2),
+                                           (2001, 514, 0, 16, 4), (2047, 500, 524, 9, 2), (1999, 526, 500, 7, 6),
+                                           (4099, 1024, 1024, 16, 0), (4100, 2048, 0, 3, 0), (2501, 1006, 130, 10, 2),
+                                           (9, 1500, 484, 8, 4), (70001, 2046, 0, 2, 2)])
+def test_gram_pass_bf16_block_edges(n, d0, d1, k, off):
+    srp = _srp()
+    rng = np.random.default_rng(n + d0 + d1)
+    A = [rng.integers(-1, 2, size=(n, d)).astype(np.float32) for d in (d0, d1) if d]
+    W = [rng.integers(-1, 2, size=(d, k)).astype(np.float64) for d in (d0, d1) if d]
+    if d1 and n > 2:
+        A[1][n // 2, 40] = np.inf
+    D = []
+    for a in A:
+        buf = torch.zeros(a.size + off, dtype=torch.bfloat16, device=DEV)
+        buf[off:] = torch.from_numpy(a).reshape(-1).to(DEV)
+        D.append(buf[off:].view(a.shape))
+    out = srp.srp_gram_pass(D[0], torch.from_numpy(W[0]).to(DEV), *([D[1], torch.from_numpy(W[1]).to(DEV)] if d1 else []),
+                            compute="bf16")
+    with np.errstate(invalid="ignore"):
+        P = np.concatenate([a.astype(np.float64) @ w for a, w in zip(A, W)], axis=1)
+        ref = [a.T.astype(np.float64) @ P for a in A]
+    assert np.max(np.abs(P[np.isfinite(P)])) <= 256
+    for g, r in zip(out, ref):
+        g = g.cpu().numpy()
+        ok = np.isfinite(r)
+        assert np.array_equal(np.isfinite(g), ok)
+        np.testing.assert_array_equal(g[ok], r[ok])
