@@ -11,7 +11,6 @@
 #include "kernels.hpp"
 
 #include <type_traits>
-#include <vector>
 
 namespace srp {
 
@@ -403,7 +402,8 @@ __global__ void k_sum_parts(const double* parts, int nparts, int64_t stride, int
 // are summed in split order (diag_add on the diagonal); those below the
 // diagonal, which no upper tile need cover and nothing reads, are set to
 // zero without reading the partials (so the partials need no clearing).
-__global__ void k_sum_upper(const double* parts, int nparts, int64_t stride, int d, double diag_add, double* out) {
+__global__ void k_sum_upper(const double* parts, int nparts, int64_t stride, int d, double diag_add, double* out,
+                            double* __restrict__ zero0, double* __restrict__ zero1) {
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (e >= (int64_t)d * d) return;
   const int i = (int)(e / d), j = (int)(e - (int64_t)i * d);
@@ -413,6 +413,8 @@ __global__ void k_sum_upper(const double* parts, int nparts, int64_t stride, int
     if (i == j) v += diag_add;
   }
   out[e] = v;
+  zero0[e] = 0.0;
+  zero1[e] = 0.0;
 }
 
 int sum_parts_f64(const double* parts, int nparts, int64_t stride, int64_t count, double* out, int d,
@@ -783,46 +785,70 @@ __device__ __forceinline__ double readlane_f64(double x, int l) {
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-__global__ void __launch_bounds__(256) k_potrf_block(const double* __restrict__ G, int64_t ld, int k0, int nb,
-                                                     double* __restrict__ R, double* __restrict__ Dinv,
-                                                     int* flag) {
-  __shared__ double a[64][65];
-  __shared__ double x[64][65];
-  __shared__ double piv[64];
-  __shared__ double row[2][65];   // unscaled row j of the trailing matrix, double-buffered by step parity
-  __shared__ double rdiag[64];    // 1 / R[j][j]
-  __shared__ double tsc[3][16][17];   // per-wave 16 x 16 scratch of the blocked inverse
+constexpr int kCholPitch = 65;
+struct CholLds {
+  double a[64][kCholPitch];       // the block (k_chol_step: a column block of R before)
+  double x[64][kCholPitch];       // its inverse (k_chol_step: the other column block)
+  double rdiag[64];               // 1 / R[j][j]
+  double tsc[3][16][17];          // per-wave 16 x 16 scratch of the blocked inverse
+};
+
+// v with the 4 lanes of every quad permuted.
+template <int CTRL>
+__device__ __forceinline__ double quad_perm_f64(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xF, 0xF, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Inverse of the 16 x 16 diagonal block at o of L.a into L.x, by
+// back-substitution in one wave: four lanes a column c, lane q holds rows
+// l = q mod 4 of the column in registers.  Row r takes its products with the
+// rows r + 1 .. c over the four lanes, each in ascending order, then the lane
+// sums in pairs counted from row r + 1.
+__device__ __forceinline__ void invert_diag16(CholLds& L, int o, int ln) {
+  const int c = ln >> 2, q = ln & 3;
+  double xr[4] = {0.0, 0.0, 0.0, 0.0};   // rows q, q + 4, q + 8, q + 12
+#pragma unroll
+  for (int r = 15; r >= 0; --r) {
+    double sum = 0.0;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const int l = q + 4 * m;
+      const double prod = L.a[o + r][o + l] * xr[m];
+      if (4 * m + 3 > r) sum += (l > r && l <= c) ? prod : 0.0;
+    }
+    sum += (r & 1) ? quad_perm_f64<0xB1>(sum) : quad_perm_f64<0x1B>(sum);   // [1,0,3,2] or [3,2,1,0]
+    sum += quad_perm_f64<0x4E>(sum);                                        // [2,3,0,1]
+    const double v = (r <= c) ? ((r == c) ? 1.0 : -sum) * L.rdiag[o + r] : 0.0;
+    if (q == (r & 3)) xr[r >> 2] = v;
+  }
+#pragma unroll
+  for (int m = 0; m < 4; ++m) L.x[o + q + 4 * m][o + c] = xr[m];
+}
+
+// Factor the block in L.a (upper triangle, identity past nb) and invert it.
+__device__ __forceinline__ void potrf_lds(CholLds& L, int64_t ld, int k0, int nb, double* __restrict__ R,
+                                          double* __restrict__ Dinv, int* flag) {
+  auto& a = L.a;
+  auto& x = L.x;
+  auto& rdiag = L.rdiag;
+  auto& tsc = L.tsc;
   const int t = threadIdx.x;
   const int wv = t >> 6, ln = t & 63;
-  // The upper triangle of the block in LDS (rows past nb: the identity).
-  {
-    // all sixteen loads of a thread in flight together (masked entries read
-    // the block's first element and are replaced)
-    double v[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = t + 256 * u, r = e >> 6, c = e & 63;
-      const bool in = r <= c && r < nb && c < nb;
-      v[u] = G[in ? (int64_t)(k0 + r) * ld + k0 + c : (int64_t)k0 * ld + k0];
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = t + 256 * u, r = e >> 6, c = e & 63;
-      const bool in = r <= c && r < nb && c < nb;
-      a[r][c] = in ? v[u] : ((r == c) ? 1.0 : 0.0);
-    }
-  }
-  __syncthreads();
   // Four panels of 16 rows, right-looking.  Wave 0 factors a panel alone
   // with lane c holding rows p0 .. p0+15 of column c in registers: step j
   // takes the pivot from lane p0+j, scales row j and subtracts its outer
   // product from the rows below, the row-j entries of the other columns
   // broadcast by readlane (no barrier inside the panel).  Then all waves
   // subtract the panel's rows' products from the trailing triangle on FP64
-  // matrix cores.
+  // matrix cores.  Beside a panel, another wave inverts the diagonal block of
+  // the panel before.
   for (int p0 = 0; p0 < 64; p0 += 16) {
     if (wv == 0) {
-      double pr[16];
+      double pr[16], rd = 0.0;
+      bool any_bad = false;   // no branch inside the panel: its steps overlap
 #pragma unroll
       for (int i = 0; i < 16; ++i) pr[i] = a[p0 + i][ln];
 #pragma unroll
@@ -830,15 +856,12 @@ __global__ void __launch_bounds__(256) k_potrf_block(const double* __restrict__ 
         const int pl = p0 + j;   // lane (column) of the pivot
         double p = readlane_f64(pr[j], pl);
         const bool bad = !(p > 0.0) || !isfinite(p);
-        if (bad) p = 1.0;
+        any_bad |= bad;
+        p = bad ? 1.0 : p;
         double rs = __builtin_amdgcn_rsq(p);
         rs = rs * fma(-0.5 * p * rs, rs, 1.5);
         rs = rs * fma(-0.5 * p * rs, rs, 1.5);   // 1 / sqrt(p), two Newton steps
-        if (ln == 0) {
-          if (bad) atomicOr(flag, 1);
-          piv[pl] = p;
-          rdiag[pl] = rs;
-        }
+        rd = ln == pl ? rs : rd;
         const double rj = pr[j] * rs;   // row j of R in column ln (ln >= pl)
 #pragma unroll
         for (int i = j + 1; i < 16; ++i) {
@@ -851,7 +874,13 @@ __global__ void __launch_bounds__(256) k_potrf_block(const double* __restrict__ 
 #pragma unroll
         for (int i = 0; i < 16; ++i)
           if (p0 + i <= ln) a[p0 + i][ln] = pr[i];
+        if (ln < p0 + 16) rdiag[ln] = rd;
       }
+      if (any_bad && ln == 0) atomicOr(flag, 1);
+    } else if (p0 == 0) {
+      for (int e = t - 64; e < 4096; e += 192) x[e >> 6][e & 63] = 0.0;
+    } else if (wv == p0 >> 4) {
+      invert_diag16(L, p0 - 16, ln);
     }
     __syncthreads();
     const int q0 = p0 + 16;
@@ -876,30 +905,12 @@ __global__ void __launch_bounds__(256) k_potrf_block(const double* __restrict__ 
       __syncthreads();
     }
   }
-  // x = a^-1 (upper) by 16 x 16 blocks: the four diagonal blocks by
-  // back-substitution (wave w inverts block w; four lanes per column),
-  // then the blocks at distance d = 1, 2, 3 from the diagonal as
+  // x = a^-1 (upper) by 16 x 16 blocks: the diagonal blocks by
+  // back-substitution (the first three beside the next panel), then the
+  // blocks at distance d = 1, 2, 3 from the diagonal as
   // X_ij = -X_ii sum_{i < l <= j} R_il X_lj on FP64 matrix cores (a level
   // needs only blocks closer to the diagonal).
-  for (int e = t; e < 4096; e += 256) x[e >> 6][e & 63] = 0.0;
-  __syncthreads();
-  {
-    const int c = ln >> 2, q = ln & 3, o = 16 * wv;
-    for (int r = 15; r >= 0; --r) {
-      double sum = 0.0;
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {   // unconditional loads (clamped index), masked products
-        const int l = r + 1 + q + 4 * m;
-        const int lc = min(l, 15);
-        const double prod = a[o + r][o + lc] * x[o + lc][o + c];
-        sum += (l <= c) ? prod : 0.0;
-      }
-      sum += __shfl_xor(sum, 1, 64);
-      sum += __shfl_xor(sum, 2, 64);
-      if (q == 0 && r <= c) x[o + r][o + c] = ((r == c) ? 1.0 : -sum) * rdiag[o + r];
-      wave_fence_sync();
-    }
-  }
+  if (wv == 0) invert_diag16(L, 48, ln);
   __syncthreads();
   {
     const int m16 = ln & 15, kq = ln >> 4;
@@ -932,18 +943,205 @@ __global__ void __launch_bounds__(256) k_potrf_block(const double* __restrict__ 
   }
 }
 
-// Copy 64x64 block inverses onto the diagonal of X (d x d).
-__global__ void k_place_diag_blocks(const double* __restrict__ Dinv, int d, double* __restrict__ X, int kb0) {
-  const int kb = kb0 + blockIdx.x;
-  const int k0 = kb * 64;
-  const int nb = min(64, d - k0);
-  for (int e = threadIdx.x; e < 4096; e += blockDim.x) {
-    const int r = e >> 6, c = e & 63;
-    if (r < nb && c < nb) X[(int64_t)(k0 + r) * d + k0 + c] = Dinv[(int64_t)kb * 4096 + e];
+__global__ void __launch_bounds__(256) k_potrf_block(const double* __restrict__ G, int64_t ld, int k0, int nb,
+                                                     double* __restrict__ R, double* __restrict__ Dinv, int* flag) {
+  extern __shared__ char chol_lds[];
+  CholLds& L = *reinterpret_cast<CholLds*>(chol_lds);
+  const int t = threadIdx.x;
+  // The upper triangle of the block in LDS (rows past nb: the identity).
+  // all sixteen loads of a thread in flight together (masked entries read
+  // the block's first element and are replaced)
+  double v[16];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int e = t + 256 * u, r = e >> 6, c = e & 63;
+    const bool in = r <= c && r < nb && c < nb;
+    v[u] = G[in ? (int64_t)(k0 + r) * ld + k0 + c : (int64_t)k0 * ld + k0];
   }
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int e = t + 256 * u, r = e >> 6, c = e & 63;
+    const bool in = r <= c && r < nb && c < nb;
+    L.a[r][c] = in ? v[u] : ((r == c) ? 1.0 : 0.0);
+  }
+  __syncthreads();
+  potrf_lds(L, ld, k0, nb, R, Dinv, flag);
 }
 
-constexpr int kInvSplit = 8;   // split of the contraction in the R^-1 column blocks
+// Workgroup `wg` of column block kb of X = R^-1 (left to right): X_kk =
+// R_kk^-1 (from the diagonal block's factor, by workgroup 4 kb) and X[0:k0, kb]
+// = -X[0:k0, 0:k0] R[0:k0, kb] X_kk, 16 rows a workgroup, 16 columns a wave.
+// It needs R's columns up to kb and X's earlier column blocks.  Bounds: the
+// latency of its operands, written by other XCDs a launch before: two 64-row
+// blocks are read ahead of the one multiplied.
+__device__ __forceinline__ void rinv_strip(CholLds& L, int wg, int kb, int d, const double* __restrict__ R,
+                                           const double* __restrict__ Dinv, double* __restrict__ X) {
+  const int k0 = kb * 64, nb = min(64, d - k0);
+  const double* Dk = Dinv + (size_t)kb * 4096;
+  if (wg == 4 * kb) {
+    for (int e = threadIdx.x; e < 4096; e += 256) {
+      const int r = e >> 6, c = e & 63;
+      if (r < nb && c < nb) X[(int64_t)(k0 + r) * d + k0 + c] = Dk[e];
+    }
+    return;
+  }
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, l16 = lane & 15;
+  const int i0 = 16 * wg, c = k0 + 16 * w + l16;
+  const int ar = threadIdx.x >> 4, ac = 4 * (threadIdx.x & 15);   // this thread's share of a block of X: one row, 4 columns
+  const double* xa = X + (int64_t)(i0 + ar) * d + ac;
+  const double* rb = R + min(c, d - 1);   // past d: not stored
+  double a[3][4], b[3][16], q[16];
+#pragma unroll
+  for (int s = 0; s < 16; ++s) q[s] = Dk[(4 * s + g) * 64 + 16 * w + l16];
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  auto read = [&](int kk, int u) __attribute__((always_inline)) {
+    kk = min(kk, k0 - 64);   // past the last: read again, not used
+#pragma unroll
+    for (int s = 0; s < 4; ++s) a[u][s] = xa[kk + s];
+#pragma unroll
+    for (int s = 0; s < 16; ++s) b[u][s] = rb[(int64_t)(kk + 4 * s + g) * d];
+    __builtin_amdgcn_sched_barrier(0);   // ahead of the products before it in use
+  };
+  // L.x: two 16 x 64 blocks of X in turn
+  int kk = i0 & ~63;   // X is upper triangular
+  read(kk, 0);
+  read(kk + 64, 1);
+  for (int p = 0; kk < k0; kk += 192)
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+      if (kk + 64 * u < k0) {
+        double(*xs)[kCholPitch] = L.x + 16 * (p & 1);
+        ++p;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) xs[ar][ac + s] = a[u][s];
+        __syncthreads();
+        read(kk + 64 * u + 128, (u + 2) % 3);
+#pragma unroll
+        for (int s = 0; s < 16; ++s) acc = mfma16x16x4(xs[l16][4 * s + g], b[u][s], acc);
+      }
+    }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) L.a[acc_row<double>(lane, r)][16 * w + l16] = acc[r];
+  __syncthreads();
+  f64x4 out = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < 16; ++s) out = mfma16x16x4(L.a[l16][4 * s + g], q[s], out);
+  if (c < d)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) X[(int64_t)(i0 + acc_row<double>(lane, r)) * d + c] = -out[r];
+}
+
+// One step of the right-looking factorisation, 64 columns: with the
+// inverse of diagonal block kb, each workgroup takes a 64 x 64 tile (i, j) of
+// the upper triangle past it, forms the two column blocks of R it needs
+// (R_k. = R_kk^-T G_k.; a tile of the first row also stores its R_kj) and
+// subtracts R_ki^T R_kj.  The first workgroup, whose tile is the next
+// diagonal block, goes on to factor and invert it; workgroups past the
+// `ntiles` tiles form column block kb of R^-1 in the meantime.
+// Bounds: the first workgroup's chain, 26 us a step: 64 pivots in turn, each
+// about 300 clocks of dependent FP64 operations (12 us), the block's inverse
+// (4 us), its own products on operands that other XCDs wrote a launch before
+// (5 us).  The column blocks of R are formed again by every tile: three
+// products a tile instead of one, for one launch a step instead of three (and
+// four more for R^-1 on a second stream).  Measured, s x d sketch, us before
+// and now: 4000 x 1000 1000 -> 622, 8000 x 2000 2733 -> 2022 (1000 of it the
+// Gram), 524 x 131 245 -> 162, 4200 x 4096 6425 -> 5640.
+__global__ void __launch_bounds__(256) k_chol_step(double* __restrict__ G, int d, int kb, int ntiles,
+                                                   double* __restrict__ Dinv, double* __restrict__ R,
+                                                   double* __restrict__ X, int* flag) {
+  extern __shared__ char chol_lds[];
+  CholLds& L = *reinterpret_cast<CholLds*>(chol_lds);
+  // tile of the upper triangle, by columns: (0, 0), (0, 1), (1, 1), (0, 2), ...
+  const int b = blockIdx.x;
+  if (b >= ntiles) {
+    rinv_strip(L, b - ntiles, kb, d, R, Dinv, X);
+    return;
+  }
+  int tj = (int)((sqrtf(8.f * b + 1.f) - 1.f) * 0.5f);
+  while (tj * (tj + 1) / 2 > b) --tj;
+  while ((tj + 1) * (tj + 2) / 2 <= b) ++tj;
+  const int ti = b - tj * (tj + 1) / 2;
+  const int64_t ld = d;
+  const int k0 = kb * 64, i0 = k0 + 64 * (ti + 1), j0 = k0 + 64 * (tj + 1);
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, g = lane >> 4, l16 = lane & 15;
+  const double* Dk = Dinv + (size_t)kb * 4096;
+  // this wave's 16 columns of a column block of G, and the tile's
+  auto column = [&](int c0, double (&p)[16]) __attribute__((always_inline)) {
+    const int c = c0 + 16 * w + l16;
+#pragma unroll
+    for (int s = 0; s < 16; ++s) p[s] = G[(int64_t)(k0 + 4 * s + g) * ld + min(c, d - 1)];   // past d: not stored
+  };
+  double pj[16], pi[16], old[4][4], q[4][16];
+  column(j0, pj);
+#pragma unroll
+  for (int m = 0; m < 4; ++m)
+#pragma unroll
+    for (int s = 0; s < 4 * (m + 1); ++s) q[m][s] = Dk[(4 * s + g) * 64 + 16 * m + l16];
+  if (ti != tj) column(i0, pi);
+  const int cj = j0 + 16 * w + l16;
+#pragma unroll
+  for (int m = 0; m < 4; ++m)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = i0 + 16 * m + acc_row<double>(lane, r);
+      old[m][r] = G[(int64_t)min(row, d - 1) * ld + min(cj, d - 1)];
+    }
+  __builtin_amdgcn_sched_barrier(0);   // all of it in flight before the first product
+  // R_k. by 16 rows: R_kk^-1 is upper, its rows past the 16 are zero
+  f64x4 rj[4], ri[4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    rj[m] = ri[m] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 4 * (m + 1); ++s) rj[m] = mfma16x16x4(q[m][s], pj[s], rj[m]);
+    if (ti != tj)
+#pragma unroll
+      for (int s = 0; s < 4 * (m + 1); ++s) ri[m] = mfma16x16x4(q[m][s], pi[s], ri[m]);
+  }
+#pragma unroll
+  for (int m = 0; m < 4; ++m)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 16 * m + acc_row<double>(lane, r);
+      L.x[row][16 * w + l16] = rj[m][r];
+      if (ti != tj) L.a[row][16 * w + l16] = ri[m][r];
+      if (ti == 0 && cj < d) R[(int64_t)(k0 + row) * ld + cj] = rj[m][r];
+    }
+  __syncthreads();
+  auto& ai = ti == tj ? L.x : L.a;
+  f64x4 acc[4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) acc[m] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < 16; ++s) {
+    const double bv = L.x[4 * s + g][16 * w + l16];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) acc[m] = mfma16x16x4(ai[4 * s + g][16 * m + l16], bv, acc[m]);
+  }
+  if (b != 0) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = i0 + 16 * m + acc_row<double>(lane, r);
+        if (row <= cj && cj < d) G[(int64_t)row * ld + cj] = old[m][r] - acc[m][r];
+      }
+    return;
+  }
+  // the next diagonal block (a was not in use)
+  const int nb = min(64, d - i0);
+#pragma unroll
+  for (int m = 0; m < 4; ++m)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 16 * m + acc_row<double>(lane, r), c = 16 * w + l16;
+      const bool in = row <= c && row < nb && c < nb;
+      L.a[row][c] = in ? old[m][r] - acc[m][r] : (row == c ? 1.0 : 0.0);
+    }
+  __syncthreads();
+  potrf_lds(L, ld, i0, nb, R, Dinv + (size_t)(kb + 1) * 4096, flag);
+}
+
 
 // Split of the sketch Gram over the s rows: about 256 workgroups of the
 // big-tile kernel over the upper 128 x 128 tiles (measured best: d = 1000,
@@ -963,7 +1161,7 @@ size_t factor_ws_bytes(int s, int d) {
   const int ksplit = gram_ksplit(s, d);
   const size_t dd = (size_t)d * d;
   return bytes_of<double>(dd) * (ksplit + 1) + bytes_of<double>((size_t)tiles * 4096) +
-         bytes_of<double>((size_t)64 * d) + bytes_of<double>(dd) + bytes_of<double>((size_t)kInvSplit * 64 * d);
+         bytes_of<double>(dd);
 }
 
 // Full symmetric Gram from the upper-tile split partials: H[i][j] is the
@@ -1017,58 +1215,8 @@ int gram_split(int s, int d0, int d1) {
   return ks < 1 ? 1 : ks;
 }
 
-// Events of the calling thread on the current device, reused call after
-// call (a wait takes the event's state when it is issued).  Never freed.
-static int factor_events(int count, hipEvent_t** out) {
-  thread_local std::vector<hipEvent_t>* pools[64] = {};
-  int dev = 0;
-  SRP_HIP(hipGetDevice(&dev));
-  if (dev < 0 || dev >= 64) { set_error("factor: device %d out of range", dev); return SRP_EDEVICE; }
-  if (!pools[dev]) pools[dev] = new std::vector<hipEvent_t>();
-  std::vector<hipEvent_t>& pool = *pools[dev];
-  while ((int)pool.size() < count) {
-    hipEvent_t e = nullptr;
-    SRP_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    pool.push_back(e);
-  }
-  *out = pool.data();
-  return SRP_OK;
-}
-
-// Column block kb of X = R^-1 (left to right): X_kk = R_kk^-1 (from the
-// diagonal block's factor) and X[0:k0, kb] = -X[0:k0, 0:k0] R[0:k0, kb] X_kk.
-// It needs only R's columns up to kb and X's earlier column blocks, so it
-// runs while the Cholesky works on the columns after kb.
-static int rinv_column(int kb, int d, const double* R, const double* Dinv, double* X, double* Tmp, double* Tparts,
-                       hipStream_t st) {
-  const int k0 = kb * 64, nb = std::min(64, d - k0);
-  hipLaunchKernelGGL(k_place_diag_blocks, dim3(1), dim3(256), 0, st, Dinv, d, X, kb);
-  SRP_LAUNCH_CHECK();
-  if (kb == 0) return SRP_OK;
-  const int rows = k0;
-  GemmArgs a{};
-  a.m = rows; a.n = nb; a.kk = rows; a.alpha = 1.0; a.beta = 0.0;
-  a.A = X; a.lda = d; a.ta = false;
-  a.B = R + k0; a.ldb = d; a.tb = false;
-  const int ks = std::min(kInvSplit, (rows + 127) / 128);
-  if (ks > 1) {   // rows x nb outputs are few tiles: split the contraction
-    a.C = Tparts; a.ldc = nb; a.ksplit = ks; a.c_split_stride = (int64_t)rows * nb;
-    SRP_TRY(gemm_f64(a, st));
-    SRP_TRY(sum_parts_f64(Tparts, ks, (int64_t)rows * nb, (int64_t)rows * nb, Tmp, 0, 0.0, st));
-  } else {
-    a.C = Tmp; a.ldc = nb;
-    SRP_TRY(gemm_f64(a, st));
-  }
-  GemmArgs b{};
-  b.m = rows; b.n = nb; b.kk = nb; b.alpha = -1.0; b.beta = 0.0;
-  b.A = Tmp; b.lda = nb; b.ta = false;
-  b.B = Dinv + (size_t)kb * 4096; b.ldb = 64; b.tb = false;
-  b.C = X + k0; b.ldc = d;
-  return gemm_f64(b, st);
-}
-
 int sketch_factor_run(const void* SA, int dtype, int s, int d, double lambda, double* R, double* Rinv,
-                      double* Minv, int* flag_dev, Arena& ws, hipStream_t st, double* Hfull, hipStream_t aux) {
+                      double* Minv, int* flag_dev, Arena& ws, hipStream_t st, double* Hfull) {
   const int tiles = (d + 63) / 64;
   const int ksplit = gram_ksplit(s, d);
   const int64_t dd = (int64_t)d * d;
@@ -1076,10 +1224,8 @@ int sketch_factor_run(const void* SA, int dtype, int s, int d, double lambda, do
   const bool use_parts = ksplit > 1 || Hfull;
   double* parts = use_parts ? ws.take<double>(dd * ksplit) : nullptr;
   double* Dinv = ws.take<double>((size_t)tiles * 4096);
-  double* Tmp = ws.take<double>((size_t)64 * d);
   double* X = Rinv ? Rinv : ws.take<double>(dd);
-  double* Tparts = ws.take<double>((size_t)kInvSplit * 64 * d);
-  if (!G || !Dinv || !Tmp || !X || !Tparts || (use_parts && !parts)) {
+  if (!G || !Dinv || !X || (use_parts && !parts)) {
     set_error("sketch_factor: workspace too small");
     return SRP_ENOMEM;
   }
@@ -1096,7 +1242,7 @@ int sketch_factor_run(const void* SA, int dtype, int s, int d, double lambda, do
     g.C = parts; g.ldc = d; g.ksplit = ksplit; g.c_split_stride = dd;
     SRP_TRY(gemm_f64(g, st));
     hipLaunchKernelGGL(k_sum_upper, dim3((unsigned)((dd + 255) / 256)), dim3(256), 0, st, parts, ksplit, dd, d,
-                       lambda, G);
+                       lambda, G, R, X);
     SRP_LAUNCH_CHECK();
     if (Hfull) {
       hipLaunchKernelGGL(k_gram_full, dim3((unsigned)((dd + 255) / 256)), dim3(256), 0, st, parts, ksplit, dd, d,
@@ -1106,60 +1252,22 @@ int sketch_factor_run(const void* SA, int dtype, int s, int d, double lambda, do
   } else {
     g.C = G; g.ldc = d;
     SRP_TRY(gemm_f64(g, st));
-    hipLaunchKernelGGL(k_sum_upper, dim3((unsigned)((dd + 255) / 256)), dim3(256), 0, st, G, 1, dd, d, lambda, G);
+    hipLaunchKernelGGL(k_sum_upper, dim3((unsigned)((dd + 255) / 256)), dim3(256), 0, st, G, 1, dd, d, lambda, G,
+                       R, X);
     SRP_LAUNCH_CHECK();
   }
-  // Right-looking blocked Cholesky, 64-wide panels; column block kb of
-  // X = R^-1 follows diagonal block kb, on the second stream when there is
-  // one (the same arithmetic either way, so the result does not depend on
-  // it).
-  const bool overlap = aux != nullptr && aux != st && tiles > 1;
-  hipEvent_t* ev = nullptr;
-  if (overlap) SRP_TRY(factor_events(tiles + 1, &ev));
-  // joins the second stream into st on every return (an error return too,
-  // so the caller's stream-ordered release of the workspace follows it)
-  struct Join {
-    hipStream_t st, aux;
-    hipEvent_t e;
-    ~Join() {
-      if (aux) {
-        (void)hipEventRecord(e, aux);
-        (void)hipStreamWaitEvent(st, e, 0);
-      }
-    }
-  } join{st, overlap ? aux : nullptr, overlap ? ev[tiles] : nullptr};
-  SRP_TRY(fill_f64(R, dd, 0.0, st));
-  SRP_TRY(fill_f64(X, dd, 0.0, st));
+  // Right-looking blocked Cholesky, 64 columns a launch, and R^-1 a column
+  // block behind it.
+  SRP_TRY(allow_dynamic_lds((const void*)k_potrf_block, sizeof(CholLds)));
+  SRP_TRY(allow_dynamic_lds((const void*)k_chol_step, sizeof(CholLds)));
+  hipLaunchKernelGGL(k_potrf_block, dim3(1), dim3(256), sizeof(CholLds), st, G, (int64_t)d, 0, std::min(64, d), R, Dinv,
+                     flag_dev);
+  SRP_LAUNCH_CHECK();
   for (int kb = 0; kb < tiles; ++kb) {
-    const int k0 = kb * 64, nb = min(64, d - k0);
-    hipLaunchKernelGGL(k_potrf_block, dim3(1), dim3(256), 0, st, G, (int64_t)d, k0, nb, R,
-                       Dinv + (size_t)kb * 4096, flag_dev);
+    const int T = tiles - kb - 1, ntiles = T * (T + 1) / 2;   // block columns past this one, their tiles
+    hipLaunchKernelGGL(k_chol_step, dim3(ntiles + 4 * kb + 1), dim3(256), sizeof(CholLds), st, G, d, kb, ntiles, Dinv,
+                       R, X, flag_dev);
     SRP_LAUNCH_CHECK();
-    if (overlap) {
-      SRP_HIP(hipEventRecord(ev[kb], st));
-      SRP_HIP(hipStreamWaitEvent(aux, ev[kb], 0));
-    }
-    SRP_TRY(rinv_column(kb, d, R, Dinv, X, Tmp, Tparts, overlap ? aux : st));
-    const int rest = d - k0 - nb;
-    if (rest <= 0) continue;
-    GemmArgs t{};
-    t.m = nb; t.n = rest; t.kk = nb; t.alpha = 1.0; t.beta = 0.0;
-    t.A = Dinv + (size_t)kb * 4096; t.lda = 64; t.ta = true;
-    t.B = G + (int64_t)k0 * d + k0 + nb; t.ldb = d; t.tb = false;
-    t.C = R + (int64_t)k0 * d + k0 + nb; t.ldc = d;
-    SRP_TRY(gemm_f64(t, st));
-    GemmArgs u{};
-    u.m = rest; u.n = rest; u.kk = nb; u.alpha = -1.0; u.beta = 1.0;
-    u.A = R + (int64_t)k0 * d + k0 + nb; u.lda = d; u.ta = true;
-    u.B = R + (int64_t)k0 * d + k0 + nb; u.ldb = d; u.tb = false;
-    u.C = G + (int64_t)(k0 + nb) * d + k0 + nb; u.ldc = d;
-    u.upper_only = true;
-    SRP_TRY(gemm_f64(u, st));
-  }
-  if (overlap) {   // R^-1 done on the second stream: join it
-    join.aux = nullptr;
-    SRP_HIP(hipEventRecord(ev[tiles], aux));
-    SRP_HIP(hipStreamWaitEvent(st, ev[tiles], 0));
   }
   if (Minv) {
     GemmArgs mm{};

@@ -198,3 +198,32 @@ def test_gram_pass_bf16_block_edges(n, d0, d1, k, off):
         ok = np.isfinite(r)
         assert np.array_equal(np.isfinite(g), ok)
         np.testing.assert_array_equal(g[ok], r[ok])
+
+
+# one diagonal block, a block with one column more and with one less, column
+# blocks of R^-1 with one, two, three and four 64-row blocks to add
+@pytest.mark.parametrize("d", [1, 63, 64, 65, 127, 129, 193, 256, 321])
+def test_sketch_factor_block_edges(d):
+    srp = _srp()
+    rng = np.random.default_rng(d)
+    A = rng.standard_normal((2 * d + 3, d))
+    R, Rinv = srp.srp_sketch_factor(torch.from_numpy(A).to(DEV), 0.5)
+    R, Rinv = R.cpu().numpy(), Rinv.cpu().numpy()
+    G = A.T @ A + 0.5 * np.eye(d)
+    assert not np.tril(R, -1).any() and not np.tril(Rinv, -1).any()
+    # backward error of the factor: (d + 1) u |R|^T |R|, and of the Gram: n u |A|^T |A|
+    u = 2.0 ** -53
+    assert np.all(np.abs(R.T @ R - G) <= 4 * (3 * d + 8) * u * (np.abs(R).T @ np.abs(R) + np.abs(A).T @ np.abs(A)))
+    # residual of the triangular inverse, formed by blocks: d u |R^-1| |R| |R^-1| |R|
+    W = np.abs(Rinv) @ np.abs(R)
+    assert np.all(np.abs(Rinv @ R - np.eye(d)) <= 4 * (d + 8) * u * (W @ W))
+
+
+@pytest.mark.parametrize("d,col", [(64, 63), (150, 64), (150, 149), (200, 130)])
+def test_sketch_factor_bad_pivot_in_any_block(d, col):
+    srp = _srp()
+    A = np.random.default_rng(d).standard_normal((2 * d, d))
+    A[:, col] = 0.0
+    with pytest.raises(srp.SrpError) as e:
+        srp.srp_sketch_factor(torch.from_numpy(A).to(DEV), 0.0)
+    assert e.value.code == srp.SRP_ENOTSPD
