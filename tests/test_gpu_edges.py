@@ -227,3 +227,28 @@ def test_sketch_factor_bad_pivot_in_any_block(d, col):
     with pytest.raises(srp.SrpError) as e:
         srp.srp_sketch_factor(torch.from_numpy(A).to(DEV), 0.0)
     assert e.value.code == srp.SRP_ENOTSPD
+
+
+# one bucket of more rows than a sorting workgroup holds and than a chunk it
+# compares with, more buckets than rows, rows of less than a wave of 16-byte
+# pieces and the first of more, a rest of columns, several column chunks, rows
+# off vector boundaries, data past the memory-side cache; every row added in
+# ascending order in the sketch's type, so bit for bit
+@pytest.mark.parametrize("n,d,s,dt,off", [(9001, 70, 1, "f32", 1), (5, 3, 9, "f64", 0), (2500, 127, 1, "f64", 1),
+                                          (2049, 128, 2, "f64", 1), (1025, 255, 1, "f32", 0), (4097, 257, 40, "f32", 3),
+                                          (1500, 511, 3, "bf16", 0), (1024, 1031, 8, "bf16", 1), (300, 2049, 3, "f32", 2),
+                                          (130, 4099, 2, "bf16", 1), (34001, 2001, 900, "f32", 1)])
+def test_countsketch_bucket_edges(n, d, s, dt, off):
+    from oracle import sketch as osk
+    srp = _srp()
+    tdt = {"f32": torch.float32, "bf16": torch.bfloat16, "f64": torch.float64}[dt]
+    X = torch.from_numpy(np.random.default_rng(n + d).standard_normal((n, d), dtype=np.float32)).to(tdt)
+    buf = torch.zeros(n * d + off, dtype=tdt, device=DEV)
+    buf[off:] = X.reshape(-1).to(DEV)
+    out = srp.srp_countsketch(buf[off:].view(n, d), s, 77).cpu().numpy()
+    h, g = osk.countsketch_hash(n, s, 77)
+    cols = np.unique(np.r_[0:min(d, 20), max(0, d - 20):d])
+    acc = np.float64 if dt == "f64" else np.float32
+    ref = np.zeros((s, cols.size), dtype=acc)
+    np.add.at(ref, h, g.astype(acc)[:, None] * X[:, torch.from_numpy(cols)].to(torch.float64 if dt == "f64" else torch.float32).numpy())
+    np.testing.assert_array_equal(out[:, cols], ref)
