@@ -394,7 +394,7 @@ def bench_sparse(args):
                       "parallelism": "single-gpu"},
            "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                         "frac": achieved / HBM_PEAK_GBS, "traffic": None,
-                        "kernel": "sparse data pass (CSR row products, segmented CSC column products)",
+                        "kernel": "sparse data pass (CSR row and column products)",
                         "bytes_per_launch": bytes_per_pass, "avg_launch_ms": avg_ms, "launches": launches},
            "solve": {key: infos[-1][key] for key in ("status", "iterations", "warm_iterations", "passes",
                                                      "ms_sketch", "ms_factor", "ms_warm", "ms_iterate",
@@ -547,6 +547,7 @@ def main():
                 "frac": achieved / HBM_PEAK_GBS, "traffic": profiled_traffic(prof),
                 "kernel": kname + {"k_pass_bf": " (BF16 data pass)",
                                    "k_pass_quad": " (fused FP32 data pass, 4x4 matrix-core blocks)",
+                                   "k_pass_quad1": " (fused FP32 data pass, one view, 4x4 matrix-core blocks)",
                                    "k_pass_dma": " (fused FP32 data pass)",
                                    "k_pass": " (fused data pass, register-staged rows)"}.get(kname, ""),
                 "bytes_per_launch": bytes_per_launch,
