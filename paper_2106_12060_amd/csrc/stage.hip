@@ -82,9 +82,8 @@ static StageGeom stage_geom(int64_t n, int d) {
   g.runs = (int)((int64_t)g.M * d / 4);
   g.groups = n / g.M;
   const unsigned gx = (unsigned)((g.runs + 255) / 256);
-  // about four workgroups a CU, at least eight groups each: the maxima's
-  // read of 200000 x 1000 equal values takes 132 us so, 148 with
-  // eight and 158 with sixteen a CU (more threads end in atomics)
+  // about four workgroups a CU (more only write more maxima to join), at
+  // least eight groups each
   int64_t gy = std::max<int64_t>(1, 4ll * num_cus() / gx);
   gy = std::min(gy, std::max<int64_t>(1, (g.groups + 7) / 8));
   g.per = (int)((g.groups + gy - 1) / gy);
@@ -93,16 +92,15 @@ static StageGeom stage_geom(int64_t n, int d) {
   return g;
 }
 
-// Column maxima of |x|: non-negative floats order like their bit patterns,
-// so an integer atomic max gives the exact (order-independent) maximum; a
-// thread whose maxima are not above what the array already holds skips the
-// atomic.  A whole read of the matrix, so HBM bounds it: each thread keeps
-// eight vector loads in flight (one column per thread with one 4-byte load
-// in flight: 831 us at 200000 x 1000; so: 183 us,
-// the atomics about 45 of them).
+// Maxima of |x| over a workgroup's groups, one for every position of a group.
+// A whole read of the matrix, so HBM bounds it: each thread keeps eight vector
+// loads in flight (one column per thread with one 4-byte load in flight: 831 us
+// at 200000 x 1000).  The maxima go to memory as they are (an atomic maximum a
+// column from every thread took 45 us of 183; so: 124 us, 6.5 TB/s, and 5 to
+// join them; 200000 x 64, where many threads share a column: the call 715 -> 57).
 template <class T>
-__global__ void __launch_bounds__(256) k_col_amax(const T* __restrict__ X, int64_t n, int d, StageGeom g,
-                                                  uint32_t* __restrict__ amax_bits) {
+__global__ void __launch_bounds__(256) k_col_amax(const T* __restrict__ X, int d, StageGeom g,
+                                                  float* __restrict__ part) {
   constexpr int UN = 8;
   const int t = blockIdx.x * 256 + threadIdx.x;
   if (t < g.runs) {
@@ -126,19 +124,42 @@ __global__ void __launch_bounds__(256) k_col_amax(const T* __restrict__ X, int64
 #pragma unroll
       for (int u = 0; u < 4; ++u) m[u] = fmaxf(m[u], fabsf(v[u]));
     }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      uint32_t* a = &amax_bits[(4ll * t + u) % d];
-      const uint32_t b = __float_as_uint(m[u]);
-      if (b > __hip_atomic_load(a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(a, b);
-    }
+    float4* out = reinterpret_cast<float4*>(part) + (int64_t)blockIdx.y * g.runs + t;
+    *out = make_float4(m[0], m[1], m[2], m[3]);
   }
-  if (blockIdx.y == 0) {   // the rows past the last group
-    const int64_t e0 = g.groups * g.M * d, e1 = n * d;
-    for (int64_t e = e0 + t; e < e1; e += (int64_t)gridDim.x * 256) {
-      const float m = fmaxf(0.f, fabsf(load_as<float>(X + e)));
-      atomicMax(&amax_bits[e % d], __float_as_uint(m));
-    }
+}
+
+// The column maxima from `parts` maxima of every position of a group (64
+// positions a workgroup, sixteen slices of the parts), and from the rows past
+// the last group, one workgroup past the positions.  Non-negative floats order
+// like their bit patterns, so an integer atomic maximum over a group's few rows
+// is exact whatever the order.
+template <class T>
+__global__ void __launch_bounds__(1024) k_amax_parts(const T* __restrict__ X, int64_t n, int d, StageGeom g,
+                                                     const float* __restrict__ part, int parts,
+                                                     uint32_t* __restrict__ amax_bits) {
+  __shared__ float q[16][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, count = 4 * g.runs;
+  const int p = blockIdx.x * 64 + lane;
+  if ((int)blockIdx.x * 64 >= count) {
+    for (int64_t e = g.groups * g.M * d + threadIdx.x; e < n * d; e += 1024)
+      atomicMax(&amax_bits[e % d], __float_as_uint(fmaxf(0.f, fabsf(load_as<float>(X + e)))));
+    return;
+  }
+  float m = 0.f;
+  for (int z = w; z < parts; z += 128) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = z + 16 * u < parts && p < count ? part[(int64_t)(z + 16 * u) * count + p] : 0.f;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) m = fmaxf(m, v[u]);
+  }
+  q[w][lane] = m;
+  __syncthreads();
+  if (w == 0 && p < count) {
+#pragma unroll
+    for (int i = 1; i < 16; ++i) m = fmaxf(m, q[i][lane]);
+    atomicMax(&amax_bits[p % d], __float_as_uint(m));
   }
 }
 
@@ -238,16 +259,31 @@ int stage_bf16_run(const float* X, int64_t n, int d, uint16_t* out, hipStream_t 
   return SRP_OK;
 }
 
-size_t stage_fp8_ws_bytes(int d) { return bytes_of<uint32_t>(d) + bytes_of<float>(d); }
+// The maxima of a group's positions: at most max(4 num_cus, workgroups a
+// group is wide) workgroups of 1024.
+static size_t stage_parts(int d) {
+  const int64_t wide = (4ll * ((256 + (int64_t)d - 1) / d) * d / 4 + 255) / 256;
+  return (size_t)std::max<int64_t>(4ll * num_cus(), wide) * 1024;
+}
+
+size_t stage_fp8_ws_bytes(int d) {
+  return bytes_of<uint32_t>(d) + bytes_of<float>(d) + bytes_of<float>(stage_parts(d));
+}
 
 template <class T>
 static int stage_fp8_t(const T* X, int64_t n, int d, uint8_t* out, double* scales, Arena& ws, hipStream_t st) {
   uint32_t* amax = ws.take<uint32_t>(d);
   float* inv = ws.take<float>(d);
-  if (!amax || !inv) { set_error("stage_fp8: workspace too small"); return SRP_ENOMEM; }
+  float* part = ws.take<float>(stage_parts(d));
+  if (!amax || !inv || !part) { set_error("stage_fp8: workspace too small"); return SRP_ENOMEM; }
   SRP_TRY(fill_i32((int*)amax, d, 0, st));
   const StageGeom g = stage_geom(n, d);
-  hipLaunchKernelGGL((k_col_amax<T>), g.grid, dim3(256), 0, st, X, n, d, g, amax);
+  if (g.groups > 0) {
+    hipLaunchKernelGGL((k_col_amax<T>), g.grid, dim3(256), 0, st, X, d, g, part);
+    SRP_LAUNCH_CHECK();
+  }
+  hipLaunchKernelGGL((k_amax_parts<T>), dim3((4 * g.runs + 63) / 64 + 1), dim3(1024), 0, st, X, n, d, g, part,
+                     g.groups > 0 ? (int)g.grid.y : 0, amax);
   SRP_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_fp8_scales, dim3((d + 255) / 256), dim3(256), 0, st, amax, d, scales, inv);
   SRP_LAUNCH_CHECK();
