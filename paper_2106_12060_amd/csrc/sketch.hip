@@ -286,100 +286,108 @@ int countsketch_run(const void* A, int dtype, int64_t n, int d, int s, uint64_t 
 }
 
 // --------------------------------------------------------------- SRHT
+// The threshold key of the row sample: its rows are those whose keys are at
+// most `T`, the s-th smallest of the n' keys.  The keys are a hash, so the s-th
+// smallest lies within a few standard deviations of s / n' of their range: the
+// keys in a window of eight on either side are listed and ranked, those below
+// it counted.  Where the window misses (or a list is full) one workgroup selects
+// over all keys by 8-bit digits: the same threshold, only later.
 struct SelectState {
-  uint64_t prefix;   // digits fixed so far (all 64 bits once done)
-  int need;          // how many keys still to take at or below the prefix
-  int done;          // the threshold is final: a whole bucket was taken
+  uint64_t T;
 };
-
-__global__ void k_sel_init(SelectState* st, int s) {
-  st->prefix = 0;
-  st->need = s;
-  st->done = 0;
-}
-
-// Histogram of 16-bit digit `round` (0 = most significant) over keys whose
-// higher digits equal the prefix found so far.
-__global__ void k_sel_hist(int64_t n_pad, uint64_t seed, int round, const SelectState* st, int* hist) {
-  int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= n_pad || st->done) return;
-  const uint64_t key = splitmix64(seed, (uint64_t)i);
-  if (round > 0 && (key >> (64 - 16 * round)) != st->prefix) return;
-  const int digit = (int)((key >> (48 - 16 * round)) & 0xFFFFull);
-  atomicAdd(&hist[digit], 1);
-}
-
-// Find the digit holding the need-th smallest remaining key; zero hist.
-// Thread t owns digits 64 t .. 64 t + 63 (sixteen 16-byte loads in flight),
-// the counts are scanned by lane shuffles within a wave and the sixteen
-// wave totals through LDS.  When the need-th key closes its bucket (the
-// bucket is taken whole) the threshold is that bucket's prefix followed by
-// all ones, the same key set as finishing the remaining rounds, and they
-// are skipped.
-__global__ void __launch_bounds__(1024) k_sel_pick(int* hist, SelectState* st, int round) {
-  __shared__ int wsum[16];
-  __shared__ int found_digit, found_before, found_count;
-  if (st->done) return;
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  int4* h4 = reinterpret_cast<int4*>(hist) + 16 * t;
-  int4 v[16];
-#pragma unroll
-  for (int j = 0; j < 16; ++j) v[j] = h4[j];
-  int sum = 0;
-#pragma unroll
-  for (int j = 0; j < 16; ++j) sum += v[j].x + v[j].y + v[j].z + v[j].w;
-  int incl = sum;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int u = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += u;
-  }
-  if (lane == 63) wsum[wv] = incl;
-  __syncthreads();
-  for (int k = 0; k < wv; ++k) incl += wsum[k];
-  const int need = st->need;
-  const int before = incl - sum;
-  if (before < need && need <= incl) {
-    int run = before;
-    bool done = false;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const int c4[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (!done && run + c4[q] >= need) {
-          found_digit = 64 * t + 4 * j + q;
-          found_before = run;
-          found_count = c4[q];
-          done = true;
-        }
-        run += c4[q];
-      }
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < 16; ++j) h4[j] = make_int4(0, 0, 0, 0);
-  __syncthreads();
-  if (t == 0) {
-    const uint64_t prefix = (st->prefix << 16) | (uint64_t)found_digit;
-    const int left = need - found_before;
-    const int rest = 16 * (3 - round);   // key bits below this digit
-    if (rest > 0 && left == found_count) {
-      st->prefix = (prefix << rest) | ((uint64_t(1) << rest) - 1);
-      st->done = 1;
-    } else {
-      st->prefix = prefix;
-    }
-    st->need = left;
-  }
-}
-
 constexpr int kSelChunk = 1024;
+constexpr int kSelList = 32768;   // keys of all chunks' lists
+constexpr int kSelRank = 4096;    // keys ranked
+
+// Keys a chunk may list.
+static int sel_cap(int chunks) { return std::min(128, kSelList / chunks); }
+
+// Chunk `blockIdx.x`: keys under lo counted, those in [lo, hi] listed.
+__global__ void __launch_bounds__(256) k_sel_window(int64_t n_pad, uint64_t seed, uint64_t lo, uint64_t hi, int cap,
+                                                    int* __restrict__ below, int* __restrict__ inside,
+                                                    uint64_t* __restrict__ list) {
+  __shared__ int nb, ni;
+  if (threadIdx.x == 0) nb = ni = 0;
+  __syncthreads();
+  const int64_t base = (int64_t)blockIdx.x * kSelChunk;
+  int c = 0;
+#pragma unroll
+  for (int j = 0; j < kSelChunk / 256; ++j) {
+    const int64_t i = base + threadIdx.x + 256 * j;
+    if (i >= n_pad) continue;
+    const uint64_t key = splitmix64(seed, (uint64_t)i);
+    if (key < lo) {
+      ++c;
+    } else if (key <= hi) {
+      const int pos = atomicAdd(&ni, 1);
+      if (pos < cap) list[(int64_t)blockIdx.x * cap + pos] = key;
+    }
+  }
+  if (c) atomicAdd(&nb, c);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    below[blockIdx.x] = nb;
+    inside[blockIdx.x] = ni;
+  }
+}
+
+// T from the chunks' counts and lists (at most 1024 chunks, one a thread).
+__global__ void __launch_bounds__(1024) k_sel_rank(int64_t n_pad, uint64_t seed, int s, int chunks, int cap,
+                                                   const int* __restrict__ below, const int* __restrict__ inside,
+                                                   const uint64_t* __restrict__ list, SelectState* __restrict__ st) {
+  __shared__ uint64_t keys[kSelRank];
+  __shared__ int hist[256];
+  __shared__ int total, low, bad, digit, before;
+  const int t = threadIdx.x;
+  if (t == 0) total = low = bad = 0;
+  __syncthreads();
+  if (t < chunks) {
+    const int m = inside[t];
+    atomicAdd(&low, below[t]);
+    if (m > cap) bad = 1;
+    const int at = atomicAdd(&total, m);
+    if (m <= cap && at + m <= kSelRank)
+      for (int i = 0; i < m; ++i) keys[at + i] = list[(int64_t)t * cap + i];
+  }
+  __syncthreads();
+  const int W = total, need = s - low;
+  if (!bad && W <= kSelRank && need >= 1 && need <= W) {
+    for (int e = t; e < W; e += 1024) {
+      const uint64_t k = keys[e];
+      int r = 0;
+      for (int i = 0; i < W; ++i) r += keys[i] < k;
+      if (r == need - 1) st->T = k;   // the keys are distinct
+    }
+    return;
+  }
+  uint64_t prefix = 0;
+  int left = s;
+  for (int shift = 56; shift >= 0; shift -= 8) {
+    if (t < 256) hist[t] = 0;
+    __syncthreads();
+    for (int64_t i = t; i < n_pad; i += 1024) {
+      const uint64_t key = splitmix64(seed, (uint64_t)i);
+      if (shift == 56 || (key >> (shift + 8)) == (prefix >> (shift + 8))) atomicAdd(&hist[(key >> shift) & 255], 1);
+    }
+    __syncthreads();
+    if (t == 0) {
+      int run = 0, q = 0;
+      while (q < 255 && run + hist[q] < left) run += hist[q++];
+      digit = q;
+      before = run;
+    }
+    __syncthreads();
+    prefix |= (uint64_t)digit << shift;
+    left -= before;
+    __syncthreads();
+  }
+  if (t == 0) st->T = prefix;
+}
 
 __global__ void __launch_bounds__(256) k_sel_count(int64_t n_pad, uint64_t seed, const SelectState* st, int* counts) {
   __shared__ int red[256];
   const int64_t base = (int64_t)blockIdx.x * kSelChunk;
-  const uint64_t T = st->prefix;
+  const uint64_t T = st->T;
   int c = 0;
   for (int j = threadIdx.x; j < kSelChunk; j += 256) {
     const int64_t i = base + j;
@@ -398,7 +406,7 @@ __global__ void __launch_bounds__(256) k_sel_write(int64_t n_pad, uint64_t seed,
                                                    const int* offsets, int64_t* rows) {
   __shared__ int pre[256];
   const int64_t base = (int64_t)blockIdx.x * kSelChunk;
-  const uint64_t T = st->prefix;
+  const uint64_t T = st->T;
   // each thread owns 4 consecutive indices
   int flags[4];
   int c = 0;
@@ -454,22 +462,21 @@ static SrhtGeom srht_geom(int64_t n, int s = 0) {
 
 static int srht_select_rows(int64_t n_pad, int s, uint64_t seed, int64_t* rows, Arena& ws, hipStream_t st) {
   const uint64_t seedR = seed ^ kSrhtRowSalt;
-  int* hist = ws.take<int>(65536);
+  uint64_t* list = ws.take<uint64_t>(kSelList);
   SelectState* state = ws.take<SelectState>(1);
   const int chunks = (int)((n_pad + kSelChunk - 1) / kSelChunk);
   int* counts = ws.take<int>(chunks + 1);
   int* offsets = ws.take<int>(chunks + 1);
   if (!offsets) { set_error("srht: workspace too small"); return SRP_ENOMEM; }
-  SRP_TRY(fill_i32(hist, 65536, 0, st));
-  hipLaunchKernelGGL(k_sel_init, dim3(1), dim3(1), 0, st, state, s);
+  // about eight standard deviations of the count under a key on either side
+  const double n = (double)n_pad, sd = 8.0 * std::sqrt(s * (1.0 - s / n)) + 8.0, unit = 18446744073709551616.0 / n;
+  const uint64_t lo = s > sd ? (uint64_t)((s - sd) * unit) : 0;
+  const uint64_t hi = s + sd < n ? (uint64_t)((s + sd) * unit) : ~uint64_t(0);
+  const int cap = sel_cap(chunks);
+  hipLaunchKernelGGL(k_sel_window, dim3(chunks), dim3(256), 0, st, n_pad, seedR, lo, hi, cap, counts, offsets, list);
   SRP_LAUNCH_CHECK();
-  const unsigned nb = (unsigned)((n_pad + 255) / 256);
-  for (int round = 0; round < 4; ++round) {
-    hipLaunchKernelGGL(k_sel_hist, dim3(nb), dim3(256), 0, st, n_pad, seedR, round, state, hist);
-    SRP_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_sel_pick, dim3(1), dim3(1024), 0, st, hist, state, round);
-    SRP_LAUNCH_CHECK();
-  }
+  hipLaunchKernelGGL(k_sel_rank, dim3(1), dim3(1024), 0, st, n_pad, seedR, s, chunks, cap, counts, offsets, list, state);
+  SRP_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_sel_count, dim3(chunks), dim3(256), 0, st, n_pad, seedR, state, counts);
   SRP_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_scan_excl, dim3(1), dim3(1024), 0, st, counts, chunks, offsets, (int*)nullptr);
@@ -1182,7 +1189,7 @@ size_t srht_ws_bytes(int64_t n, int d, int s, int dtype) {
   SrhtGeom g = srht_geom(n, s);
   const size_t acc = dtype == SRP_F64 ? 8 : 4;
   const int chunks = (int)((g.n_pad + kSelChunk - 1) / kSelChunk);
-  return bytes_of<int>(65536) + bytes_of<SelectState>(1) + 2 * bytes_of<int>(chunks + 1) +
+  return bytes_of<uint64_t>(kSelList) + bytes_of<SelectState>(1) + 2 * bytes_of<int>(chunks + 1) +
          bytes_of<int64_t>(s) + bytes_of<int>(g.B + 1) + 2 * bytes_of<int>(s) +
          bytes_of<uint32_t>((size_t)srht_sign_words(g)) + (((size_t)g.A_eff * g.B * d * acc + 255) & ~size_t(255));
 }

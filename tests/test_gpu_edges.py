@@ -252,3 +252,16 @@ def test_countsketch_bucket_edges(n, d, s, dt, off):
     ref = np.zeros((s, cols.size), dtype=acc)
     np.add.at(ref, h, g.astype(acc)[:, None] * X[:, torch.from_numpy(cols)].to(torch.float64 if dt == "f64" else torch.float32).numpy())
     np.testing.assert_array_equal(out[:, cols], ref)
+
+
+# the window around the threshold: whole key range, all rows, one row, lists
+# that overflow (selection over all keys instead), one chunk, the most chunks
+@pytest.mark.parametrize("n,s", [(2, 1), (2, 2), (100, 128), (1024, 512), (1024, 1), (3000, 2048), (4096, 4096),
+                                 (65536, 30000), (200000, 4000), (200000, 262144), (1 << 20, 1), (1 << 20, 20000),
+                                 (1 << 20, 500000)])
+@pytest.mark.parametrize("seed", [0, 987654321])
+def test_srht_row_sample_edges(n, s, seed):
+    from oracle import sketch as osk
+    srp = _srp()
+    rows = srp.srp_srht_rows(n, s, seed).cpu().numpy()
+    np.testing.assert_array_equal(rows, osk.srht_rows(osk.srht_padded_rows(n), s, seed))
