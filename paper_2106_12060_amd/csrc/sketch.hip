@@ -289,7 +289,7 @@ int countsketch_run(const void* A, int dtype, int64_t n, int d, int s, uint64_t 
 // The threshold key of the row sample: its rows are those whose keys are at
 // most `T`, the s-th smallest of the n' keys.  The keys are a hash, so the s-th
 // smallest lies within a few standard deviations of s / n' of their range: the
-// keys in a window of eight on either side are listed and ranked, those below
+// keys in a window of six on either side are listed and ranked, those below
 // it counted.  Where the window misses (or a list is full) one workgroup selects
 // over all keys by 8-bit digits: the same threshold, only later.
 struct SelectState {
@@ -297,7 +297,7 @@ struct SelectState {
 };
 constexpr int kSelChunk = 1024;
 constexpr int kSelList = 32768;   // keys of all chunks' lists
-constexpr int kSelRank = 4096;    // keys ranked
+constexpr int kSelRank = 3072;    // keys ranked
 
 // Keys a chunk may list.
 static int sel_cap(int chunks) { return std::min(128, kSelList / chunks); }
@@ -332,11 +332,11 @@ __global__ void __launch_bounds__(256) k_sel_window(int64_t n_pad, uint64_t seed
 }
 
 // T from the chunks' counts and lists (at most 1024 chunks, one a thread).
-__global__ void __launch_bounds__(1024) k_sel_rank(int64_t n_pad, uint64_t seed, int s, int chunks, int cap,
+__global__ void __launch_bounds__(1024) k_sel_rank(int64_t n_pad, uint64_t seed, int s, uint64_t lo, uint64_t hi, int chunks, int cap,
                                                    const int* __restrict__ below, const int* __restrict__ inside,
                                                    const uint64_t* __restrict__ list, SelectState* __restrict__ st) {
-  __shared__ uint64_t keys[kSelRank];
-  __shared__ int hist[256];
+  __shared__ uint64_t keys[kSelRank], few[kSelRank];
+  __shared__ int hist[256], bins[1024];
   __shared__ int total, low, bad, digit, before;
   const int t = threadIdx.x;
   if (t == 0) total = low = bad = 0;
@@ -352,10 +352,40 @@ __global__ void __launch_bounds__(1024) k_sel_rank(int64_t n_pad, uint64_t seed,
   __syncthreads();
   const int W = total, need = s - low;
   if (!bad && W <= kSelRank && need >= 1 && need <= W) {
-    for (int e = t; e < W; e += 1024) {
-      const uint64_t k = keys[e];
-      int r = 0;
-      for (int i = 0; i < W; ++i) r += keys[i] < k;
+    // the bin of the window (one a thread) that holds the need-th key, then
+    // the rank among that bin's few (every key against all of a list of a
+    // thousand: 27 us, the reads of LDS)
+    const int sh = max(0, 54 - __clzll((long long)((hi - lo) | 1)));
+    auto bin_of = [&](uint64_t k) { return (int)((k - lo) >> sh); };   // < 1024
+    bins[t] = 0;
+    __syncthreads();
+    for (int e = t; e < W; e += 1024) atomicAdd(&bins[bin_of(keys[e])], 1);
+    __syncthreads();
+    const int mine = bins[t], lane = t & 63, w = t >> 6;
+    int incl = mine;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int o = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += o;
+    }
+    if (lane == 63) hist[w] = incl;
+    if (t == 0) total = 0;
+    __syncthreads();
+    for (int i = 0; i < w; ++i) incl += hist[i];
+    if (incl - mine < need && need <= incl) {
+      digit = t;
+      before = incl - mine;
+    }
+    __syncthreads();
+    const int target = digit;
+    for (int e = t; e < W; e += 1024)
+      if (bin_of(keys[e]) == target) few[atomicAdd(&total, 1)] = keys[e];
+    __syncthreads();
+    const int m = total;
+    for (int e = t; e < m; e += 1024) {
+      const uint64_t k = few[e];
+      int r = before;
+      for (int i = 0; i < m; ++i) r += few[i] < k;
       if (r == need - 1) st->T = k;   // the keys are distinct
     }
     return;
@@ -468,14 +498,14 @@ static int srht_select_rows(int64_t n_pad, int s, uint64_t seed, int64_t* rows, 
   int* counts = ws.take<int>(chunks + 1);
   int* offsets = ws.take<int>(chunks + 1);
   if (!offsets) { set_error("srht: workspace too small"); return SRP_ENOMEM; }
-  // about eight standard deviations of the count under a key on either side
-  const double n = (double)n_pad, sd = 8.0 * std::sqrt(s * (1.0 - s / n)) + 8.0, unit = 18446744073709551616.0 / n;
+  // six standard deviations of the count under a key on either side
+  const double n = (double)n_pad, sd = 6.0 * std::sqrt(s * (1.0 - s / n)) + 8.0, unit = 18446744073709551616.0 / n;
   const uint64_t lo = s > sd ? (uint64_t)((s - sd) * unit) : 0;
   const uint64_t hi = s + sd < n ? (uint64_t)((s + sd) * unit) : ~uint64_t(0);
   const int cap = sel_cap(chunks);
   hipLaunchKernelGGL(k_sel_window, dim3(chunks), dim3(256), 0, st, n_pad, seedR, lo, hi, cap, counts, offsets, list);
   SRP_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_sel_rank, dim3(1), dim3(1024), 0, st, n_pad, seedR, s, chunks, cap, counts, offsets, list, state);
+  hipLaunchKernelGGL(k_sel_rank, dim3(1), dim3(1024), 0, st, n_pad, seedR, s, lo, hi, chunks, cap, counts, offsets, list, state);
   SRP_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_sel_count, dim3(chunks), dim3(256), 0, st, n_pad, seedR, state, counts);
   SRP_LAUNCH_CHECK();
