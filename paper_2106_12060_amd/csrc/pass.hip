@@ -12,7 +12,10 @@
 // accumulates A_b^T [P_0 | P_1] for half of the columns, which halves the
 // accumulator registers a wave must keep.
 // The block is staged in LDS (row-major, row pitch = 4 mod 64 elements so
-// both access patterns below are bank-conflict free); while the matrix
+// both access patterns below are bank-conflict free; A_1's tiles follow
+// A_0's, and the columns between a view's last and its last tile's are
+// zeros: the tiles there meet zero directions, which an infinity or a NaN of
+// another column would survive); while the matrix
 // cores work on block i, the global loads of the workgroup's next block are
 // already in flight into registers.  The direction operands of a wave's
 // P tiles stay in registers for the whole launch when they fit (64 per
@@ -37,7 +40,8 @@ namespace srp {
 
 constexpr int kPassWaves = 8;
 constexpr int kPassThreads = 64 * kPassWaves;
-constexpr int kPassLds = 150 * 1024;   // LDS budget of the row-block stage
+constexpr int kLdsBytes = 160 * 1024;   // of a CU
+constexpr int kPassLds = 150 * 1024;    // of the row-block stage for rows of d0 + d1 columns; whole tiles take 8 KB more at most
 
 // Largest d0 + d1 per compute type, and loads per row per thread.
 template <class CT> struct PassCfg;
@@ -109,7 +113,9 @@ __global__ void __launch_bounds__(kPassThreads) k_pass(const DT* __restrict__ A0
   using acc_t = typename Acc4<CT>::type;
   extern __shared__ unsigned char pass_smem[];
   const int D = d0 + (NB == 2 ? d1 : 0);
-  const int pitch = pass_pitch(D);
+  const int T0 = (d0 + 15) >> 4;
+  const int TT = T0 + (NB == 2 ? ((d1 + 15) >> 4) : 0);
+  const int pitch = pass_pitch(16 * TT);
   CT* xs = reinterpret_cast<CT*>(pass_smem);                 // [16][pitch]
   CT* red = xs + 16 * pitch;                                  // [waves][NT][256]
   CT* pfull = red + kPassWaves * NT * 256;                    // [NT][16][17]
@@ -118,8 +124,12 @@ __global__ void __launch_bounds__(kPassThreads) k_pass(const DT* __restrict__ A0
   const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, l16 = lane & 15;
-  const int T0 = (d0 + 15) >> 4;
-  const int TT = T0 + (NB == 2 ? ((d1 + 15) >> 4) : 0);
+  // the columns past each view's last, which the staging leaves alone
+  for (int e = tid; e < 16 * 16 * NB; e += kPassThreads) {
+    const int r = (e >> 4) & 15, v = e >> 8;
+    const int c = (v ? 16 * T0 + d1 : d0) + (e & 15);
+    if (c < 16 * (v ? TT : T0)) xs[r * pitch + c] = CT(0);
+  }
   // pair mapping: XCD x, half h, group q  ->  row group rg
   const int bx = blockIdx.x;
   const int xcd = bx % kXcds, half = (bx / kXcds) % kPassSplit, grp = bx / (kXcds * kPassSplit);
@@ -191,20 +201,20 @@ __global__ void __launch_bounds__(kPassThreads) k_pass(const DT* __restrict__ A0
     __syncthreads();   // previous block fully consumed
 #pragma unroll
     for (int j = 0; j < JPF; ++j) {
-      const int c = tid + kPassThreads * j;
+      const int c = tid + kPassThreads * j, at = c < d0 ? c : c - d0 + 16 * T0;
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        if (c < pitch) xs[r * pitch + c] = (c < D) ? cvt<CT>(pf[r][j]) : CT(0);
+        if (c < D) xs[r * pitch + at] = cvt<CT>(pf[r][j]);
     }
     if (JPF < JPR) {
 #pragma unroll
       for (int j = JPF; j < JPR; ++j) {
-        const int c = tid + kPassThreads * j;
-        if (kPassThreads * j < pitch) {
+        const int c = tid + kPassThreads * j, at = c < d0 ? c : c - d0 + 16 * T0;
+        if (kPassThreads * j < D) {
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const DT v = load_elem((int64_t)rb * 16 + r, j);
-            if (c < pitch) xs[r * pitch + c] = (c < D) ? cvt<CT>(v) : CT(0);
+            if (c < D) xs[r * pitch + at] = cvt<CT>(v);
           }
         }
       }
@@ -222,11 +232,9 @@ __global__ void __launch_bounds__(kPassThreads) k_pass(const DT* __restrict__ A0
       const int t = w + kPassWaves * i;
       if (t < TT) {
         const bool b1 = (NB == 2) && (t >= T0);
-        const int ct = b1 ? t - T0 : t;
-        const int cbase = (b1 ? d0 : 0) + ct * 16;   // column of the tile in xs
 #pragma unroll
         for (int s2 = 0; s2 < 4; ++s2) {
-          const CT a = xs[l16 * pitch + cbase + 4 * s2 + g];
+          const CT a = xs[l16 * pitch + 16 * t + 4 * s2 + g];
 #pragma unroll
           for (int kt = 0; kt < KT; ++kt) {
             const CT bw = WREG ? wreg[WREG ? i : 0][s2][kt] : w_operand(t, s2, kt);
@@ -259,11 +267,9 @@ __global__ void __launch_bounds__(kPassThreads) k_pass(const DT* __restrict__ A0
     for (int i = 0; i < TPW; ++i) {
       const int t = tbeg + w + kPassWaves * i;
       if (t < tend) {
-        const bool b1 = (NB == 2) && (t >= T0);
-        const int cbase = (b1 ? d0 + (t - T0) * 16 : t * 16) + l16;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-          const CT a = xs[(4 * g + s) * pitch + cbase];
+          const CT a = xs[(4 * g + s) * pitch + 16 * t + l16];
 #pragma unroll
           for (int nt = 0; nt < NT; ++nt)
             acc[i][nt] = mfma16x16x4(a, pfull[nt * 272 + (4 * g + s) * 17 + l16], acc[i][nt]);
@@ -991,8 +997,9 @@ static bool dma_fits(int d0, int d1, int k, int nb, int vec) {
   return dma_lds_bytes(d0, d1) <= (size_t)kPassLds + 8 * 1024;
 }
 
-template <class CT> static size_t pass_lds_bytes(int D, int NT) {
-  return ((size_t)16 * pass_pitch(D) + (size_t)kPassWaves * NT * 256 + (size_t)NT * 272) * sizeof(CT);
+// cols: columns of a staged row (16 a tile).
+template <class CT> static size_t pass_lds_bytes(int cols, int NT) {
+  return ((size_t)16 * pass_pitch(cols) + (size_t)kPassWaves * NT * 256 + (size_t)NT * 272) * sizeof(CT);
 }
 
 // Counter that the pass reductions of the current gram_pass_run call on
@@ -1430,11 +1437,11 @@ static int pass_launch(const DT* A0, const DT* A1, int64_t n, int d0, int d1, in
   if (!Wp0 || !part || (NB == 2 && !Wp1)) { set_error("gram_pass: workspace too small"); return SRP_ENOMEM; }
   SRP_TRY(pack_dirs<CT>(W0, d0, dp0, Wp0, W1, d1, dp1, Wp1, k, KP, st));
   const int nrb = (int)((n + 15) / 16);
-  const size_t lds = pass_lds_bytes<CT>(Dtot, NB * KT);
+  const size_t lds = pass_lds_bytes<CT>(dp0 + dp1, NB * KT);
   constexpr int TM = PassCfg<CT>::dmax / 16;
   auto launch = [&](auto tmax) -> int {
     constexpr int T = decltype(tmax)::value;
-    SRP_TRY(allow_dynamic_lds((const void*)k_pass<DT, CT, NB, KT, T>, kPassLds));
+    SRP_TRY(allow_dynamic_lds((const void*)k_pass<DT, CT, NB, KT, T>, kLdsBytes));
     if (before_pass) SRP_HIP(hipEventRecord(before_pass, st));
     hipLaunchKernelGGL((k_pass<DT, CT, NB, KT, T>), dim3(grid), dim3(kPassThreads), lds, st, A0, A1, n, d0,
                        NB == 2 ? d1 : 0, k, Wp0, Wp1, nrb, part, done);

@@ -265,3 +265,41 @@ def test_srht_row_sample_edges(n, s, seed):
     srp = _srp()
     rows = srp.srp_srht_rows(n, s, seed).cpu().numpy()
     np.testing.assert_array_equal(rows, osk.srht_rows(osk.srht_padded_rows(n), s, seed))
+
+
+def poison_lds():
+    """Leaves quiet NaNs of both precisions all over every CU's LDS: a pass
+    over rows that hold nothing else, more row blocks than workgroups."""
+    srp = _srp()
+    bits = torch.full((16 * 2048, 896), 0x7FFFFFFF7FFFFFFF, dtype=torch.int64, device=DEV)
+    srp.srp_gram_pass(bits.view(torch.float64), torch.ones((896, 16), dtype=torch.float64, device=DEV), compute="f64")
+
+
+# views whose last tile reaches past the row's pitch (the last row's into what
+# follows the block), or past the columns that are staged (2048 in FP32); the
+# first view's last tile ends inside the second's columns
+@pytest.mark.parametrize("d0,d1,dt,comp", [(63, 65, "f64", "f64"), (100, 27, "f64", "f64"), (127, 65, "bf16", "f64"),
+                                           (35, 29, "f32", "f32"), (30, 33, "bf16", "f32"), (1985, 63, "f32", "f32"),
+                                           (1023, 1025, "bf16", "f32"), (831, 65, "f32", "f64")])
+def test_gram_pass_reads_only_its_columns(d0, d1, dt, comp):
+    """Whole numbers (exact in every precision here), after a call that
+    filled LDS with NaNs; then an infinity in the second view's first column,
+    which must reach P_1 and J_1's first row only."""
+    srp = _srp()
+    tdt = {"f32": torch.float32, "bf16": torch.bfloat16, "f64": torch.float64}[dt]
+    n, k = 70, 3
+    rng = np.random.default_rng(d0)
+    A = [rng.choice([-1.0, 1.0], size=(n, d)) for d in (d0, d1)]
+    W = [rng.choice([-1.0, 1.0], size=(d, k)) for d in (d0, d1)]
+    for planted in (False, True):
+        if planted:
+            A[1][n // 2, 0] = np.inf
+        with np.errstate(invalid="ignore"):
+            P = np.concatenate([a @ w for a, w in zip(A, W)], axis=1)
+            ref = [a.T @ P for a in A]
+        D = [torch.from_numpy(a).to(tdt).to(DEV) for a in A]
+        Wd = [torch.from_numpy(w).to(DEV) for w in W]
+        poison_lds()
+        out = srp.srp_gram_pass(D[0], Wd[0], D[1], Wd[1], compute=comp)
+        for g, r in zip(out, ref):
+            np.testing.assert_array_equal(g.cpu().numpy(), r)
