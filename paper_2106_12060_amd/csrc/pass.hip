@@ -624,12 +624,12 @@ struct PipeShape {
 // end of the data, into dst: chunks of 256 columns (16 bytes a lane), rows
 // past the end read zero through the resource's range check.  Columns
 // between a view's last and its last tile's read the next row's first
-// values (they meet zero direction rows in P and land in J rows that are not
-// stored).  Rows need not start on 16-byte boundaries (a 16-byte load takes
-// any 4-byte one); but a load that straddles the end of the matrix must not
-// lose its valid part to the range check, so the block with the last row is
-// loaded 4 bytes a lane when a row is no multiple of 16 bytes.  Returns the
-// number of loads in flight for the block (0 stands for "wait for all").
+// values (they stay out of P and land in J rows that are not stored).  Rows
+// need not start on 16-byte boundaries (a 16-byte load takes any 4-byte one);
+// but a load that straddles the end of the matrix must not lose its valid part
+// to the range check, so the block with the last row is loaded 4 bytes a lane
+// when a row is no multiple of 16 bytes.  Returns the number of loads in
+// flight for the block (0 stands for "wait for all").
 template <int NV, int R, int PITCH, bool NT>
 __device__ __forceinline__ int pipe_load(const float* a0, const float* a1, int64_t left, int d0, int d1, int T0,
                                          int T1, float* __restrict__ dst, int lane) {
@@ -672,9 +672,22 @@ __device__ __forceinline__ void pipe_wait(int n) {
   }
 }
 
+// Zeroes the columns c .. end - 1 (at most three) of the block in xs that
+// share a quadruple of columns with a view's last: they meet zero direction
+// rows in P, but an infinity or a NaN of the next row there would turn this
+// row's P into NaN.  The wave that owns the tile does it before its own reads,
+// which follow in order (the loader, after its wait for the block: 200000 x
+// (66 + 50), k = 4 83 -> 88 us a call, here 83).
+template <class S>
+__device__ __forceinline__ void pipe_clear(float* xs, int c, int end, int lane) {
+  asm volatile("");   // keeps the caller's test a scalar branch, which the other waves take
+  c += lane & 3;
+  if (c < end && lane < 4 * S::R) xs[(lane >> 2) * S::PITCH + c] = 0.f;
+}
+
 // A producer's partial of P for the block in xs (ngrp groups).  pcol: the
-// LDS column of this lane's quadruple in group 0; nok: groups whose tile of
-// this lane row exists (the zeros of the row's padding stand for the rest).
+// LDS column of this lane's quadruple in group 0; nok: groups whose quadruple
+// of this lane exists (the zeros of the row's padding stand for the rest).
 template <class S>
 __device__ __forceinline__ void pipe_produce(const float* __restrict__ xs, float* __restrict__ part, int w, int lane,
                                              int ngrp, const float (&wreg)[S::PG][4][S::KG], int pcol, int nok) {
@@ -871,10 +884,15 @@ __global__ void __launch_bounds__(kF32Threads) k_pass_quad(const float* __restri
     const int wl = v1 ? w - S::NPV : w;
     const int Tv = v1 ? T1 : T0;
     const int ngrp = (((Tv + 3) >> 2) - wl + S::NPV - 1) / S::NPV;
-    const __amdgpu_buffer_rsrc_t wrs = make_rsrc(v1 ? W1 : W0, (int64_t)(v1 ? d1 : d0) * k * 8);
+    const int dv = v1 ? d1 : d0;
+    const __amdgpu_buffer_rsrc_t wrs = make_rsrc(v1 ? W1 : W0, (int64_t)dv * k * 8);
     float wreg[PG][4][KG];
     const int pcol = 16 * ((v1 ? T0 : 0) + 4 * wl + g) + 4 * cs;
-    const int nok = (Tv - (4 * wl + g) + 4 * S::NPV - 1) / (4 * S::NPV);   // <= 0 where the first is past the last
+    const int tend = 16 * (Tv - 1) + 4 * cs < dv ? Tv : Tv - 1;   // tiles with this lane's quadruple
+    const int nok = (tend - (4 * wl + g) + 4 * S::NPV - 1) / (4 * S::NPV);   // <= 0 where the first is past the last
+    // the wave with the view's last tile clears what its last quadruple has past the view
+    const int clast = (v1 ? 16 * T0 : 0) + dv, cend = (clast + 3) & ~3;
+    const bool clears = clast < cend && ((Tv - 1) >> 2) % S::NPV == wl;
     // the padding of the ring's rows, which no load touches
     for (int e = tid; e < kPipeRing * R * 16; e += 64 * kPipeProd) dsm[(e >> 4) * S::PITCH + S::PITCH - 16 + (e & 15)] = 0.f;
 #pragma unroll
@@ -892,8 +910,10 @@ __global__ void __launch_bounds__(kF32Threads) k_pass_quad(const float* __restri
     }
     lds_only_barrier();
     for (int i = 0; i <= nst; ++i) {
-      if (i < nst)
+      if (i < nst) {
+        if (clears) pipe_clear<S>(dsm + (i & 3) * S::BUF, clast, cend, lane);
         pipe_produce<S>(dsm + (i & 3) * S::BUF, parts + (i & 1) * S::PART, w, lane, ngrp, wreg, pcol, nok);
+      }
       lds_only_barrier();
     }
   } else {

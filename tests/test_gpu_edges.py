@@ -303,3 +303,28 @@ def test_gram_pass_reads_only_its_columns(d0, d1, dt, comp):
         out = srp.srp_gram_pass(D[0], Wd[0], D[1], Wd[1], compute=comp)
         for g, r in zip(out, ref):
             np.testing.assert_array_equal(g.cpu().numpy(), r)
+
+
+# widths that end in each way inside a 16-byte piece and a tile, blocks of 4,
+# 8 and 16 rows, one and two views
+@pytest.mark.parametrize("n,d0,d1,k", [(5000, 301, 203, 8), (9000, 250, 0, 12), (4500, 333, 335, 16), (9001, 1000, 0, 19),
+                                       (9000, 998, 500, 7), (700, 66, 79, 2), (40, 2047, 0, 20), (33, 1500, 484, 8)])
+def test_gram_pass_row_keeps_to_its_columns(n, d0, d1, k):
+    """Whole numbers with an infinity in the first and in the last column of
+    single rows, one of them a block's first: it reaches the sums of its own
+    row's products only."""
+    srp = _srp()
+    assert srp.srp_gram_pass_kernel("f32", "f32", d0, d1, k).startswith("k_pass_quad")
+    rng = np.random.default_rng(n + d0)
+    for r, c in ((32, 0), (17, 0), (n - 1, 0), (15, -1)):
+        A = [rng.choice([-1.0, 1.0], size=(n, d)).astype(np.float32) for d in (d0, d1) if d]
+        W = [rng.choice([-1.0, 1.0], size=(d, k)) for d in (d0, d1) if d]
+        A[-1][r, c] = np.inf
+        with np.errstate(invalid="ignore"):
+            P = np.concatenate([a.astype(np.float64) @ w for a, w in zip(A, W)], axis=1)
+            ref = [a.T.astype(np.float64) @ P for a in A]
+        D = [torch.from_numpy(a).to(DEV) for a in A]
+        Wd = [torch.from_numpy(w).to(DEV) for w in W]
+        out = srp.srp_gram_pass(D[0], Wd[0], *((D[1], Wd[1]) if d1 else ()))
+        for g, q in zip(out, ref):
+            np.testing.assert_array_equal(g.cpu().numpy(), q)
