@@ -328,3 +328,29 @@ def test_gram_pass_row_keeps_to_its_columns(n, d0, d1, k):
         out = srp.srp_gram_pass(D[0], Wd[0], *((D[1], Wd[1]) if d1 else ()))
         for g, q in zip(out, ref):
             np.testing.assert_array_equal(g.cpu().numpy(), q)
+
+
+# the shapes of test_gram_pass_block_edges on whole numbers whose sums are
+# exact in FP32: a row or a column left out or read twice anywhere changes the
+# result
+@pytest.mark.parametrize("n,d0,d1,k,off", [(1, 64, 49, 1, 0), (3, 513, 0, 20, 1), (17, 49, 0, 16, 3),
+                                           (8209, 256, 256, 16, 0), (8200, 257, 256, 9, 1), (9001, 512, 0, 17, 2),
+                                           (9001, 513, 511, 14, 3), (2047, 1024, 0, 20, 0), (2049, 1025, 0, 3, 1),
+                                           (1777, 1024, 1024, 10, 0), (1779, 1023, 1017, 7, 2), (777, 2048, 0, 19, 0),
+                                           (640, 1500, 500, 10, 0), (3001, 99, 1201, 5, 3), (70003, 999, 50, 4, 0),
+                                           (70003, 999, 2, 4, 0), (70001, 1000, 0, 12, 1), (5003, 700, 600, 14, 1)])
+def test_gram_pass_block_edges_exact(n, d0, d1, k, off):
+    srp = _srp()
+    rng = np.random.default_rng(n + d0 + d1)
+    A = [rng.integers(-1, 2, size=(n, d)).astype(np.float32) for d in (d0, d1) if d]
+    W = [rng.choice([-1.0, 1.0], size=(d, k)) for d in (d0, d1) if d]
+    for a in A:   # the last rows and every view's first and last columns take part
+        a[-32:] = rng.choice([-1.0, 1.0], size=a[-32:].shape)
+        a[:, [0, -1]] = rng.choice([-1.0, 1.0], size=(n, 2))
+    P = np.concatenate([a.astype(np.float64) @ w for a, w in zip(A, W)], axis=1)
+    assert np.abs(P).sum(axis=0).max() < 2 ** 24   # bounds every partial sum
+    D = [off_boundary(a, off + 1 - i) if off else off_boundary(a, 0) for i, a in enumerate(A)]
+    Wd = [torch.from_numpy(w).to(DEV) for w in W]
+    out = srp.srp_gram_pass(D[0], Wd[0], *((D[1], Wd[1]) if d1 else ()))
+    for g, a in zip(out, A):
+        np.testing.assert_array_equal(g.cpu().numpy(), a.T.astype(np.float64) @ P)
