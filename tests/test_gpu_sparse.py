@@ -173,3 +173,41 @@ def test_csr_rejects_malformed_and_srht():
         srp.cca_solve_csr(to_dev(X), to_dev(Y), 2, 1e-3, 1e-3, 64,
                           options=srp.srp_default_options(sketch="srht"))
     assert ei.value.code == srp.SRP_EINVAL
+
+
+# rows enough for the products with the transpose to be summed from the rows
+# (no column copy, W and the class sums' subtraction in LDS); P of one and of
+# two tiles of columns
+@pytest.mark.parametrize("method,k", [("rcg", 4), ("rtr", 12)])
+def test_cca_solve_csr_many_rows(method, k):
+    srp = _srp()
+    n, dx, dy, lam = 70_000, 120, 90, 1e-3
+    X, Y = synth.cca_sparse(n, dx, dy, per_row=8, r=16, seed=4, dtype=np.float32)
+    Xd, Yd = dense(X), dense(Y)
+    sig_true, _, _ = direct.cca_direct(Xd, Yd, lam, lam)
+    opt = srp.srp_default_options(method=method, max_iter=2000)
+    U, V, sig, info = srp.cca_solve_csr(to_dev(X), to_dev(Y), k, lam, lam, 8 * dx, tol=1e-9, options=opt)
+    Uh, Vh = U.cpu().numpy(), V.cpu().numpy()
+    err = metrics.cca_rel_objective_error(Uh, Vh, Xd, Yd, lam, lam, sig_true)
+    cons = max(metrics.constraint_residual(Uh, Xd, lam), metrics.constraint_residual(Vh, Yd, lam))
+    print("cca csr rows", method, info, err, cons)
+    assert info["status"] == 0
+    assert err < 1e-10 and cons < 1e-11
+
+
+@pytest.mark.parametrize("method", ["rcg", "rtr"])
+def test_lda_solve_csr_many_rows(method):
+    srp = _srp()
+    n, d, c, k, lam = 70_000, 150, 8, 7, 1e-3
+    X, y = synth.lda_sparse(n, d, c, per_row=12, seed=6, dtype=np.float32)
+    Xd = dense(X)
+    rho_true, _ = direct.lda_direct(Xd, y, c, lam, k=k)
+    opt = srp.srp_default_options(method=method, max_iter=2000)
+    W, rho, info = srp.lda_solve_csr(to_dev(X), dev(y), c, k, lam, 8 * d, tol=1e-9, options=opt)
+    _, _, _, Xh, Yh = direct.lda_scatter(Xd, y, c)
+    Wh = W.cpu().numpy()
+    err = metrics.lda_rel_objective_error(Wh, Xh, Yh, lam, rho_true)
+    cons = metrics.constraint_residual(Wh, Xh, lam)
+    print("lda csr rows", method, info, err, cons)
+    assert info["status"] == 0
+    assert err < 1e-10 and cons < 1e-11
