@@ -1345,10 +1345,11 @@ __global__ void __launch_bounds__(kBfThreads) k_pass_bf(const unsigned short* __
 // The BF16 pass takes rows of whole dwords on 4-byte boundaries, views of at
 // least 113 columns (narrower ones keep the FP32 arithmetic of k_pass) and
 // at most 128 tiles of 16 columns, each view's count rounded up to even.
-static bool bf_rows_ok(const void* A0, const void* A1, int d0, int d1) {
-  if ((uintptr_t)A0 % 4 != 0 || d0 % 2 != 0 || (d0 + 15) / 16 < 8) return false;
-  return !A1 || ((uintptr_t)A1 % 4 == 0 && d1 % 2 == 0 && (d1 + 15) / 16 >= 8);
+static bool bf_widths_ok(int d0, int d1, int nb) {
+  auto ok = [](int d) { return d % 2 == 0 && (d + 15) / 16 >= 8; };
+  return ok(d0) && (nb == 1 || ok(d1));
 }
+static bool bf_aligned(const void* A0, const void* A1) { return (uintptr_t)A0 % 4 == 0 && (uintptr_t)A1 % 4 == 0; }
 
 static bool bf_fits(int d0, int d1, int k, int nb) {
   return k <= 16 && bf_geom(d0, nb == 2 ? d1 : 0).TTp <= kDmaMaxTiles;
@@ -1618,8 +1619,7 @@ const char* gram_pass_kernel_name(int dtype, int compute, int d0, int d1, int k)
   const bool al = d0 % 4 == 0 && (nb == 1 || d1 % 4 == 0);
   if (compute == SRP_BF16) {
     if (dtype != SRP_BF16) return nullptr;
-    const bool even = d0 % 2 == 0 && (nb == 1 || d1 % 2 == 0);
-    return even && bf_fits(d0, d1, k, nb) ? "k_pass_bf" : "k_pass";
+    return bf_widths_ok(d0, d1, nb) && bf_fits(d0, d1, k, nb) ? "k_pass_bf" : "k_pass";
   }
   if (compute == SRP_F32 && dtype == SRP_F32) {
     const int vec = (al && T0 >= 16 && (nb == 1 || T1 >= 16)) ? 4 : (T0 >= 4 && (nb == 1 || T1 >= 4)) ? 1 : 0;
@@ -1646,7 +1646,7 @@ int gram_pass_run(const void* A0, const void* A1, int dtype, int compute, int64_
       set_error("gram_pass: BF16 products need BF16 data");
       return SRP_EINVAL;
     }
-    if (bf_rows_ok(A0, A1, d0, d1) && bf_fits(d0, d1, k, nb))
+    if (bf_aligned(A0, A1) && bf_widths_ok(d0, d1, nb) && bf_fits(d0, d1, k, nb))
       return pass_dispatch_bf((const unsigned short*)A0, (const unsigned short*)A1, n, d0, d1, k, W0, W1, J0, J1,
                               done, ws, st, before_pass, after_pass);
     // views narrower than one 64-lane row chunk (or rows not 4-byte

@@ -117,3 +117,14 @@ def test_pass_kernel_choice_by_shape():
     assert q("f64", "f64", 300, 200, 8) == "k_pass"
     assert q("bf16", "bf16", 1000, 1000, 10) == "k_pass_bf"
     assert q("f32", "f32", 3000, 0, 4) is None                 # past the column limit
+
+
+def test_pass_kernel_choice_of_narrow_bf16_views():
+    """BF16 views under eight tiles of 16 columns keep the register-staged
+    pass, whatever the other view's width."""
+    srp = pytest.importorskip("paper_2106_12060_amd")
+    q = srp.srp_gram_pass_kernel
+    for d0, d1 in ((64, 64), (40, 0), (112, 0), (112, 500), (500, 112), (115, 0), (500, 131)):
+        assert q("bf16", "bf16", d0, d1, 4) == "k_pass", (d0, d1)
+    for d0, d1 in ((114, 0), (114, 114), (500, 114)):
+        assert q("bf16", "bf16", d0, d1, 4) == "k_pass_bf", (d0, d1)
