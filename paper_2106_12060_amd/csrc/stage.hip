@@ -131,19 +131,19 @@ __global__ void __launch_bounds__(256) k_col_amax(const T* __restrict__ X, int d
 
 // The column maxima from `parts` maxima of every position of a group (64
 // positions a workgroup, sixteen slices of the parts), and from the rows past
-// the last group, one workgroup past the positions.  Non-negative floats order
-// like their bit patterns, so an integer atomic maximum over a group's few rows
-// is exact whatever the order.
+// the last group, an element a thread in the workgroups past the positions.
+// Non-negative floats order like their bit patterns, so an integer atomic
+// maximum over a group's few rows is exact whatever the order.
 template <class T>
 __global__ void __launch_bounds__(1024) k_amax_parts(const T* __restrict__ X, int64_t n, int d, StageGeom g,
                                                      const float* __restrict__ part, int parts,
                                                      uint32_t* __restrict__ amax_bits) {
   __shared__ float q[16][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, count = 4 * g.runs;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, count = 4 * g.runs, wide = (count + 63) / 64;
   const int p = blockIdx.x * 64 + lane;
-  if ((int)blockIdx.x * 64 >= count) {
-    for (int64_t e = g.groups * g.M * d + threadIdx.x; e < n * d; e += 1024)
-      atomicMax(&amax_bits[e % d], __float_as_uint(fmaxf(0.f, fabsf(load_as<float>(X + e)))));
+  if ((int)blockIdx.x >= wide) {
+    const int64_t e = g.groups * g.M * d + ((int64_t)blockIdx.x - wide) * 1024 + threadIdx.x;
+    if (e < n * d) atomicMax(&amax_bits[e % d], __float_as_uint(fmaxf(0.f, fabsf(load_as<float>(X + e)))));
     return;
   }
   float m = 0.f;
@@ -160,6 +160,39 @@ __global__ void __launch_bounds__(1024) k_amax_parts(const T* __restrict__ X, in
 #pragma unroll
     for (int i = 1; i < 16; ++i) m = fmaxf(m, q[i][lane]);
     atomicMax(&amax_bits[p % d], __float_as_uint(m));
+  }
+}
+
+// The same from matrices wide enough to give every CU 64 columns: a column a
+// lane over all the rows there are of it, the parts' M rows (position p of a
+// group is column p mod d of its row p / d) and those past the last group.  No
+// atomics, and no workgroup for each of a group's 4 d positions (8 x 1000000:
+// 178 us a call, so 57; with the rows past the last group left to one
+// workgroup 7 x 1000000 took 1378, so 57).  By positions a width of 1000 has
+// four times the workgroups.
+template <class T>
+__global__ void __launch_bounds__(1024) k_amax_cols(const T* __restrict__ X, int64_t n, int d, StageGeom g,
+                                                    const float* __restrict__ part, int parts,
+                                                    uint32_t* __restrict__ amax_bits) {
+  __shared__ float q[16][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, W = blockDim.x >> 6;
+  const int64_t c = blockIdx.x * 64ll + lane, rows = (int64_t)parts * g.M;
+  float m = 0.f;
+  if (c < d) {
+    for (int64_t r = w; r < rows; r += 8 * W) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = r + u * W < rows ? part[(r + u * W) * d + c] : 0.f;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) m = fmaxf(m, v[u]);
+    }
+    for (int64_t r = g.groups * g.M + w; r < n; r += W) m = fmaxf(m, fabsf(load_as<float>(X + r * d + c)));
+  }
+  q[w][lane] = m;
+  __syncthreads();
+  if (w == 0 && c < d) {
+    for (int i = 1; i < W; ++i) m = fmaxf(m, q[i][lane]);
+    amax_bits[c] = __float_as_uint(m);
   }
 }
 
@@ -276,14 +309,22 @@ static int stage_fp8_t(const T* X, int64_t n, int d, uint8_t* out, double* scale
   float* inv = ws.take<float>(d);
   float* part = ws.take<float>(stage_parts(d));
   if (!amax || !inv || !part) { set_error("stage_fp8: workspace too small"); return SRP_ENOMEM; }
-  SRP_TRY(fill_i32((int*)amax, d, 0, st));
   const StageGeom g = stage_geom(n, d);
-  if (g.groups > 0) {
+  const int parts = g.groups > 0 ? (int)g.grid.y : 0;
+  if (parts > 0) {
     hipLaunchKernelGGL((k_col_amax<T>), g.grid, dim3(256), 0, st, X, d, g, part);
     SRP_LAUNCH_CHECK();
   }
-  hipLaunchKernelGGL((k_amax_parts<T>), dim3((4 * g.runs + 63) / 64 + 1), dim3(1024), 0, st, X, n, d, g, part,
-                     g.groups > 0 ? (int)g.grid.y : 0, amax);
+  if (d >= 64 * num_cus()) {
+    const int W = std::min(16, std::max(1, parts * g.M / 4));
+    hipLaunchKernelGGL((k_amax_cols<T>), dim3((unsigned)(((int64_t)d + 63) / 64)), dim3(64 * W), 0, st, X, n, d, g,
+                       part, parts, amax);
+  } else {
+    SRP_TRY(fill_i32((int*)amax, d, 0, st));
+    const int64_t rest = n * d - g.groups * g.M * d;
+    hipLaunchKernelGGL((k_amax_parts<T>), dim3((unsigned)((4 * g.runs + 63) / 64 + (rest + 1023) / 1024)), dim3(1024),
+                       0, st, X, n, d, g, part, parts, amax);
+  }
   SRP_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_fp8_scales, dim3((d + 255) / 256), dim3(256), 0, st, amax, d, scales, inv);
   SRP_LAUNCH_CHECK();

@@ -354,3 +354,41 @@ def test_gram_pass_block_edges_exact(n, d0, d1, k, off):
     out = srp.srp_gram_pass(D[0], Wd[0], *((D[1], Wd[1]) if d1 else ()))
     for g, a in zip(out, A):
         np.testing.assert_array_equal(g.cpu().numpy(), a.T.astype(np.float64) @ P)
+
+
+def call_us(f):
+    """Fastest of twenty calls (each waits for its work), in us."""
+    import time
+    f()
+    best = float("inf")
+    for _ in range(20):
+        t = time.perf_counter()
+        f()
+        best = min(best, time.perf_counter() - t)
+    return 1e6 * best
+
+
+# fewer rows than a group and a remainder of rows on either side of the width
+# (64 columns a CU) from which a column's maximum is taken by one lane
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("n,d", [(3, 16383), (7, 16383), (3, 16384), (7, 16389), (66, 16384), (1, 100003), (5, 100003)])
+def test_fp8_staging_of_wide_rows(n, d, dt):
+    srp = _srp()
+    X = torch.from_numpy(np.random.default_rng(n * d).standard_normal((n, d), dtype=np.float32))
+    X[-1, ::3] *= 1000.0   # the maximum of these columns lies in the last row
+    X = X.to(torch.bfloat16 if dt == "bf16" else torch.float32)
+    codes, scales = srp.srp_stage_fp8(X.to(DEV))
+    ref, sc = quant.fp8_stage(X.double().numpy() if dt == "bf16" else X.numpy())
+    np.testing.assert_array_equal(scales.cpu().numpy(), sc)
+    np.testing.assert_array_equal(codes.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("n", [7, 8])
+def test_fp8_staging_of_wide_rows_costs_no_more(n):
+    """A few wide rows, with and without a remainder past the last group,
+    against as many elements in rows of 1000: scales and codes are as many
+    bytes again, and the calls' fixed cost is most of either."""
+    srp = _srp()
+    X = torch.randn(8_000_000, device=DEV)
+    wide, tall = X[:n * 1_000_000].view(n, -1), X[:n * 1_000_000].view(-1, 1000)
+    assert call_us(lambda: srp.srp_stage_fp8(wide)) < 2.5 * call_us(lambda: srp.srp_stage_fp8(tall))
