@@ -150,7 +150,7 @@ int srp_stage_fp8(const void* X, int dtype, int64_t n, int d, uint8_t* out, doub
   SRP_REQUIRE(dtype == SRP_F32 || dtype == SRP_BF16, "stage_fp8: data must be F32 or BF16");
   hipStream_t st = (hipStream_t)stream;
   Scratch ws(st);
-  const size_t bytes = stage_fp8_ws_bytes(d) + 1024;
+  const size_t bytes = stage_fp8_ws_bytes(n, d) + 1024;
   SRP_TRY(device_alloc(&ws.p, bytes, st));
   Arena ar{(char*)ws.p, bytes, 0};
   SRP_TRY(stage_fp8_run(X, dtype, n, d, out, scales, ar, st));

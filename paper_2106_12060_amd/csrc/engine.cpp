@@ -116,7 +116,8 @@ size_t footprint(const srp_request& q) {
   if (q.stage == SRP_STAGE_BF16_FP8) skin = SRP_FP8E4M3;
   else if (q.stage == SRP_STAGE_NONE && q.opt.sketch_x) skin = q.opt.sketch_dtype;
   size_t ws = cca_ws_bytes(q.n, q.dx, q.dy, q.k, q.sketch_size, q.dtype, q.opt.sketch, skin);
-  if (q.stage == SRP_STAGE_BF16_FP8) ws = std::max(ws, stage_fp8_ws_bytes(std::max(q.dx, q.dy)));
+  if (q.stage == SRP_STAGE_BF16_FP8)
+    ws = std::max({ws, stage_fp8_ws_bytes(q.n, q.dx), stage_fp8_ws_bytes(q.n, q.dy)});
   return staged_bytes(q) + ws;
 }
 

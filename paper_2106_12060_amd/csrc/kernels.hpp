@@ -180,7 +180,7 @@ int fda_csr_stats_run(const CscView& A, int64_t n, int c, const int32_t* labels,
 
 // --------------------------------------------------------- staging
 int stage_bf16_run(const float* X, int64_t n, int d, uint16_t* out, hipStream_t st);
-size_t stage_fp8_ws_bytes(int d);
+size_t stage_fp8_ws_bytes(int64_t n, int d);
 int stage_fp8_run(const void* X, int dtype, int64_t n, int d, uint8_t* out, double* scales, Arena& ws,
                   hipStream_t st);
 // A (rows x d, FP32) column j times scales[j] (powers of two: exact).

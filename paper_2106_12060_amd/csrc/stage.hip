@@ -292,24 +292,20 @@ int stage_bf16_run(const float* X, int64_t n, int d, uint16_t* out, hipStream_t 
   return SRP_OK;
 }
 
-// The maxima of a group's positions: at most max(4 num_cus, workgroups a
-// group is wide) workgroups of 1024.
-static size_t stage_parts(int d) {
-  const int64_t wide = (4ll * ((256 + (int64_t)d - 1) / d) * d / 4 + 255) / 256;
-  return (size_t)std::max<int64_t>(4ll * num_cus(), wide) * 1024;
-}
+// The maxima of a group's positions, a set from every row of workgroups.
+static size_t stage_parts(const StageGeom& g) { return g.groups > 0 ? (size_t)g.grid.y * 4 * g.runs : 0; }
 
-size_t stage_fp8_ws_bytes(int d) {
-  return bytes_of<uint32_t>(d) + bytes_of<float>(d) + bytes_of<float>(stage_parts(d));
+size_t stage_fp8_ws_bytes(int64_t n, int d) {
+  return bytes_of<uint32_t>(d) + bytes_of<float>(d) + bytes_of<float>(stage_parts(stage_geom(n, d)));
 }
 
 template <class T>
 static int stage_fp8_t(const T* X, int64_t n, int d, uint8_t* out, double* scales, Arena& ws, hipStream_t st) {
   uint32_t* amax = ws.take<uint32_t>(d);
   float* inv = ws.take<float>(d);
-  float* part = ws.take<float>(stage_parts(d));
-  if (!amax || !inv || !part) { set_error("stage_fp8: workspace too small"); return SRP_ENOMEM; }
   const StageGeom g = stage_geom(n, d);
+  float* part = ws.take<float>(stage_parts(g));
+  if (!amax || !inv || !part) { set_error("stage_fp8: workspace too small"); return SRP_ENOMEM; }
   const int parts = g.groups > 0 ? (int)g.grid.y : 0;
   if (parts > 0) {
     hipLaunchKernelGGL((k_col_amax<T>), g.grid, dim3(256), 0, st, X, d, g, part);

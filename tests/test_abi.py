@@ -128,3 +128,24 @@ def test_pass_kernel_choice_of_narrow_bf16_views():
         assert q("bf16", "bf16", d0, d1, 4) == "k_pass", (d0, d1)
     for d0, d1 in ((114, 0), (114, 114), (500, 114)):
         assert q("bf16", "bf16", d0, d1, 4) == "k_pass_bf", (d0, d1)
+
+
+def test_request_footprint_of_small_fp8_staging():
+    """The scratch of the FP8 staging follows the matrix: a small request
+    needs its staged copies more than the BF16 stage of it, as a large one."""
+    import paper_2106_12060_amd as srp
+    from paper_2106_12060_amd import _lib
+    L = srp.lib()
+    def al(b):
+        return (b + 255) // 256 * 256
+    for n, dx, dy, k, s in ((64, 16, 16, 2, 32), (500, 60, 40, 3, 240), (5000, 300, 200, 4, 1200)):
+        req = _lib.SrpRequest()
+        req.problem, req.n, req.dx, req.dy, req.k, req.sketch_size = srp.SRP_PROBLEM_CCA, n, dx, dy, k, s
+        req.lambda_x = req.lambda_y = 1e-3
+        req.dtype = srp.SRP_F32
+        L.srp_default_options(ctypes.byref(req.opt))
+        req.stage = srp.SRP_STAGE_BF16
+        f1 = L.srp_request_footprint(ctypes.byref(req))
+        req.stage = srp.SRP_STAGE_BF16_FP8
+        f2 = L.srp_request_footprint(ctypes.byref(req))
+        assert f2 == f1 + al(n * dx) + al(n * dy) + al(8 * dx) + al(8 * dy), (n, dx, dy)
