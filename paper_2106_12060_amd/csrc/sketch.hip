@@ -14,7 +14,8 @@
 // of B consecutive rows (in LDS), and level 2 forms each sampled output row
 // as a +-sum over the blocks of level-1 row beta.  Only the s sampled rows
 // are ever formed.  The row sample (s smallest SplitMix64 keys) is found by
-// a 4-round 16-bit radix select and an order-preserving compaction.
+// ranking the keys around the expected threshold and an order-preserving
+// compaction.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -290,17 +291,25 @@ int countsketch_run(const void* A, int dtype, int64_t n, int d, int s, uint64_t 
 // most `T`, the s-th smallest of the n' keys.  The keys are a hash, so the s-th
 // smallest lies within a few standard deviations of s / n' of their range: the
 // keys in a window of six on either side are listed and ranked, those below
-// it counted.  Where the window misses (or a list is full) one workgroup selects
-// over all keys by 8-bit digits: the same threshold, only later.
+// it counted.  The window misses by chance (three samples in 10^7 of one row,
+// fewer of more; that a list does not fit is rarer yet): then one workgroup
+// selects over all keys by 8-bit digits, the same threshold later.  The row
+// sample of 2^19 from 2^20: 60 us a call; with room for half of such a window's
+// keys that selection ran every time and took 1545, a radix select by 16-bit
+// digits over the whole card 149.
 struct SelectState {
   uint64_t T;
 };
 constexpr int kSelChunk = 1024;
-constexpr int kSelList = 32768;   // keys of all chunks' lists
-constexpr int kSelRank = 3072;    // keys ranked
+constexpr int kSelList = 32768;   // keys of all chunks' lists (a power of two, as are the chunks)
+// Keys ranked: the window's 12 sqrt(s (1 - s / n')) + 16 are 6160 at most
+// (n' = 2^20, half of it), and its own deviation is 78.
+constexpr int kSelRank = 7168;
+constexpr int kSelFew = 256;      // keys of one of the rank's bins, 14 on average at most
 
-// Keys a chunk may list.
-static int sel_cap(int chunks) { return std::min(128, kSelList / chunks); }
+// Keys a chunk may list: all of them up to 32 chunks; 32 at 2^20, where a chunk
+// has at most six on average.
+static int sel_cap(int chunks) { return std::min(kSelChunk, kSelList / chunks); }
 
 // Chunk `blockIdx.x`: keys under lo counted, those in [lo, hi] listed.
 __global__ void __launch_bounds__(256) k_sel_window(int64_t n_pad, uint64_t seed, uint64_t lo, uint64_t hi, int cap,
@@ -331,27 +340,42 @@ __global__ void __launch_bounds__(256) k_sel_window(int64_t n_pad, uint64_t seed
   }
 }
 
-// T from the chunks' counts and lists (at most 1024 chunks, one a thread).
+// T from the chunks' counts and lists.
 __global__ void __launch_bounds__(1024) k_sel_rank(int64_t n_pad, uint64_t seed, int s, uint64_t lo, uint64_t hi, int chunks, int cap,
                                                    const int* __restrict__ below, const int* __restrict__ inside,
                                                    const uint64_t* __restrict__ list, SelectState* __restrict__ st) {
-  __shared__ uint64_t keys[kSelRank], few[kSelRank];
+  __shared__ uint64_t keys[kSelRank], few[kSelFew];
   __shared__ int hist[256], bins[1024];
   __shared__ int total, low, bad, digit, before;
   const int t = threadIdx.x;
-  if (t == 0) total = low = bad = 0;
+  if (t == 0) {
+    total = low = 0;
+    bad = chunks > 1024;   // a chunk a thread below
+  }
   __syncthreads();
+  // where a chunk's keys go and how many they are, in a word
   if (t < chunks) {
-    const int m = inside[t];
+    int m = inside[t];
     atomicAdd(&low, below[t]);
-    if (m > cap) bad = 1;
     const int at = atomicAdd(&total, m);
-    if (m <= cap && at + m <= kSelRank)
-      for (int i = 0; i < m; ++i) keys[at + i] = list[(int64_t)t * cap + i];
+    if (m > cap || at + m > kSelRank) {
+      bad = 1;
+      m = 0;
+    }
+    bins[t] = m << 16 | (at & 0xFFFF);
+  }
+  __syncthreads();
+  if (!bad) {
+    const int shift = 31 - __clz(cap), slots = chunks * cap;
+#pragma unroll 8
+    for (int e = t; e < slots; e += 1024) {
+      const int at = bins[e >> shift], i = e & (cap - 1);
+      if (i < at >> 16) keys[(at & 0xFFFF) + i] = list[e];
+    }
   }
   __syncthreads();
   const int W = total, need = s - low;
-  if (!bad && W <= kSelRank && need >= 1 && need <= W) {
+  if (!bad && need >= 1 && need <= W) {
     // the bin of the window (one a thread) that holds the need-th key, then
     // the rank among that bin's few (every key against all of a list of a
     // thousand: 27 us, the reads of LDS)
@@ -379,16 +403,21 @@ __global__ void __launch_bounds__(1024) k_sel_rank(int64_t n_pad, uint64_t seed,
     __syncthreads();
     const int target = digit;
     for (int e = t; e < W; e += 1024)
-      if (bin_of(keys[e]) == target) few[atomicAdd(&total, 1)] = keys[e];
+      if (bin_of(keys[e]) == target) {
+        const int i = atomicAdd(&total, 1);
+        if (i < kSelFew) few[i] = keys[e];
+      }
     __syncthreads();
     const int m = total;
-    for (int e = t; e < m; e += 1024) {
-      const uint64_t k = few[e];
-      int r = before;
-      for (int i = 0; i < m; ++i) r += few[i] < k;
-      if (r == need - 1) st->T = k;   // the keys are distinct
+    if (m <= kSelFew) {
+      if (t < m) {
+        const uint64_t k = few[t];
+        int r = before;
+        for (int i = 0; i < m; ++i) r += few[i] < k;
+        if (r == need - 1) st->T = k;   // the keys are distinct
+      }
+      return;
     }
-    return;
   }
   uint64_t prefix = 0;
   int left = s;

@@ -392,3 +392,24 @@ def test_fp8_staging_of_wide_rows_costs_no_more(n):
     X = torch.randn(8_000_000, device=DEV)
     wide, tall = X[:n * 1_000_000].view(n, -1), X[:n * 1_000_000].view(-1, 1000)
     assert call_us(lambda: srp.srp_stage_fp8(wide)) < 2.5 * call_us(lambda: srp.srp_stage_fp8(tall))
+
+
+# the largest windows (half of the rows), chunks whose whole keys are listed;
+# and seeds for which the smallest of 1024 keys lies past the window (found by
+# searching), where the selection over all keys runs
+@pytest.mark.parametrize("n,s,seed", [(1 << 20, 1 << 19, 3), (1 << 20, 131072, 4), (1 << 19, 262144, 5), (262144, 131072, 6),
+                                      (1024, 512, 7), (2048, 1500, 8), (32768, 16384, 9), (65536, 32768, 10),
+                                      (1024, 1, 4990599), (1000, 1, 6866827)])
+def test_srht_row_sample_windows(n, s, seed):
+    from oracle import sketch as osk
+    srp = _srp()
+    rows = srp.srp_srht_rows(n, s, seed).cpu().numpy()
+    np.testing.assert_array_equal(rows, osk.srht_rows(osk.srht_padded_rows(n), s, seed))
+
+
+def test_srht_row_sample_of_many_rows_costs_no_more():
+    """Half of 2^20 rows: 125 times the rows written, and the keys read as
+    often as for 4000 of them; either call is a few launches."""
+    srp = _srp()
+    many, few = (call_us(lambda: srp.srp_srht_rows(1 << 20, s, 5)) for s in (1 << 19, 4000))
+    assert many < 4 * few
