@@ -413,3 +413,42 @@ def test_srht_row_sample_of_many_rows_costs_no_more():
     srp = _srp()
     many, few = (call_us(lambda: srp.srp_srht_rows(1 << 20, s, 5)) for s in (1 << 19, 4000))
     assert many < 4 * few
+
+
+def csr_rows(n, d, per_row, bad=None):
+    """n rows of per_row entries, column c in [c d / per_row, (c + 1) d / per_row); `bad` replaces the last index."""
+    lo = (torch.arange(per_row, device=DEV) * d) // per_row
+    width = torch.diff(torch.cat([lo, torch.tensor([d], device=DEV)]))
+    idx = (lo + (torch.rand((n, per_row), device=DEV) * width).long().clamp(max=width - 1)).to(torch.int32).reshape(-1)
+    if bad is not None:
+        idx[-1] = bad
+    vals = torch.randint(1, 4, (n * per_row,), device=DEV).to(torch.float32)
+    return _srp().Csr(torch.arange(n + 1, device=DEV, dtype=torch.int64) * per_row, idx, vals, d)
+
+
+def test_csr_structure_check_of_long_rows_costs_no_more():
+    """As many entries in a few long rows as in many short ones; a bad last
+    index ends the call after the check."""
+    srp = _srp()
+    def refused(A):
+        with pytest.raises(srp.SrpError):
+            srp.srp_countsketch_csr(A, 64, 1)
+    few, many = csr_rows(1000, 8000, 4000, bad=-1), csr_rows(40000, 8000, 100, bad=8000)
+    assert call_us(lambda: refused(few)) < 2 * call_us(lambda: refused(many))
+
+
+# a row that ends at, one before and one after a whole step of the long rows' loop
+@pytest.mark.parametrize("length", [15, 16, 17, 112, 113, 127, 128, 129, 241, 700])
+def test_csr_structure_faults_in_a_long_row(length):
+    srp = _srp()
+    n, d = 9, 800
+    cols = np.tile(np.arange(length, dtype=np.int32), n)
+    ptr = np.arange(0, n * length + 1, length, dtype=np.int64)
+    mk = lambda c: srp.Csr(torch.from_numpy(ptr).to(DEV), torch.from_numpy(c).to(DEV), torch.ones(n * length, device=DEV), d)
+    srp.srp_countsketch_csr(mk(cols), 8, 1)
+    for at in sorted({0, 1, 15, 16, length // 2, length - 2, length - 1} & set(range(length))):
+        for value in {-1, d, cols[at - 1] if at else -7}:
+            bad = cols.copy()
+            bad[4 * length + at] = value
+            with pytest.raises(srp.SrpError):
+                srp.srp_countsketch_csr(mk(bad), 8, 1)
