@@ -67,8 +67,8 @@ __global__ void __launch_bounds__(256) k_csr_check(int64_t n, int d, int64_t nnz
 
 // A malformed matrix sets `bit` in *bad.  A wave takes up to 64 rows, as many
 // as have some 1400 entries together, and no more than leave four waves to
-// every SIMD (1000 rows of 4000 entries with 64 rows a wave: 16 waves in
-// serial loads, 680 us; so: 22).
+// every SIMD (a CountSketch of 1000 rows of 4000 entries with 64 rows a wave,
+// 16 waves in serial loads: 1430 us a call; so 207).
 int csr_validate(const CsrView& A, int bit, int* bad, hipStream_t st) {
   const int64_t by_entries = 352 * A.n / std::max<int64_t>(1, A.nnz), by_rows = A.n / (64ll * num_cus());
   const int rows = 4 * (int)std::min<int64_t>(16, std::max<int64_t>(1, std::min(by_entries, by_rows)));
@@ -704,24 +704,28 @@ __global__ void __launch_bounds__(256) k_csr_tsum_add(const double* __restrict__
 
 // P columns of a column group: sixteen at most.
 static int ts_lanes(int w) { return w <= 4 ? 4 : w <= 8 ? 8 : 16; }
-// Row ranges: two workgroups a CU, at least one block of rows each.
-static int ts_ranges(const CsrView& A) {
-  return (int)std::min<int64_t>(2ll * num_cus(), std::max<int64_t>(1, (A.n + kTsRows - 1) / kTsRows));
+// Row ranges: two workgroups a CU over all column tiles of P (a range's sums
+// are d x 16 doubles of workspace a tile), at least one block of rows or
+// entries each (1000 rows of 1000 entries, two matrices, 16 columns of P: in 8
+// ranges, a block of rows each, 3406 us a call; in 244 522).
+static int ts_ranges(const CsrView& A, int tiles) {
+  const int64_t blocks = std::max((A.n + kTsRows - 1) / kTsRows, A.nnz / kTsEntries);
+  return (int)std::min(std::max<int64_t>(1, 2ll * num_cus() / tiles), std::max<int64_t>(1, blocks));
 }
 
 bool csr_tsum_ok(const CsrView& A, int w) { return w >= 1 && A.d <= kTsMaxCols; }
 
 size_t csr_tsum_bytes(const CsrView& A, int w) {
   const int GL = ts_lanes(w), tiles = (w + GL - 1) / GL;
-  return bytes_of<double>((size_t)tiles * ts_ranges(A) * A.d * GL);
+  return bytes_of<double>((size_t)tiles * ts_ranges(A, tiles) * A.d * GL);
 }
 
 template <class T, int L>
 static int tsum_launch(const CsrView& A, const double* P, int ldp, int w, double* partial, const int* done,
                        hipStream_t st) {
   constexpr int GL = 2 * L;
-  const int G = ts_ranges(A);
-  const dim3 grid((unsigned)G, (unsigned)((w + GL - 1) / GL));
+  const int tiles = (w + GL - 1) / GL, G = ts_ranges(A, tiles);
+  const dim3 grid((unsigned)G, (unsigned)tiles);
   const size_t lds = ts_lds<T>(A.d, GL);
   const int nc = (A.d + kTsThreads / L - 1) / (kTsThreads / L);   // columns of A per group
 #define SRP_TS_CASE(NC_)                                                                                            \
@@ -756,9 +760,9 @@ int csr_tsum(const CsrView& A, const double* P, int ldp, int w, double* out, int
   SRP_REQUIRE(csr_tsum_ok(A, w), "sparse product width %d, %d columns", w, A.d);
   if (A.dtype == SRP_F64) SRP_TRY(tsum_dispatch<double>(A, P, ldp, w, partial, done, st));
   else SRP_TRY(tsum_dispatch<float>(A, P, ldp, w, partial, done, st));
-  const int GL = ts_lanes(w);
-  const dim3 grid((unsigned)(((int64_t)A.d * GL + 63) / 64), (unsigned)((w + GL - 1) / GL));
-  hipLaunchKernelGGL(k_csr_tsum_add, grid, dim3(256), 0, st, partial, ts_ranges(A), GL, A.d, w, out, ldo, done);
+  const int GL = ts_lanes(w), tiles = (w + GL - 1) / GL;
+  const dim3 grid((unsigned)(((int64_t)A.d * GL + 63) / 64), (unsigned)tiles);
+  hipLaunchKernelGGL(k_csr_tsum_add, grid, dim3(256), 0, st, partial, ts_ranges(A, tiles), GL, A.d, w, out, ldo, done);
   SRP_LAUNCH_CHECK();
   return SRP_OK;
 }

@@ -452,3 +452,12 @@ def test_csr_structure_faults_in_a_long_row(length):
             bad[4 * length + at] = value
             with pytest.raises(srp.SrpError):
                 srp.srp_countsketch_csr(mk(bad), 8, 1)
+
+
+def test_csr_products_of_few_long_rows_cost_no_more():
+    """A million entries in 1000 rows against the same number in 50000: the
+    row ranges follow the entries, not the rows alone."""
+    srp = _srp()
+    W = torch.ones((2000, 8), dtype=torch.float64, device=DEV)
+    few, many = csr_rows(1000, 2000, 1000), csr_rows(50000, 2000, 20)
+    assert call_us(lambda: srp.srp_gram_pass_csr(few, W, few, W)) < 2.5 * call_us(lambda: srp.srp_gram_pass_csr(many, W, many, W))
