@@ -325,9 +325,10 @@ int lda_solve(const void* X, const int32_t* labels, int64_t n, int d,
  * nnz < 2^31.  Every entry point checks the structure on the device first
  * and returns SRP_EINVAL for a malformed matrix.  All arithmetic on the
  * data is FP64 (the F32 values are widened).  The products A^T P
- * are summed from the rows; where that does not pay (more than 2048 columns,
- * or a solve on few rows) from a column-major copy (nnz index and value
- * words, from the library's workspace).
+ * are summed from the rows (workspace: the sums of 512 ranges of rows, up to
+ * 16 columns of P each); where that does not pay (more than 2048 columns, few
+ * entries for many columns, or a solve on few rows) from a column-major copy
+ * (nnz index and value words, from the library's workspace).
  */
 typedef struct srp_csr {
   int64_t n_rows;

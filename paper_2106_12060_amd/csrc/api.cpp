@@ -249,9 +249,11 @@ int srp_gram_pass_csr(const srp_csr* A0, const srp_csr* A1, int k, const double*
   Scratch ws(st);
   size_t bytes = bytes_of<int>(4) + bytes_of<double>((size_t)std::max<int64_t>(v[0].n, 1) * ldp) + 2048;
   size_t scr = 0;
+  bool rows[2] = {false, false};
   for (int b = 0; b < nb; ++b) {
     SRP_REQUIRE(v[b].n >= 1 && v[b].d >= 1, "bad sizes");
-    if (csr_tsum_ok(v[b], ldp)) {
+    rows[b] = csr_rows_pay(v[b], ldp, 1, false);
+    if (rows[b]) {
       bytes += csr_tsum_bytes(v[b], ldp);
       continue;
     }
@@ -270,10 +272,9 @@ int srp_gram_pass_csr(const srp_csr* A0, const srp_csr* A1, int k, const double*
   ar.used += (scr + 255) & ~size_t(255);
   double* part[2] = {nullptr, nullptr};
   for (int b = 0; b < nb; ++b) {
-    const bool rows = csr_tsum_ok(v[b], ldp);
     Arena t{sbase, scr, 0};
-    if (!rows) SRP_TRY(csc_build(v[b], &c[b], ar, t, st));
-    part[b] = (double*)ar.take<char>(rows ? csr_tsum_bytes(v[b], ldp) : csc_partial_bytes(v[b], ldp));
+    if (!rows[b]) SRP_TRY(csc_build(v[b], &c[b], ar, t, st));
+    part[b] = (double*)ar.take<char>(rows[b] ? csr_tsum_bytes(v[b], ldp) : csc_partial_bytes(v[b], ldp));
     if (!part[b]) { set_error("workspace layout overflow"); return SRP_ENOMEM; }
   }
   const double* Wb[2] = {W0, W1};
@@ -281,7 +282,7 @@ int srp_gram_pass_csr(const srp_csr* A0, const srp_csr* A1, int k, const double*
   for (int b = 0; b < nb; ++b)
     SRP_TRY(csr_times_dense(v[b], Wb[b], k, k, P + b * k, ldp, nullptr, nullptr, nullptr, st));
   for (int b = 0; b < nb; ++b) {
-    if (csr_tsum_ok(v[b], ldp)) SRP_TRY(csr_tsum(v[b], P, ldp, ldp, Jb[b], ldp, part[b], nullptr, st));
+    if (rows[b]) SRP_TRY(csr_tsum(v[b], P, ldp, ldp, Jb[b], ldp, part[b], nullptr, st));
     else SRP_TRY(csc_times_dense(c[b], P, ldp, ldp, Jb[b], ldp, part[b], nullptr, st));
   }
   return finish(ws);

@@ -268,13 +268,14 @@ struct SparseData {
   double* partial[2] = {nullptr, nullptr};   // partials of A_b^T P
 };
 
-// Whether a solve takes A^T P (w columns of P) from the rows.  With 1M rows
-// of 22 entries that is 360 us a pass against 528 from the column copy and
-// spares the 1.2 ms that building the copy takes; with 20000 rows, too few
-// blocks to fill the card, the copy's passes are as fast (a trust-region
-// solve of 717 passes: 169-177 ms, 174 from the rows) and it is kept below
-// two blocks' rows a CU.
-static bool rows_pay(const CsrView& A, int w) { return csr_tsum_ok(A, w) && A.n >= 2ll * num_cus() * 128; }
+// Whether a solve takes A^T P (w columns of P) from the rows: by the cost of
+// the hundred products or so that it forms (FDA has the column copy for the
+// class statistics anyway).  With 20000 rows, too few blocks to fill the card,
+// the copy's passes are as fast in a solve (a trust-region solve of 717 passes:
+// 169-177 ms, 174 from the rows) and it is kept below two blocks' rows a CU.
+static bool rows_pay(const CsrView& A, int w, bool copy_there) {
+  return A.n >= 2ll * num_cus() * 128 && csr_rows_pay(A, w, 100, copy_there);
+}
 
 struct RcgBuffers {
   double *U[2], *Ks[2], *Kc[2], *xi[2], *gold[2], *J[2], *Jc[2], *Z[2], *Wz[2];
@@ -470,8 +471,8 @@ static int twopass_f64(const RcgProblem& P, RcgBuffers& B, double* const* W, hip
 }
 
 // Products of CSR data, FP64: P_b = A_b W_b (n x k each, side by side in
-// B.Pn), then J_b = A_b^T [P_0 | P_1], from the rows too where csr_tsum
-// takes the width, else from the CSC copies.  FDA: the rows
+// B.Pn), then J_b = A_b^T [P_0 | P_1], from the rows too where that pays
+// (rows_pay), else from the CSC copies.  FDA: the rows
 // of Xhat = X - E C (E the one-hot labels, C the class means) give
 // Xhat W = X W - (C W)[labels] per row, and Xhat^T (Xhat W) = X^T (Xhat W)
 // because the class sums of the rows of Xhat vanish (E^T Xhat = 0): the
@@ -488,8 +489,10 @@ static int sparse_pass(const RcgProblem& P, RcgBuffers& B, double* const* W, con
     SRP_TRY(csr_times_dense(S.csr[b], W[b], k, k, B.Pn + b * k, ldp, sub, S.labels, done, st));
   }
   for (int b = 0; b < nb; ++b) {
-    if (rows_pay(S.csr[b], ldp)) SRP_TRY(csr_tsum(S.csr[b], B.Pn, ldp, ldp, B.J[b], ldp, S.partial[b], done, st));
-    else SRP_TRY(csc_times_dense(S.csc[b], B.Pn, ldp, ldp, B.J[b], ldp, S.partial[b], done, st));
+    if (rows_pay(S.csr[b], ldp, S.labels != nullptr))
+      SRP_TRY(csr_tsum(S.csr[b], B.Pn, ldp, ldp, B.J[b], ldp, S.partial[b], done, st));
+    else
+      SRP_TRY(csc_times_dense(S.csc[b], B.Pn, ldp, ldp, B.J[b], ldp, S.partial[b], done, st));
   }
   return SRP_OK;
 }
@@ -2068,8 +2071,8 @@ static int csr_common_checks(const srp_options& opt) {
 }
 
 // Bytes of the partials of A^T P for w columns of P (sparse_pass).
-static size_t csr_partial_bytes(const CsrView& A, int w) {
-  return rows_pay(A, w) ? csr_tsum_bytes(A, w) : csc_partial_bytes(A, w);
+static size_t csr_partial_bytes(const CsrView& A, int w, bool copy_there) {
+  return rows_pay(A, w, copy_there) ? csr_tsum_bytes(A, w) : csc_partial_bytes(A, w);
 }
 
 static size_t csr_scratch(const CsrView* A, int nv, int s, int k, int c) {
@@ -2091,7 +2094,7 @@ size_t cca_csr_ws_bytes(const CsrView& X, const CsrView& Y, int k, int s) {
   size_t b = bytes_of<double>((size_t)s * dx) + bytes_of<double>((size_t)s * dy);
   b += 2 * bytes_of<double>((size_t)dx * dx) + 2 * bytes_of<double>((size_t)dy * dy);   // R, M^-1
   b += 2 * bytes_of<double>((size_t)dm * dm) + bytes_of<int>(4) + bytes_of<double>((size_t)dx * dy);
-  for (const CsrView& A : v) b += (rows_pay(A, 2 * k) ? 0 : csc_bytes(A)) + csr_partial_bytes(A, 2 * k);
+  for (const CsrView& A : v) b += (rows_pay(A, 2 * k, false) ? 0 : csc_bytes(A)) + csr_partial_bytes(A, 2 * k, false);
   b += rcg_buffers_bytes(2, k, std::max<int64_t>(X.n, s), dd, SRP_F64);
   for (int q = 0; q < 2; ++q)
     if (s < dd[q]) b += woodbury_keep_bytes(s, dd[q]);
@@ -2103,7 +2106,7 @@ size_t lda_csr_ws_bytes(const CsrView& X, int c, int k, int s) {
   const int dd[2] = {d, 0};
   size_t b = bytes_of<double>((size_t)s * d) + bytes_of<double>((size_t)s * c);
   b += 3 * bytes_of<double>((size_t)d * d) + 3 * bytes_of<double>((size_t)c * d) + bytes_of<double>((size_t)c * k);
-  b += bytes_of<int>(c) + bytes_of<int>(4) + csc_bytes(X) + csr_partial_bytes(X, k);
+  b += bytes_of<int>(c) + bytes_of<int>(4) + csc_bytes(X) + csr_partial_bytes(X, k, true);
   b += rcg_buffers_bytes(1, k, std::max<int64_t>(X.n, s), dd, SRP_F64, c);
   if (s < d) b += woodbury_keep_bytes(s, d);
   return b + csr_scratch(&X, 1, s, k, c) + 4096;
@@ -2182,8 +2185,8 @@ int cca_solve_csr_impl(const CsrView& X, const CsrView& Y, int k, double lx, dou
   // steps share one scratch area in stream order
   for (int b = 0; b < 2; ++b) {
     Arena t{scratch_base, scr, 0};
-    if (!rows_pay(views[b], 2 * k)) SRP_TRY(csc_build(views[b], &sd.csc[b], keep, t, st));
-    sd.partial[b] = (double*)keep.take<char>(csr_partial_bytes(views[b], 2 * k));
+    if (!rows_pay(views[b], 2 * k, false)) SRP_TRY(csc_build(views[b], &sd.csc[b], keep, t, st));
+    sd.partial[b] = (double*)keep.take<char>(csr_partial_bytes(views[b], 2 * k, false));
   }
   if (!sd.partial[1]) { set_error("workspace layout overflow"); return SRP_ENOMEM; }
   SRP_TRY(fill_i32(flag, 1, 0, st));
@@ -2323,7 +2326,7 @@ int lda_solve_csr_impl(const CsrView& X, const int32_t* labels, int c, int k, do
   {
     Arena t{scratch_base, scr, 0};
     SRP_TRY(csc_build(X, &sd.csc[0], keep, t, st));
-    sd.partial[0] = (double*)keep.take<char>(csr_partial_bytes(X, k));
+    sd.partial[0] = (double*)keep.take<char>(csr_partial_bytes(X, k, true));
   }
   if (!sd.partial[0]) { set_error("workspace layout overflow"); return SRP_ENOMEM; }
   // class statistics; the sketch of Xhat = X - E C is S X - (S E) C

@@ -154,10 +154,12 @@ int csc_build(const CsrView& A, CscView* out, Arena& keep, Arena& scratch, hipSt
 // A set *done makes the launch a no-op.
 int csr_times_dense(const CsrView& A, const double* D, int ldd, int w, double* out, int ldo, const double* sub,
                     const int32_t* labels, const int* done, hipStream_t st);
-// out (d x w) = A^T P straight from the rows, for the widths csr_tsum_ok
-// takes (partial: csr_tsum_bytes(A, w) bytes); wider matrices go through
-// the column copy below.
-bool csr_tsum_ok(const CsrView& A, int w);
+// Whether `products` products A^T P (w columns of P) are faster from the rows
+// (csr_tsum) than from the column copy below; copy_there: the copy is built
+// for another use.
+bool csr_rows_pay(const CsrView& A, int w, int products, bool copy_there);
+// out (d x w) = A^T P straight from the rows (partial: csr_tsum_bytes(A, w)
+// bytes).
 size_t csr_tsum_bytes(const CsrView& A, int w);
 int csr_tsum(const CsrView& A, const double* P, int ldp, int w, double* out, int ldo, double* partial,
              const int* done, hipStream_t st);

@@ -461,15 +461,16 @@ __global__ void __launch_bounds__(kRowsThreads) k_spmm_rows_lds(int64_t rows, in
 // workgroup's range, then the ranges in order), so the result is the same
 // bit for bit every time.
 //
-// Entries and P stream once.  22M entries in 1M rows, 1000 columns, 16
+// Entries and P stream once up to 16 columns of P; past that the blocks are
+// sorted again for every 16.  22M entries in 1M rows, 1000 columns, 16
 // columns of P: 347 us and 13 for the ranges' sums, bound by the issue of the
 // gather's instructions and the LDS latency of its short column runs.  The
 // column copy it replaces takes 1053 us to place, then 466 us of 128-byte
 // gathers of P at the last-level cache's rate and 62 us of sums; adding row
 // after row into LDS sums takes 792 us (random FP64 LDS adds, about 29
-// cycles for 44 lanes), one P column a lane instead of two 590 us.  Taken up to kTsMaxCols columns, where the
-// masks and two columns' sums a lane still fit; wider matrices go through
-// the copy.
+// cycles for 44 lanes), one P column a lane instead of two 590 us.
+// Taken up to kTsMaxCols columns, where the masks and two columns' sums a lane still
+// fit, by the rule of csr_rows_pay; other matrices go through the copy.
 constexpr int kTsMaxCols = 2048;
 constexpr int kTsThreads = 512;
 constexpr int kTsRows = 128;
@@ -713,7 +714,34 @@ static int ts_ranges(const CsrView& A, int tiles) {
   return (int)std::min(std::max<int64_t>(1, 2ll * num_cus() / tiles), std::max<int64_t>(1, blocks));
 }
 
-bool csr_tsum_ok(const CsrView& A, int w) { return w >= 1 && A.d <= kTsMaxCols; }
+static bool csr_tsum_ok(const CsrView& A, int w) { return w >= 1 && A.d <= kTsMaxCols; }
+
+// Whether `products` products A^T P (w columns of P) take less time from the
+// rows than from the column copy, its build included unless it is there
+// anyway.  Both are nearly linear in a few terms; in us, fitted on 64 to 2000
+// columns, 1 to 32 entries a row, 66000 and 300000 rows, 8 to 64 columns of P:
+//  * rows: a block of rows costs 7.4, its columns (by the columns of P a tile
+//    has) and entries more, 1.8 times as much where the sums leave room for one
+//    workgroup a CU; the ranges' sums go through memory;
+//  * copy: a segment's serial loads, or the gathers of P; the build's fixed
+//    cost, a chunk's rows in turn, and placing the entries.
+// The rows lose where a block has few entries for each column it looks at:
+// 300000 x 1000, 2 entries a row, 32 columns of P: 142 against 35 (the copy
+// built in 190); 16 entries, 16 columns 115 and 98; 32 entries 131 and 194; 1M
+// rows of 22 entries 360 and 528.
+bool csr_rows_pay(const CsrView& A, int w, int products, bool copy_there) {
+  if (!csr_tsum_ok(A, w)) return false;
+  const int GL = ts_lanes(w), tiles = (w + GL - 1) / GL, G = ts_ranges(A, tiles);
+  const double nnz = (double)A.nnz, x = A.d * GL / 16.0;
+  const double blocks = (double)std::max<int64_t>(1, std::max((A.n + kTsRows - 1) / kTsRows, A.nnz / kTsEntries));
+  double block = 7.4 + 0.0045 * std::min(x, 1024.0) + nnz / blocks * (0.001 + 1.5e-6 * x);
+  if (x > 1024.0) block *= 1.8;
+  const double rows = (blocks / G + 1.0) * block + 5.0 + (double)A.d * GL * G * tiles * 1e-6;
+  const double segment = std::min<double>(kCscSeg, nnz / A.d) * (w <= 8 ? 0.14 : 0.1);
+  const double copy = 5.0 + std::max(segment, nnz * 1e-6 * (w <= 16 ? 18.0 : 1.1 * w));
+  const double build = copy_there ? 0.0 : 130.0 + 0.19 * csc_chunk_rows(A.n, A.d, A.nnz) + 22e-6 * nnz;
+  return products * rows <= products * copy + build;
+}
 
 size_t csr_tsum_bytes(const CsrView& A, int w) {
   const int GL = ts_lanes(w), tiles = (w + GL - 1) / GL;

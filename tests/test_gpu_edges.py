@@ -461,3 +461,29 @@ def test_csr_products_of_few_long_rows_cost_no_more():
     W = torch.ones((2000, 8), dtype=torch.float64, device=DEV)
     few, many = csr_rows(1000, 2000, 1000), csr_rows(50000, 2000, 20)
     assert call_us(lambda: srp.srp_gram_pass_csr(few, W, few, W)) < 2.5 * call_us(lambda: srp.srp_gram_pass_csr(many, W, many, W))
+
+
+# both sides of the rule that sums A^T P from the rows or from the column copy:
+# few entries for a block's columns and many, P of one, two and four tiles
+@pytest.mark.parametrize("n,d,per_row,k", [(300000, 1000, 2, 64), (300000, 2000, 8, 32), (300000, 2000, 30, 16),
+                                           (300000, 1000, 2, 16), (66000, 2048, 40, 33), (66000, 2048, 3, 64)])
+def test_csr_products_on_either_route(n, d, per_row, k):
+    srp = _srp()
+    A = csr_rows(n, d, per_row)
+    W = torch.randint(-3, 4, (d, k), device=DEV).to(torch.float64)
+    J, _ = srp.srp_gram_pass_csr(A, W)
+    dense = torch.zeros((n, d), dtype=torch.float64, device=DEV)
+    dense.scatter_(1, A.col_idx.view(n, per_row).long(), A.values.view(n, per_row).double())
+    assert torch.equal(J, dense.t().contiguous() @ (dense @ W))   # whole numbers: exact whatever the order
+
+
+def test_csr_solve_iterations_take_the_faster_route():
+    """Two entries a row in 2000 columns: an iteration with eight times the
+    directions is bound by the same few entries."""
+    srp = _srp()
+    X, Y = csr_rows(300000, 2000, 2), csr_rows(300000, 2000, 2)
+    opt = srp.srp_default_options(max_iter=40, warm_start_iters=4)
+    def iteration(k):
+        infos = [srp.cca_solve_csr(X, Y, k, 0.1, 0.1, 6000, tol=1e-30, options=opt)[3] for _ in range(4)]
+        return min(i["ms_iterate"] / i["iterations"] for i in infos)
+    assert iteration(16) < 2.5 * iteration(2)

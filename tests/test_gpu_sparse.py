@@ -178,11 +178,11 @@ def test_csr_rejects_malformed_and_srht():
 # rows enough for the products with the transpose to be summed from the rows
 # (no column copy, W and the class sums' subtraction in LDS); P of one and of
 # two tiles of columns
-@pytest.mark.parametrize("method,k", [("rcg", 4), ("rtr", 12)])
-def test_cca_solve_csr_many_rows(method, k):
+@pytest.mark.parametrize("method,k,per_row", [("rcg", 4, 8), ("rtr", 12, 8), ("rtr", 12, 40)])
+def test_cca_solve_csr_many_rows(method, k, per_row):
     srp = _srp()
     n, dx, dy, lam = 70_000, 120, 90, 1e-3
-    X, Y = synth.cca_sparse(n, dx, dy, per_row=8, r=16, seed=4, dtype=np.float32)
+    X, Y = synth.cca_sparse(n, dx, dy, per_row=per_row, r=16, seed=4, dtype=np.float32)
     Xd, Yd = dense(X), dense(Y)
     sig_true, _, _ = direct.cca_direct(Xd, Yd, lam, lam)
     opt = srp.srp_default_options(method=method, max_iter=2000)
