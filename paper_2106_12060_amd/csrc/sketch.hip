@@ -206,9 +206,21 @@ __global__ void __launch_bounds__(512) k_cs_gather(const T* __restrict__ A, int 
       for (int j = 0; j < V; ++j) acc[j] += g * v[j];
     }
   }
+  Acc* o = out + (int64_t)b * d + c0;
+  if (whole) {
+    // whole pieces, 16 bytes at a time: sketches of more buckets than rows
+    // are bound by their stores (119 x 9427 BF16 to 11602: one store a column
+    // 302 us a call, so 142)
+    typedef Acc piece_t __attribute__((ext_vector_type(V), aligned(sizeof(Acc))));
+    piece_t q;
 #pragma unroll
-  for (int j = 0; j < V; ++j)
-    if (c0 + j < d) out[(int64_t)b * d + c0 + j] = acc[j];
+    for (int j = 0; j < V; ++j) q[j] = acc[j];
+    *reinterpret_cast<piece_t*>(o) = q;
+  } else {
+#pragma unroll
+    for (int j = 0; j < V; ++j)
+      if (c0 + j < d) o[j] = acc[j];
+  }
 }
 
 size_t countsketch_ws_bytes(int64_t n, int s) {

@@ -487,3 +487,12 @@ def test_csr_solve_iterations_take_the_faster_route():
         infos = [srp.cca_solve_csr(X, Y, k, 0.1, 0.1, 6000, tol=1e-30, options=opt)[3] for _ in range(4)]
         return min(i["ms_iterate"] / i["iterations"] for i in infos)
     assert iteration(16) < 2.5 * iteration(2)
+
+
+def test_countsketch_of_few_bf16_rows_costs_no_more():
+    """More buckets than rows: the sketch's FP32 stores are the work, the same
+    for BF16 and FP32 rows."""
+    srp = _srp()
+    A = torch.randn((119, 9427), device=DEV)
+    B = A.to(torch.bfloat16)
+    assert call_us(lambda: srp.srp_countsketch(B, 11602, 5)) < 1.35 * call_us(lambda: srp.srp_countsketch(A, 11602, 5))
