@@ -1143,6 +1143,15 @@ __global__ void __launch_bounds__(256) k_chol_step(double* __restrict__ G, int d
 }
 
 
+// Past this many trailing 64-column tiles a step's products go to the GEMM:
+// k_chol_step forms R's column blocks again in every tile, three products for
+// one, which costs more than the launches it saves.  Factor calls, us, of 1.02 d x d
+// FP32 sketches with the tiles at every step, with the GEMM past 110, and
+// with the GEMM at every step and R^-1 on a second stream: d = 7168 20350,
+// 20350, 20830; 9000 38850, 38310, 39010; 12288 99290, 96510, 95470; 16384
+// 251500, 241900, 246700 (GEMM past 48 instead: d = 5120 9260 for 8660).
+constexpr int kStepTiles = 110;
+
 // Split of the sketch Gram over the s rows: about 256 workgroups of the
 // big-tile kernel over the upper 128 x 128 tiles (measured best: d = 1000,
 // s = 4000 splits 8 ways, d = 2000, s = 8000 2 ways), each contraction at
@@ -1256,15 +1265,35 @@ int sketch_factor_run(const void* SA, int dtype, int s, int d, double lambda, do
                        R, X);
     SRP_LAUNCH_CHECK();
   }
-  // Right-looking blocked Cholesky, 64 columns a launch, and R^-1 a column
-  // block behind it.
+  // Right-looking blocked Cholesky, 64 columns a launch (the first columns of
+  // a large matrix four), and R^-1 a column block behind it.
   SRP_TRY(allow_dynamic_lds((const void*)k_potrf_block, sizeof(CholLds)));
   SRP_TRY(allow_dynamic_lds((const void*)k_chol_step, sizeof(CholLds)));
   hipLaunchKernelGGL(k_potrf_block, dim3(1), dim3(256), sizeof(CholLds), st, G, (int64_t)d, 0, std::min(64, d), R, Dinv,
                      flag_dev);
   SRP_LAUNCH_CHECK();
   for (int kb = 0; kb < tiles; ++kb) {
-    const int T = tiles - kb - 1, ntiles = T * (T + 1) / 2;   // block columns past this one, their tiles
+    const int T = tiles - kb - 1, k0 = kb * 64, rest = d - k0 - 64;
+    int ntiles = T * (T + 1) / 2;   // block columns past this one, their tiles
+    if (T > kStepTiles) {
+      GemmArgs t{};   // R_k. = R_kk^-T G_k.
+      t.m = 64; t.n = rest; t.kk = 64; t.alpha = 1.0; t.beta = 0.0;
+      t.A = Dinv + (size_t)kb * 4096; t.lda = 64; t.ta = true;
+      t.B = G + (int64_t)k0 * d + k0 + 64; t.ldb = d; t.tb = false;
+      t.C = R + (int64_t)k0 * d + k0 + 64; t.ldc = d;
+      SRP_TRY(gemm_f64(t, st));
+      GemmArgs u{};   // the trailing triangle
+      u.m = rest; u.n = rest; u.kk = 64; u.alpha = -1.0; u.beta = 1.0;
+      u.A = t.C; u.lda = d; u.ta = true;
+      u.B = t.C; u.ldb = d; u.tb = false;
+      u.C = G + (int64_t)(k0 + 64) * d + k0 + 64; u.ldc = d;
+      u.upper_only = true;
+      SRP_TRY(gemm_f64(u, st));
+      hipLaunchKernelGGL(k_potrf_block, dim3(1), dim3(256), sizeof(CholLds), st, G, (int64_t)d, k0 + 64,
+                         std::min(64, rest), R, Dinv + (size_t)(kb + 1) * 4096, flag_dev);
+      SRP_LAUNCH_CHECK();
+      ntiles = 0;
+    }
     hipLaunchKernelGGL(k_chol_step, dim3(ntiles + 4 * kb + 1), dim3(256), sizeof(CholLds), st, G, d, kb, ntiles, Dinv,
                        R, X, flag_dev);
     SRP_LAUNCH_CHECK();

@@ -496,3 +496,21 @@ def test_countsketch_of_few_bf16_rows_costs_no_more():
     A = torch.randn((119, 9427), device=DEV)
     B = A.to(torch.bfloat16)
     assert call_us(lambda: srp.srp_countsketch(B, 11602, 5)) < 1.35 * call_us(lambda: srp.srp_countsketch(A, 11602, 5))
+
+
+# the first steps' products by the GEMM: one such step (the last column block
+# of a single column), three, and the largest without
+@pytest.mark.parametrize("d", [7105, 7300, 7104])
+def test_sketch_factor_large(d):
+    srp = _srp()
+    A = torch.randn((d + 70, d), device=DEV, dtype=torch.float64)
+    R, Rinv = srp.srp_sketch_factor(A, 1.0)
+    assert not torch.tril(R, -1).any() and not torch.tril(Rinv, -1).any()
+    G = A.t().contiguous() @ A + torch.eye(d, device=DEV, dtype=torch.float64)
+    # bounds of test_sketch_factor_block_edges
+    u = 2.0 ** -53
+    Ra, Aa = R.abs(), A.abs()
+    bound = 4 * (3 * d + 8) * u * (Ra.t().contiguous() @ Ra + Aa.t().contiguous() @ Aa)
+    assert torch.all((R.t().contiguous() @ R - G).abs() <= bound)
+    W = Rinv.abs() @ Ra
+    assert torch.all((Rinv @ R - torch.eye(d, device=DEV, dtype=torch.float64)).abs() <= 4 * (d + 8) * u * (W @ W))
