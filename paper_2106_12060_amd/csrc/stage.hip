@@ -203,7 +203,9 @@ __global__ void k_fp8_scales(const uint32_t* __restrict__ amax_bits, int d, doub
   const double a = (double)__uint_as_float(amax_bits[c]);
   int e = 0;
   if (a > 0.0) {
-    e = (int)ceil(log2(a / 448.0));
+    // an infinity: the largest exponent there is (448 2^1015 is still finite),
+    // not a search for it from the integer that infinity converts to
+    e = (int)fmin(ceil(log2(a / 448.0)), 1016.0);
     while (a > 448.0 * ldexp(1.0, e)) ++e;
     while (a <= 448.0 * ldexp(1.0, e - 1)) --e;
   }

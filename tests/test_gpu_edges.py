@@ -514,3 +514,20 @@ def test_sketch_factor_large(d):
     assert torch.all((R.t().contiguous() @ R - G).abs() <= bound)
     W = Rinv.abs() @ Ra
     assert torch.all((Rinv @ R - torch.eye(d, device=DEV, dtype=torch.float64)).abs() <= 4 * (d + 8) * u * (W @ W))
+
+
+def test_fp8_staging_of_an_infinity():
+    """The column's scale is the largest power of two that 448 leaves finite
+    one step down; finite entries vanish beside it, the infinity saturates and
+    the other columns are as without it."""
+    srp = _srp()
+    X = np.random.default_rng(0).standard_normal((700, 40)).astype(np.float32)
+    ref, sc = quant.fp8_stage(X)
+    X[333, 7] = np.inf
+    codes, scales = srp.srp_stage_fp8(torch.from_numpy(X).to(DEV))
+    codes, scales = codes.cpu().numpy(), scales.cpu().numpy()
+    other = np.arange(40) != 7
+    np.testing.assert_array_equal(scales[other], sc[other])
+    np.testing.assert_array_equal(codes[:, other], ref[:, other])
+    assert scales[7] == 2.0 ** 1016
+    assert codes[333, 7] & 0x7F == 0x7E and not np.delete(codes[:, 7], 333).any()
