@@ -412,8 +412,8 @@ __global__ void __launch_bounds__(kF32Threads) k_pass_dma(const float* __restric
   // Loads of row block rbk into buffer xb: wave w moves chunks j = w, w + 16,
   // ... of every row.  One buffer resource per view and block; rows past n
   // lie past its num_records and read as zero.  A chunk's tail past the
-  // view's last column reads the next row's leading values (finite; they
-  // meet zero direction rows in P and land in J rows that are not stored).
+  // view's last column reads the next row's leading values, which
+  // clear_block takes out.
   auto issue_block = [&](int rbk, float* xb) __attribute__((always_inline)) {
     const int64_t row0 = (int64_t)rbk * R;
     const int rows = (int)(n - row0 < R ? n - row0 : R);
@@ -433,6 +433,22 @@ __global__ void __launch_bounds__(kF32Threads) k_pass_dma(const float* __restric
     }
   };
 
+  // The columns between a view's last and its last tile's, zeroed by the wave
+  // that loaded them: they meet zero direction rows in P, but an infinity or a
+  // NaN of the next row would turn this row's P into NaN.
+  auto clear_block = [&](float* xb) __attribute__((always_inline)) {
+    static_assert(R == 8, "four rows a store, two stores");
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      const int c = (v ? d1 : d0) + l16, span = (v ? T1 : T0) * 16;
+      if (w == ((v ? nch : nch0) - 1) % kF32Waves && c < span) {
+        float* x = xb + g * pitch + (v ? T0 * 16 : 0) + c;
+        x[0] = 0.f;
+        x[4 * pitch] = 0.f;
+      }
+    }
+  };
+
   // per-lane operand bases (floats); slot i adds 16 (w + 16 i)
   const int base_b = (l16 & (R - 1)) * pitch + g + 16 * w;   // P phase: row l16 mod 8, column 4 s2 + g
   const int base_d = g * pitch + l16 + 16 * w;               // J phase: row g + 4 s, column l16
@@ -443,6 +459,7 @@ __global__ void __launch_bounds__(kF32Threads) k_pass_dma(const float* __restric
   if (rb < nrb) issue_block(rb, dsm);
   for (; rb < nrb; rb += gridDim.x) {
     __builtin_amdgcn_s_waitcnt(0);   // this wave's loads of the block have landed
+    clear_block(dsm + boff);
     __syncthreads();                 // ... and every wave's; the other buffer is free
     const float* xs = dsm + boff;
     if (rb + (int)gridDim.x < nrb) issue_block(rb + gridDim.x, dsm + (R * pitch - boff));

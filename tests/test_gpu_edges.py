@@ -531,3 +531,22 @@ def test_fp8_staging_of_an_infinity():
     np.testing.assert_array_equal(codes[:, other], ref[:, other])
     assert scales[7] == 2.0 ** 1016
     assert codes[333, 7] & 0x7F == 0x7E and not np.delete(codes[:, 7], 333).any()
+
+
+# the streamed pass of two views with many directions: the same with its rows
+@pytest.mark.parametrize("n,d0,d1,k", [(5003, 701, 598, 14), (33, 1500, 484, 10), (900, 1023, 1018, 16), (17, 1600, 79, 12)])
+def test_gram_pass_streamed_row_keeps_to_its_columns(n, d0, d1, k):
+    assert _srp().srp_gram_pass_kernel("f32", "f32", d0, d1, k) == "k_pass_dma"
+    srp = _srp()
+    rng = np.random.default_rng(n + d0)
+    for v, r, c in ((0, 8, 0), (0, 11, 0), (1, 16, 0), (1, 9, 1), (0, n - 1, 0), (1, 15, -1)):
+        A = [rng.choice([-1.0, 1.0], size=(n, d)).astype(np.float32) for d in (d0, d1)]
+        W = [rng.choice([-1.0, 1.0], size=(d, k)) for d in (d0, d1)]
+        A[v][r, c] = np.inf
+        with np.errstate(invalid="ignore"):
+            P = np.concatenate([a.astype(np.float64) @ w for a, w in zip(A, W)], axis=1)
+            ref = [a.T.astype(np.float64) @ P for a in A]
+        D = [torch.from_numpy(a).to(DEV) for a in A]
+        Wd = [torch.from_numpy(w).to(DEV) for w in W]
+        for g, q in zip(srp.srp_gram_pass(D[0], Wd[0], D[1], Wd[1]), ref):
+            np.testing.assert_array_equal(g.cpu().numpy(), q)
