@@ -34,7 +34,7 @@ int finish(hipStream_t st) {
 
 // The scratch goes back in stream order while the kernels run, so that one
 // wait ends the call (a wait before the free and one after it: 65 us for a
-// pass over 2000 x (60 + 40) in FP64, 45 now; its kernels take 22).
+// pass over 2000 x (60 + 40) in FP64, so 49; its kernels take 22).
 int finish(Scratch& ws) {
   (void)ws.give_back();
   return finish(ws.st);

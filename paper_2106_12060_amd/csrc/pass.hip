@@ -794,9 +794,9 @@ __device__ __forceinline__ float pipe_sum(const float* p) {
 // tiles (its groups that hold any), P from the producers' partials.  xs: the
 // block at this wave's first tile.  pq, pr: this lane's element of a row of
 // P for column l16 of the whole tiles and column q4 of the groups past them.
-// The operands are read two batches ahead of the products that use them (the
-// scheduling barriers keep them there), so that a wave does not wait for LDS
-// at every product.
+// The order of reads and products is the compiler's: reads two batches ahead
+// behind scheduling barriers come in bursts that hold up the loader's writes
+// (200000 x (1000 + 1000), k = 10: 364 us, 335 so).
 template <class S, int NV, int NACT>
 __device__ __forceinline__ void pipe_consume(const float* __restrict__ xs, const float* __restrict__ part, int lane,
                                              const int (&pq)[2], const int (&pr)[3],
@@ -1101,7 +1101,11 @@ __global__ void __launch_bounds__(256) k_pass_reduce(const CT* __restrict__ part
 //     columns of A and the 32 of [P_0 | P_1] (16 a view) at a time on
 //     32x32x8 products, whose contraction is eight rows of a block; A comes
 //     transposed out of LDS (ds_read_b64_tr_b16: a lane's column, four rows).
-// Bounds: the row stream (5.3 to 5.7 TB/s); narrow rows, the chain of a step.
+// Bounds: the row stream (5.3 to 5.7 TB/s) where the loader stays a block
+// ahead.  Two views whose widths are both no multiple of 8 have 64 loads a
+// block or more with 16 rows, past what bf_wait counts: the loader then waits
+// for the block it has just issued, and a step also for a trip to memory
+// (52344 x (532 + 348): 3.3 TB/s).
 // Measured, us, against eight waves that did both products in turn with A
 // read from LDS two bytes a lane: 200000 x (1000 + 1000), k = 10 230 -> 151;
 // 100000 x 2000, k = 16 96 -> 71; 52344 x (532 + 348), k = 9 83 -> 28;
@@ -1181,7 +1185,8 @@ __device__ __forceinline__ int bf_load(const unsigned short* a0, const unsigned 
   return cnt;
 }
 
-__device__ __forceinline__ void bf_wait(int n) {   // at most n (a multiple of 8) of this wave's loads outstanding
+// At most n (a multiple of 8) of this wave's loads outstanding; none past 56.
+__device__ __forceinline__ void bf_wait(int n) {
   switch (n) {
 #define SRP_VM(N) case N: __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8)); break;
     SRP_VM(8) SRP_VM(16) SRP_VM(24) SRP_VM(32) SRP_VM(40) SRP_VM(48) SRP_VM(56)
