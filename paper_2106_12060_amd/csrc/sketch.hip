@@ -377,13 +377,11 @@ __global__ void __launch_bounds__(1024) k_sel_rank(int64_t n_pad, uint64_t seed,
     bins[t] = m << 16 | (at & 0xFFFF);
   }
   __syncthreads();
-  if (!bad) {
-    const int shift = 31 - __clz(cap), slots = chunks * cap;
-#pragma unroll 8
-    for (int e = t; e < slots; e += 1024) {
-      const int at = bins[e >> shift], i = e & (cap - 1);
-      if (i < at >> 16) keys[(at & 0xFFFF) + i] = list[e];
-    }
+  if (!bad) {   // 1024 / chunks threads a chunk (a thread a place of the lists: 14 us more of a call)
+    const int shift = 10 - (31 - __clz(chunks)), c = t >> shift;
+    const int at = bins[c], m = at >> 16;
+    for (int i = t & ((1 << shift) - 1); i < m; i += 1 << shift)
+      keys[(at & 0xFFFF) + i] = list[(int64_t)c * cap + i];
   }
   __syncthreads();
   const int W = total, need = s - low;

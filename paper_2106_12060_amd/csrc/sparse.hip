@@ -16,6 +16,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace srp {
 
@@ -28,31 +29,33 @@ constexpr int kCscSeg = 256;
 // columns in [0, d) and strictly increasing.  Entries are only read inside
 // [0, nnz), whatever the pointers hold.  Sixteen lanes take a row's entries
 // together, so the indexes stream (one thread a row: 141 us for 22M entries
-// in 1M rows, its loads a cache line apart; so: 62 us); a wave walks `rows`
+// in 1M rows, its loads a cache line apart; so: 62 us); a wave walks ROWS
 // rows, four at a time.
+template <int ROWS>
 __global__ void __launch_bounds__(256) k_csr_check(int64_t n, int d, int64_t nnz, const int64_t* __restrict__ ptr,
-                                                   const int32_t* __restrict__ idx, int rows, int bit, int* bad) {
+                                                   const int32_t* __restrict__ idx, int bit, int* bad) {
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
-  const int64_t base = (blockIdx.x * 4ll + (threadIdx.x >> 6)) * rows;
+  const int64_t base = (blockIdx.x * 4ll + (threadIdx.x >> 6)) * ROWS;
   bool ok = true;
 #pragma unroll 4
-  for (int q = 0; q < rows; q += 4) {
+  for (int q = 0; q < ROWS; q += 4) {
     const int64_t i = base + q + g;
     if (i >= n) break;
     const int64_t p0 = ptr[i], p1 = ptr[i + 1];
     if (p0 >= 0 && p0 <= p1 && p1 <= nnz && (i != 0 || p0 == 0) && (i != n - 1 || p1 == nnz)) {
       int64_t e = p0 + c;
-      for (; e + 112 < p1; e += 128) {   // a long row: sixteen loads in flight
-        int j[8], prev[8];
+      if constexpr (ROWS < 64)
+        for (; e + 112 < p1; e += 128) {   // a long row: sixteen loads in flight
+          int j[8], prev[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          j[u] = idx[e + 16 * u];
-          prev[u] = idx[max(p0, e + 16 * u - 1)];
+          for (int u = 0; u < 8; ++u) {
+            j[u] = idx[e + 16 * u];
+            prev[u] = idx[max(p0, e + 16 * u - 1)];
+          }
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if ((e + 16 * u > p0 && j[u] <= prev[u]) || j[u] < 0 || j[u] >= d) ok = false;
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if ((e + 16 * u > p0 && j[u] <= prev[u]) || j[u] < 0 || j[u] >= d) ok = false;
-      }
       for (; e < p1; e += 16) {
         const int j = idx[e];
         const int prev = e > p0 ? idx[e - 1] : -1;
@@ -65,17 +68,22 @@ __global__ void __launch_bounds__(256) k_csr_check(int64_t n, int d, int64_t nnz
   if (!ok) atomicOr(bad, bit);
 }
 
-// A malformed matrix sets `bit` in *bad.  A wave takes up to 64 rows, as many
-// as have some 1400 entries together, and no more than leave four waves to
-// every SIMD (a CountSketch of 1000 rows of 4000 entries with 64 rows a wave,
-// 16 waves in serial loads: 1430 us a call; so 207).
+// A malformed matrix sets `bit` in *bad.  A wave takes 64 rows, 16 or 4: no
+// more than have some 1400 entries together, and than leave four waves to every
+// SIMD (a CountSketch of 1000 rows of 4000 entries with 64 rows a wave, 16 waves
+// in serial loads: 1430 us a call; so 207).
 int csr_validate(const CsrView& A, int bit, int* bad, hipStream_t st) {
-  const int64_t by_entries = 352 * A.n / std::max<int64_t>(1, A.nnz), by_rows = A.n / (64ll * num_cus());
-  const int rows = 4 * (int)std::min<int64_t>(16, std::max<int64_t>(1, std::min(by_entries, by_rows)));
-  const unsigned blocks = (unsigned)((A.n + 4ll * rows - 1) / (4 * rows));
-  hipLaunchKernelGGL(k_csr_check, dim3(blocks), dim3(256), 0, st, A.n, A.d, A.nnz, A.ptr, A.idx, rows, bit, bad);
-  SRP_LAUNCH_CHECK();
-  return SRP_OK;
+  auto launch = [&](auto rows_) -> int {
+    constexpr int ROWS = decltype(rows_)::value;
+    const unsigned blocks = (unsigned)((A.n + 4 * ROWS - 1) / (4 * ROWS));
+    hipLaunchKernelGGL((k_csr_check<ROWS>), dim3(blocks), dim3(256), 0, st, A.n, A.d, A.nnz, A.ptr, A.idx, bit, bad);
+    SRP_LAUNCH_CHECK();
+    return SRP_OK;
+  };
+  const int64_t rows = std::min<int64_t>(1408 * A.n / std::max<int64_t>(1, A.nnz), A.n / (16ll * num_cus()));
+  if (rows >= 64) return launch(std::integral_constant<int, 64>{});
+  if (rows >= 16) return launch(std::integral_constant<int, 16>{});
+  return launch(std::integral_constant<int, 4>{});
 }
 
 // ------------------------------------------------------- CSC build
