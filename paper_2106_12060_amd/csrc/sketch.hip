@@ -306,7 +306,7 @@ int countsketch_run(const void* A, int dtype, int64_t n, int d, int s, uint64_t 
 // it counted.  The window misses by chance (three samples in 10^7 of one row,
 // fewer of more; that a list does not fit is rarer yet): then one workgroup
 // selects over all keys by 8-bit digits, the same threshold later.  The row
-// sample of 2^19 from 2^20: 60 us a call; with room for half of such a window's
+// sample of 2^19 from 2^20: 53 us a call; with room for half of such a window's
 // keys that selection ran every time and took 1545, a radix select by 16-bit
 // digits over the whole card 149.
 struct SelectState {

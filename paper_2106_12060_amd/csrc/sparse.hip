@@ -727,27 +727,31 @@ static bool csr_tsum_ok(const CsrView& A, int w) { return w >= 1 && A.d <= kTsMa
 // Whether `products` products A^T P (w columns of P) take less time from the
 // rows than from the column copy, its build included unless it is there
 // anyway.  Both are nearly linear in a few terms; in us, fitted on 64 to 2000
-// columns, 1 to 32 entries a row, 66000 and 300000 rows, 8 to 64 columns of P:
-//  * rows: a block of rows costs 7.4, its columns (by the columns of P a tile
-//    has) and entries more, 1.8 times as much where the sums leave room for one
-//    workgroup a CU; the ranges' sums go through memory;
-//  * copy: a segment's serial loads, or the gathers of P; the build's fixed
-//    cost, a chunk's rows in turn, and placing the entries.
+// columns, 1 to 32 entries a row, 66000 to 3M rows, 8 to 64 columns of P:
+//  * rows: a block of rows costs 6 to 7.4, its columns (by the columns of P a
+//    tile has) and entries more, 1.8 times as much where the sums leave room for
+//    one workgroup a CU; the ranges' sums go through memory;
+//  * copy: a segment's serial loads, or the gathers of P, a quarter dearer once
+//    P is past the caches; the build's fixed cost, a chunk's rows in turn, the
+//    chunks' column counts, and placing the entries.
 // The rows lose where a block has few entries for each column it looks at:
 // 300000 x 1000, 2 entries a row, 32 columns of P: 142 against 35 (the copy
-// built in 190); 16 entries, 16 columns 115 and 98; 32 entries 131 and 194; 1M
-// rows of 22 entries 360 and 528.
+// built in 190); 16 entries, 16 columns 115 and 98; 32 entries 131 and 194; 1M x
+// 500, 10 entries, 16 columns 190 and 224 (505).
 bool csr_rows_pay(const CsrView& A, int w, int products, bool copy_there) {
   if (!csr_tsum_ok(A, w)) return false;
   const int GL = ts_lanes(w), tiles = (w + GL - 1) / GL, G = ts_ranges(A, tiles);
-  const double nnz = (double)A.nnz, x = A.d * GL / 16.0;
+  const double n = (double)A.n, nnz = (double)A.nnz, x = A.d * GL / 16.0;
   const double blocks = (double)std::max<int64_t>(1, std::max((A.n + kTsRows - 1) / kTsRows, A.nnz / kTsEntries));
-  double block = 7.4 + 0.0045 * std::min(x, 1024.0) + nnz / blocks * (0.001 + 1.5e-6 * x);
+  double block = (GL <= 8 ? 6.0 : 7.4) + 0.0045 * std::min(x, 1024.0) + nnz / blocks * (0.001 + 1.5e-6 * x);
   if (x > 1024.0) block *= 1.8;
   const double rows = (blocks / G + 1.0) * block + 5.0 + (double)A.d * GL * G * tiles * 1e-6;
   const double segment = std::min<double>(kCscSeg, nnz / A.d) * (w <= 8 ? 0.14 : 0.1);
-  const double copy = 5.0 + std::max(segment, nnz * 1e-6 * (w <= 16 ? 18.0 : 1.1 * w));
-  const double build = copy_there ? 0.0 : 130.0 + 0.19 * csc_chunk_rows(A.n, A.d, A.nnz) + 22e-6 * nnz;
+  const double far = 1.0 + 0.25 * std::min(1.0, std::max(0.0, (n - 3e5) / 7e5));
+  const double copy = 5.0 + std::max(segment, nnz * 1e-6 * (w <= 16 ? 18.0 : 1.1 * w) * far);
+  const double build = copy_there ? 0.0
+                                  : 130.0 + 0.19 * csc_chunk_rows(A.n, A.d, A.nnz) + 15e-6 * nnz +
+                                        30e-6 * std::max(0.0, nnz - 4e6) + 10e-6 * A.d * csc_nchunks(A);
   return products * rows <= products * copy + build;
 }
 
