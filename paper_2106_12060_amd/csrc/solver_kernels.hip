@@ -1906,7 +1906,8 @@ int launch_apply_rot(const ProbView& p, hipStream_t st) {
 }
 
 // Sign convention: flip column j of every block so that the entry of
-// largest magnitude in U_0[:, j] is positive (ties: lowest index).
+// largest magnitude in U_0[:, j] is positive (ties: lowest index).  A column
+// of NaNs has none and stays as it is.
 __global__ void __launch_bounds__(256) k_sign_fix(ProbView p) {
   const int j = blockIdx.x, k = p.k;
   const SideView& s0 = p.s[0];
@@ -1935,7 +1936,7 @@ __global__ void __launch_bounds__(256) k_sign_fix(ProbView p) {
   // One thread reads the winning entry's sign; every thread waits for it
   // before any write to the column (the thread that owns that row negates it).
   __shared__ int flip_sh;
-  if (threadIdx.x == 0) flip_sh = s0.U[(int64_t)bi[0] * k + j] < 0.0;
+  if (threadIdx.x == 0) flip_sh = bi[0] < s0.d && s0.U[(int64_t)bi[0] * k + j] < 0.0;
   __syncthreads();
   if (!flip_sh) return;
   for (int b = 0; b < p.nb; ++b) {

@@ -550,3 +550,25 @@ def test_gram_pass_streamed_row_keeps_to_its_columns(n, d0, d1, k):
         Wd = [torch.from_numpy(w).to(DEV) for w in W]
         for g, q in zip(srp.srp_gram_pass(D[0], Wd[0], D[1], Wd[1]), ref):
             np.testing.assert_array_equal(g.cpu().numpy(), q)
+
+
+# FP64 CCA whose last tile ends past the rows' pitch, after a call that filled
+# LDS with NaNs: the products of every iteration and of the finish, whose
+# rotation and signs follow from them, are those of the data alone
+@pytest.mark.parametrize("dx,dy", [(9, 177), (63, 65), (39, 152)])
+def test_cca_solve_after_nans_in_lds(dx, dy):
+    from oracle import direct, metrics
+    srp = _srp()
+    rng = np.random.default_rng(dx)
+    n, k, lam = 4000, 3, 1e-2
+    Z = rng.standard_normal((n, 6))
+    X = Z @ rng.standard_normal((6, dx)) + rng.standard_normal((n, dx))
+    Y = Z @ rng.standard_normal((6, dy)) + rng.standard_normal((n, dy))
+    sig_true, _, _ = direct.cca_direct(X, Y, lam, lam)
+    Xd, Yd = torch.from_numpy(X).to(DEV), torch.from_numpy(Y).to(DEV)
+    poison_lds()
+    U, V, sig, info = srp.cca_solve(Xd, Yd, k, lam, lam, 4 * dy, tol=1e-10, options=srp.srp_default_options(max_iter=2000))
+    Uh, Vh = U.cpu().numpy(), V.cpu().numpy()
+    assert info["status"] == 0
+    assert metrics.cca_rel_objective_error(Uh, Vh, X, Y, lam, lam, sig_true) < 1e-10
+    assert max(metrics.constraint_residual(Uh, X, lam), metrics.constraint_residual(Vh, Y, lam)) < 1e-11
