@@ -1678,7 +1678,9 @@ int launch_combine(const ProbView& p, hipStream_t st) {
 // L_b L_b^T = U_b^T B_b U_b, CCA forms C = L_0^-1 (U_0^T Kc_0) L_1^-T and its
 // SVD (Jacobi on [[0, C], [C^T, 0]]); FDA the eigen-decomposition of
 // L^-1 (W^T S_B W) L^-T.  Rotations R_b = L_b^-T (singular/eigen vectors)
-// are stored in the KK_ROT slots, sigma (descending) in sigma_out.
+// are stored in the KK_ROT slots, sigma (descending) in sigma_out.  Where a
+// Gram is not positive definite the rotations are the identity: the kernels
+// after this one read them all the same.
 __global__ void __launch_bounds__(64) k_ctrl_final(ProbView p, double* sigma_out) {
   extern __shared__ double sm[];
   __shared__ WaveJacobiScratch jsc;
@@ -1709,6 +1711,8 @@ __global__ void __launch_bounds__(64) k_ctrl_final(ProbView p, double* sigma_out
     wave_sync();
     if (!wave_chol(G[b], k, lane)) {
       if (lane == 0) { p.ctrl->status = SRP_ENOTSPD; p.ctrl->done = 1; }
+      for (int q = 0; q < nb; ++q)
+        for (int e = lane; e < kk2; e += 64) kkslot(p, q, KK_ROT)[e] = sdiv(e, k) == e - sdiv(e, k) * k ? 1.0 : 0.0;
       return;
     }
     wave_lower_inv(G[b], Li[b], k, lane);
