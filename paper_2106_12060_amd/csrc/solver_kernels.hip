@@ -1673,6 +1673,10 @@ int launch_combine(const ProbView& p, hipStream_t st) {
   return SRP_OK;
 }
 
+// What eigenvalues are ranked by: NaNs last, so that the ranks are a
+// permutation whatever the values (the order is used as an index).
+__device__ __forceinline__ double rank_key(double v) { return v == v ? v : -INFINITY; }
+
 // -------------------------------------------------------------- final
 // FP64 retraction onto the constraint and Rayleigh-Ritz rotation: with
 // L_b L_b^T = U_b^T B_b U_b, CCA forms C = L_0^-1 (U_0^T Kc_0) L_1^-T and its
@@ -1765,10 +1769,10 @@ __global__ void __launch_bounds__(64) k_ctrl_final(ProbView p, double* sigma_out
     wave_sync();
     wave_jacobi(JA, GV, GT, mg, lane, jsc);
     if (lane < mg) {
-      const double vi = JA[lane * mg + lane];
+      const double vi = rank_key(JA[lane * mg + lane]);
       int rank = 0;
       for (int j = 0; j < mg; ++j) {
-        const double vj = JA[j * mg + j];
+        const double vj = rank_key(JA[j * mg + j]);
         rank += (vj > vi) || (vj == vi && j < lane);
       }
       order[rank] = lane;
@@ -1832,10 +1836,10 @@ __global__ void __launch_bounds__(64) k_ctrl_final(ProbView p, double* sigma_out
   wave_jacobi(JA, JV, JT, m, lane, jsc);
   // order eigenvalues descending (rank of each by counting)
   if (lane < m) {
-    const double vi = JA[lane * m + lane];
+    const double vi = rank_key(JA[lane * m + lane]);
     int rank = 0;
     for (int j = 0; j < m; ++j) {
-      const double vj = JA[j * m + j];
+      const double vj = rank_key(JA[j * m + j]);
       rank += (vj > vi) || (vj == vi && j < lane);
     }
     order[rank] = lane;
@@ -2127,10 +2131,10 @@ __global__ void __launch_bounds__(256) k_rr_eig(const double* __restrict__ G, in
   }
   __syncthreads();
   if (tid < n) {
-    const double vi = A[tid * 64 + tid];
+    const double vi = rank_key(A[tid * 64 + tid]);
     int rank = 0;
     for (int j = 0; j < n; ++j) {
-      const double vj = A[j * 64 + j];
+      const double vj = rank_key(A[j * 64 + j]);
       rank += (vj > vi) || (vj == vi && j < tid);
     }
     order[rank] = tid;
