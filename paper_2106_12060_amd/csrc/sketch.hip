@@ -576,6 +576,7 @@ __global__ void __launch_bounds__(1024) k_srht_group(const int64_t* rows, int s,
   }
   __syncthreads();
   for (int b = t; b <= B; b += 1024) goff[b] = off[b];
+  __syncthreads();   // the offsets become the cursors
   for (int j = t; j < s; j += 1024) {
     const int64_t r = rows[j];
     const int pos = atomicAdd(&off[(int)(r & (B - 1))], 1);
